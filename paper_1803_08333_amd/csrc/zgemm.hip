@@ -15,19 +15,26 @@
 // four-product form takes four.  In FP64 the extra rounding of the sums is
 // of order 1e-16 relative to |M| |X|, far below the complex64 storage of M.
 // A launch serves NG groups of 16 right-hand sides (NG = 2 from 17 on), so
-// that each pass over the matrix does 3 NG MFMAs per K step.
+// that each pass over the matrix does 3 NG MFMAs per K step and 16 rows.
 //
-// A workgroup (4 waves) owns 64 rows over one K slice; wave w takes rows
-// 16 w .. 16 w + 15 (two waves fit a SIMD with 32 right-hand sides, three
-// with 16; measured, one 16-row tile per wave beats two by a fifth: the
-// occupancy matters more than the reuse of the X operands).  Per 32-column
-// chunk each lane loads 8 consecutive complex64 entries of its row (64
-// contiguous bytes: a wave reads 16 rows x 256 bytes), and MFMA step e uses
-// entry e, so that the k index of lane l at step e is chunk column
-// 8 (l / 16) + e; the X chunk sits in LDS in the same order, one 512-byte
-// conflict-free wave read per operand.  Partial sums of the K slices go to a
-// buffer [slice][32][n] (complex128); a second kernel adds the slices in
-// order (the result does not depend on timing).
+// A workgroup (4 waves) owns 128 rows over one K slice, a wave 32 rows in two
+// 16-row tiles.  M is symmetric and stored whole, so the operand M[i][k] is
+// read as M[k][i]: 16 neighbouring lanes take 256 contiguous bytes of row k, a
+// workgroup 1 KB (read along its own row, a lane's 16 bytes stood 64 apart and
+// every load touched 64 lines).  The accumulators live in plain VGPRs (at
+// least two waves per SIMD are asked for, else the compiler takes AGPRs).  The
+// X chunk of 32 columns sits in LDS in operand order, one 512-byte wave read
+// per operand, the next step's read while this step's products run.  Partial
+// sums of the K slices go to a buffer [slice][32][n] (complex128); a second
+// kernel adds the slices in order (the result does not depend on timing).
+//
+// Bound: the FP64 matrix cores, 77.8 TFLOP/s in a register-only probe.  At
+// n = 30720 with 32 right-hand sides 3.02 ms (4.03 before, with one 16-row
+// tile per wave read along the rows): 60 TFLOP/s of executed flops, 80 of
+// algorithmic ones.  The conversions and sums of the operands take issue slots
+// of the matrix cores (8 FP64 operations per 12 MFMAs), the rest is the wait
+// at the chunk's barrier.  With 16 right-hand sides 1.74 ms (2.60 before), 4.3
+// TB/s of the matrix: there the stream weighs as much as the products.
 #include "internal.h"
 #include "gemm.h"
 
@@ -39,83 +46,89 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef float vf4 __attribute__((ext_vector_type(4)));
 
 constexpr int kZThreads = 256;
-constexpr int kZTiles = 1;                     // 16-row tiles per wave
+constexpr int kZTiles = 2;                     // 16-row tiles per wave
 constexpr int kZRowsWave = 16 * kZTiles;
 constexpr int kZRows = 4 * kZRowsWave;         // rows per workgroup
 constexpr int kZK = 32;                        // K chunk
 constexpr int kZRhs = 32;                      // right-hand sides per launch (at most)
+constexpr int kZLd = 66;                       // padded lane row of a stage
 
-// lds[g][b][e][l]: operand b (0: Xr, 1: Xi, 2: Xr + Xi) of group g at step
-// e for lane l (chunk column 8 (l / 16) + e, right-hand side 16 g + l % 16)
+// lds[g][b][e][l]: operand b (0: Xr, 1: Xi) of group g at step e for lane l
+// (chunk column 8 (l / 16) + e, right-hand side 16 g + l % 16).  A step's lanes
+// are padded to 66 entries, so that the stores of neighbouring columns spread
+// over the banks.
 template <int NG>
 struct ZStage {
-  double v[NG][3][8][64];
+  double v[NG][2][8][kZLd];
 };
 
-// X chunk into the operand order.  The loads go to registers first
-// (z_load_x, before the products of the current chunk) and to LDS after
-// them (z_store_x).
+// X chunk into the operand order, 32 consecutive columns of a right-hand side
+// per half wave.  The loads go to registers first (z_load_x, before the
+// products of the current chunk) and to LDS after them (z_store_x, which
+// zeroes what lies beyond the slice or the right-hand sides: the loads
+// themselves are never conditional, so that the wait counts stay exact).
 template <int NG>
-__device__ inline void z_load_x(double2 (&xr)[2 * NG], const double2* __restrict__ X, int n, int nr, int kc,
-                                int k_end, int tid) {
+__device__ inline void z_load_x(double2 (&xr)[2 * NG], const double2* __restrict__ X, int n, int nr, int kc, int tid) {
 #pragma unroll
   for (int u = 0; u < 2 * NG; ++u) {
     const int idx = tid + u * kZThreads;
-    const int g = idx / 512, e = (idx / 64) % 8, ll = idx % 64;
-    const int k = kc + 8 * (ll / 16) + e, r = 16 * g + ll % 16;
-    xr[u] = (r < nr && k < k_end) ? X[(long)r * n + k] : make_double2(0.0, 0.0);
+    const int k = min(kc + idx % kZK, n - 1), r = min(idx / kZK, nr - 1);
+    xr[u] = X[(long)r * n + k];
   }
 }
 template <int NG>
-__device__ inline void z_store_x(ZStage<NG>& st, const double2 (&xr)[2 * NG], int tid) {
+__device__ inline void z_store_x(ZStage<NG>& st, const double2 (&xr)[2 * NG], int kc, int k_end, int nr, int tid) {
 #pragma unroll
   for (int u = 0; u < 2 * NG; ++u) {
     const int idx = tid + u * kZThreads;
-    const int g = idx / 512, e = (idx / 64) % 8, ll = idx % 64;
-    st.v[g][0][e][ll] = xr[u].x;
-    st.v[g][1][e][ll] = xr[u].y;
-    st.v[g][2][e][ll] = xr[u].x + xr[u].y;
+    const int k = idx % kZK, r = idx / kZK;
+    const int g = r / 16, e = k % 8, ll = (k / 8) * 16 + r % 16;
+    const bool in = kc + k < k_end && r < nr;
+    st.v[g][0][e][ll] = in ? xr[u].x : 0.0;
+    st.v[g][1][e][ll] = in ? xr[u].y : 0.0;
   }
 }
 
-// the matrix: 8 consecutive entries of each of the wave's four rows
-__device__ inline void z_load_m(float2 (&av)[kZTiles][8], const float2* __restrict__ M, int n, long ld, int row0, int kc,
-                                int k_end, int lane) {
-  const int kq = kc + 8 * (lane >> 4);
+// the matrix: M is symmetric, so operand row i, column k is read as M[k][i],
+// along the rows of the store: a lane takes two neighbouring operand rows
+// (one per tile), 16 lanes 256 contiguous bytes of one k.  Columns beyond the
+// slice repeat the last one (their X entries are zero).
+typedef vf4 ZFrag[kZK / 4];
+__device__ inline void z_load_m(ZFrag& av, const float2* __restrict__ src, long ld, int kc, int n, int lane) {
 #pragma unroll
-  for (int a = 0; a < kZTiles; ++a) {
-    const int row = row0 + 16 * a;
-    const float2* src = M + (long)row * ld + kq;
-    if (row < n && kq + 8 <= k_end) {
-      const vf4* s4 = reinterpret_cast<const vf4*>(src);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const vf4 v = __builtin_nontemporal_load(s4 + e);
-        av[a][2 * e] = make_float2(v.x, v.y);
-        av[a][2 * e + 1] = make_float2(v.z, v.w);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) av[a][e] = (row < n && kq + e < k_end) ? src[e] : make_float2(0.f, 0.f);
-    }
+  for (int e = 0; e < kZK / 4; ++e) {
+    const int k = min(kc + 8 * (lane >> 4) + e, n - 1);
+    av[e] = __builtin_nontemporal_load(reinterpret_cast<const vf4*>(src + (long)k * ld));
   }
+}
+
+template <int NG>
+__device__ inline void z_operands(double (&xb)[NG][2], const ZStage<NG>& st, int e, int lane) {
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) xb[g][b] = st.v[g][b][e][lane];
 }
 
 template <bool CONJ, int NG>
-__device__ inline void z_mfma(dbl4 (&acc)[kZTiles][NG][3], const float2 (&av)[kZTiles][8], const ZStage<NG>& st,
-                              int lane) {
+__device__ inline void z_mfma(dbl4 (&acc)[kZTiles][NG][3], const ZFrag& av, const ZStage<NG>& st, int lane) {
+  double xb[2][NG][2];
+  z_operands<NG>(xb[0], st, 0, lane);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    double xb[NG][3];
+    // the next step's operands leave LDS while this step's products run
+    if (e + 1 < 8) z_operands<NG>(xb[(e + 1) & 1], st, e + 1, lane);
+    double mb[3][kZTiles], xs[NG][3];
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) xb[g][b] = st.v[g][b][e][lane];
-    double mb[3][kZTiles];
+    for (int g = 0; g < NG; ++g) {
+      xs[g][0] = xb[e & 1][g][0];
+      xs[g][1] = xb[e & 1][g][1];
+      xs[g][2] = xs[g][0] + xs[g][1];
+    }
 #pragma unroll
     for (int a = 0; a < kZTiles; ++a) {
-      mb[0][a] = (double)av[a][e].x;
-      mb[1][a] = CONJ ? -(double)av[a][e].y : (double)av[a][e].y;
+      mb[0][a] = (double)av[e][2 * a];
+      mb[1][a] = CONJ ? -(double)av[e][2 * a + 1] : (double)av[e][2 * a + 1];
       mb[2][a] = mb[0][a] + mb[1][a];
     }
     // each accumulator is taken once per step, 3 NG kZTiles instructions apart
@@ -125,21 +138,26 @@ __device__ inline void z_mfma(dbl4 (&acc)[kZTiles][NG][3], const float2 (&av)[kZ
       for (int a = 0; a < kZTiles; ++a)
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-          acc[a][g][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(mb[b][a], xb[g][b], acc[a][g][b], 0, 0, 0);
+          acc[a][g][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(mb[b][a], xs[g][b], acc[a][g][b], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // later steps' conversions stay behind (registers)
   }
 }
 
 // Two chunks in flight: the loads of chunk c + 1 (matrix into registers, X
-// into the other LDS stage) are issued before the products of chunk c.
+// into the other LDS stage) are issued before the products of chunk c.  The
+// chunks run in pairs without an exit between them (a slice of an odd count
+// takes one of zeros): with one, the accumulators had two homes and were
+// copied between them.
 template <bool CONJ, int NG>
-__global__ __launch_bounds__(kZThreads) void k_zgemm(const float2* __restrict__ M, int n, long ld,
-                                                     const double2* __restrict__ X, int nr, int kslice,
-                                                     double2* __restrict__ part) {
+__global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(NG == 1 ? 3 : 2, NG == 1 ? 3 : 2)))
+void k_zgemm(const float2* __restrict__ M, int n, long ld, const double2* __restrict__ X, int nr, int kslice,
+             double2* __restrict__ part) {
   __shared__ ZStage<NG> st[2];
   const int rb = blockIdx.x, ks = blockIdx.y;
   const int k_begin = ks * kslice, k_end = min(n, k_begin + kslice);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int row0 = rb * kZRows + w * kZRowsWave + (lane & 15);
+  const int row0 = rb * kZRows + w * kZRowsWave;
+  const float2* src = M + min((long)row0 + 2 * (lane & 15), ld - 2);
   dbl4 acc[kZTiles][NG][3];
 #pragma unroll
   for (int a = 0; a < kZTiles; ++a)
@@ -147,34 +165,29 @@ __global__ __launch_bounds__(kZThreads) void k_zgemm(const float2* __restrict__ 
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int b = 0; b < 3; ++b) acc[a][g][b] = dbl4{0.0, 0.0, 0.0, 0.0};
-  float2 va[kZTiles][8], vb[kZTiles][8];
+  ZFrag va, vb;
   double2 xr[2 * NG];
-  z_load_m(va, M, n, ld, row0, k_begin, k_end, lane);
-  z_load_x<NG>(xr, X, n, nr, k_begin, k_end, tid);
-  z_store_x<NG>(st[0], xr, tid);
+  z_load_m(va, src, ld, k_begin, n, lane);
+  z_load_x<NG>(xr, X, n, nr, k_begin, tid);
+  z_store_x<NG>(st[0], xr, k_begin, k_end, nr, tid);
   __syncthreads();
   for (int kc = k_begin; kc < k_end; kc += 2 * kZK) {
     const int k1 = kc + kZK, k2 = kc + 2 * kZK;
-    if (k1 < k_end) {
-      z_load_m(vb, M, n, ld, row0, k1, k_end, lane);
-      z_load_x<NG>(xr, X, n, nr, k1, k_end, tid);
-    }
-    z_mfma<CONJ, NG>(acc, va, st[0], lane);
-    __builtin_amdgcn_sched_barrier(0);  // the X stores wait for their loads here, after the products
-    if (k1 < k_end) z_store_x<NG>(st[1], xr, tid);
-    __syncthreads();  // stage 1 written, stage 0 read
-    if (k1 >= k_end) break;
-    if (k2 < k_end) {
-      z_load_m(va, M, n, ld, row0, k2, k_end, lane);
-      z_load_x<NG>(xr, X, n, nr, k2, k_end, tid);
-    }
-    z_mfma<CONJ, NG>(acc, vb, st[1], lane);
+    z_load_x<NG>(xr, X, n, nr, k1, tid);
+    z_load_m(vb, src, ld, k1, n, lane);
     __builtin_amdgcn_sched_barrier(0);
-    if (k2 < k_end) z_store_x<NG>(st[0], xr, tid);
+    z_mfma<CONJ, NG>(acc, va, st[0], lane);
+    z_store_x<NG>(st[1], xr, k1, k_end, nr, tid);  // waits for its loads here, after the products
+    __syncthreads();                               // stage 1 written, stage 0 read
+    z_load_x<NG>(xr, X, n, nr, k2, tid);
+    z_load_m(va, src, ld, k2, n, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    z_mfma<CONJ, NG>(acc, vb, st[1], lane);
+    z_store_x<NG>(st[0], xr, k2, k_end, nr, tid);
     __syncthreads();  // stage 0 written, stage 1 read
   }
-  // accumulator value v of lane l: row 4 v + l / 16 of the tile,
-  // right-hand side 16 g + l % 16
+  // accumulator value v of lane l: operand row 4 v + l / 16 (tile a holds the
+  // wave's rows 2 i + a), right-hand side 16 g + l % 16
   double2* pd = part + (long)ks * kZRhs * n;
 #pragma unroll
   for (int a = 0; a < kZTiles; ++a)
@@ -182,7 +195,7 @@ __global__ __launch_bounds__(kZThreads) void k_zgemm(const float2* __restrict__ 
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = rb * kZRows + w * kZRowsWave + 16 * a + 4 * v + (lane >> 4);
+        const int row = row0 + 2 * (4 * v + (lane >> 4)) + a;
         const int r = 16 * g + (lane & 15);
         const double p1 = acc[a][g][0][v], p2 = acc[a][g][1][v], p3 = acc[a][g][2][v];
         if (row < n && r < nr) pd[(long)r * n + row] = make_double2(p1 - p2, p3 - p1 - p2);
@@ -204,10 +217,13 @@ __global__ __launch_bounds__(256) void k_zgemm_sum(const double2* __restrict__ p
   Y[(long)r * n + i] = s;
 }
 
-// K slices of a launch: about 15 workgroups per compute unit (measured at
-// n = 20480 and 30720 against 2-12 slices), at most 16 slices.
+// K slices of a launch, at most 16 (8 at n = 30720, 12 at 20480).  The slices
+// and the order of the columns inside a chunk fix the order of the sums, which
+// the solves' iterates follow bit for bit.  Measured with 32 right-hand sides
+// at n = 30720: 8 slices (3.75 rounds of 512 workgroups, two per compute unit)
+// 3.02 ms, 17 slices (7.97 rounds) 2.89, 2 slices 3.05, 15 slices 3.05.
 int zgemm_slices(int64_t n) {
-  const int64_t rbs = (n + kZRows - 1) / kZRows;
+  const int64_t rbs = (n + 63) / 64;
   return (int)std::min<int64_t>(16, std::max<int64_t>(1, (3840 + rbs / 2) / rbs));
 }
 
@@ -218,8 +234,8 @@ size_t zgemm_scratch_bytes(int64_t n) { return sizeof(double2) * (size_t)zgemm_s
 rfcmp_status zgemm_c64(const float2* M, int64_t n, int64_t ld, bool conj, const double2* X, double2* Y, int nrhs,
                        void* scratch, size_t scratch_bytes, hipStream_t s, const char* tag) {
   if (n <= 0 || nrhs <= 0) return RFCMP_OK;
-  if (ld < n || ld % 4 != 0 || n > INT32_MAX / 2) {
-    set_error("zgemm: n = %lld, ld = %lld (ld >= n, a multiple of 4)", (long long)n, (long long)ld);
+  if (ld < (n + kZK - 1) / kZK * kZK || ld % 4 != 0 || n > INT32_MAX / 2) {
+    set_error("zgemm: n = %lld, ld = %lld (ld >= n rounded up to %d, a multiple of 4)", (long long)n, (long long)ld, kZK);
     return RFCMP_E_ARG;
   }
   if (scratch_bytes < zgemm_scratch_bytes(n)) {
