@@ -225,6 +225,7 @@ __global__ __launch_bounds__(kAcaThreads) void k_aca(const AcaArgs a, int b0) {
       continue;
     }
     const float2 piv = Vk[bj];
+    __syncthreads();  // every thread has the pivot before its owner scales it
     const float dd = piv.x * piv.x + piv.y * piv.y;
     const float2 inv = make_float2(piv.x / dd, -piv.y / dd);
     double nv = 0.0, nu = 0.0;
