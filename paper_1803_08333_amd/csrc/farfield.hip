@@ -1,0 +1,335 @@
+// Far field and radar cross section of RWG currents (Sec. 4), FP64.
+//
+// F_r(d) = int j_r exp(-i k dhat_d . x) dS: on cell c the RWG current is
+// sum_i j_m sigma_i (x - v_i)/(2 A_c) (v_i opposite local edge i) and the
+// rule's weights sum to one, so F = sum_p J_r(p) exp(-i k dhat . x_p) over the
+// 7 C quadrature points, J_r(p) = w_q/2 sum_i sigma_i j_m (x_q - v_i), and
+// sigma_r(d) = k^2/(4 pi) |F - dhat (dhat . F)|^2 (unit incident amplitude).
+// With js != nullptr, j is the loop (divergence-free) part of the current and
+// js its star part: a loop current carries no net current, so its phase
+// factor is taken as exp(-i t) - 1 = -2 sin^2(t/2) - i sin t, without
+// cancellation at any k; js takes the plain phase.
+//
+// The sum is a product of the phases (directions x points) with the point
+// currents (points x 6 real columns per right-hand side) on the FP64 matrix
+// cores (v_mfma_f64_16x16x4): each lane forms the sine and cosine of one
+// direction and point, which is its own operand entry, and every right-hand
+// side shares them.  The current of a point is formed once per call
+// (k_ff_current) instead of once per direction.
+//
+// Bound: FP64 arithmetic, about 40 operations per sine and cosine and 24 per
+// right-hand side (6 columns, twice, as MFMA; padded to 16 columns), 7 C ndir
+// of each.  One workgroup takes 16 directions, a slice of the points and up to
+// 8 of the column groups; its four waves take every fourth group of four
+// points.  Level 4 (C = 5120), 362 directions, 4 currents: 65 us for the sums
+// and 15 for the two small kernels around them, 98 us a call (306 before, one
+// workgroup per direction and right-hand side, each forming every phase and
+// every point current again); C = 2352, 11 directions, 27 currents: 68 us a
+// call (84 before).
+#include <algorithm>
+
+#include "farpair.h"
+#include "internal.h"
+
+namespace rfcmp {
+namespace {
+
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+constexpr int kFfDirs = 16;         // directions per workgroup (an MFMA operand)
+// workgroups of a launch: what the chip holds at once (registers: 4, 3 or 2
+// per compute unit), since a second round would run nearly empty
+constexpr int ff_waves(int ng) { return ng == 1 ? 4 : ng == 2 ? 3 : 2; }
+constexpr int kFfDirChunk = 16384;  // directions per launch (bounds the partial sums)
+
+// sin and cos of t.  Up to |t| = 1e5 (a body of 16 000 wavelengths) the
+// nearest multiple of pi/2 is taken off with pi/2 as the sum of two doubles
+// (absolute error below 1e-21) and the rest, |r| <= pi/4, goes through the
+// Taylor series of both functions (the terms left out are below 2^-58 of
+// either); beyond, the library's.  About 35 operations where the library's
+// takes over 100.
+constexpr double kPio2Hi = 1.57079632679489655800e+00;
+constexpr double kPio2Lo = 6.12323399573676603587e-17;
+__device__ inline void ff_sincos(double t, double& sn, double& cs) {
+  if (!(fabs(t) <= 1e5)) {
+    sincos(t, &sn, &cs);
+    return;
+  }
+  const double n = rint(t * 0.63661977236758134308);
+  const double r = fma(-n, kPio2Lo, fma(-n, kPio2Hi, t));
+  const double z = r * r;
+  double a = 1.0 / 355687428096000.0;         // 1/17!
+  a = fma(a, z, -1.0 / 1307674368000.0);      // 1/15!
+  a = fma(a, z, 1.0 / 6227020800.0);          // 1/13!
+  a = fma(a, z, -1.0 / 39916800.0);           // 1/11!
+  a = fma(a, z, 1.0 / 362880.0);              // 1/9!
+  a = fma(a, z, -1.0 / 5040.0);               // 1/7!
+  a = fma(a, z, 1.0 / 120.0);
+  a = fma(a, z, -1.0 / 6.0);
+  const double s = fma(r * z, a, r);
+  double b = -1.0 / 6402373705728000.0;       // 1/18!
+  b = fma(b, z, 1.0 / 20922789888000.0);      // 1/16!
+  b = fma(b, z, -1.0 / 87178291200.0);        // 1/14!
+  b = fma(b, z, 1.0 / 479001600.0);           // 1/12!
+  b = fma(b, z, -1.0 / 3628800.0);            // 1/10!
+  b = fma(b, z, 1.0 / 40320.0);               // 1/8!
+  b = fma(b, z, -1.0 / 720.0);
+  b = fma(b, z, 1.0 / 24.0);
+  const double hz = 0.5 * z, w = 1.0 - hz;
+  const double c = w + fma(z * z, b, (1.0 - w) - hz);
+  const int q = (int)n;
+  const double u = (q & 1) ? c : s, v = (q & 1) ? s : c;
+  sn = (q & 2) ? -u : u;
+  cs = ((q + 1) & 2) ? -v : v;
+}
+
+// x [7 C][3] and the point currents J [7 C][ld], column 6 r + 2 k + (0: real,
+// 1: imaginary) of component k of right-hand side r; js (nullable) into Js.
+__global__ __launch_bounds__(256) void k_ff_current(int C, int N, int nr, int ld, const int* __restrict__ cell_edge,
+                                                    const float* __restrict__ sgn, const double* __restrict__ vtx,
+                                                    RuleArgs rule, const double2* __restrict__ j,
+                                                    const double2* __restrict__ js, double* __restrict__ x,
+                                                    double* __restrict__ J, double* __restrict__ Js) {
+  const long t = (long)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (long)C * kQ * nr) return;
+  const int r = (int)(t % nr);
+  const long p = t / nr;
+  const int c = (int)(p / kQ), q = (int)(p % kQ);
+  double P[9];
+  for (int k = 0; k < 9; ++k) P[k] = vtx[(long)c * 9 + k];
+  double2 jc[3], jsc[3];
+  double sg[3];
+  for (int i = 0; i < 3; ++i) {
+    const long m = (long)r * N + cell_edge[3 * c + i];
+    jc[i] = j[m];
+    jsc[i] = js ? js[m] : make_double2(0.0, 0.0);
+    sg[i] = 0.5 * (double)sgn[3 * c + i];
+  }
+  const double wq = rule.wd[q], b0 = rule.bary[q][0], b1 = rule.bary[q][1], b2 = rule.bary[q][2];
+  for (int k = 0; k < 3; ++k) {
+    const double xk = b0 * P[k] + b1 * P[3 + k] + b2 * P[6 + k];
+    if (r == 0) x[3 * p + k] = xk;
+    double cr = 0.0, ci = 0.0, dr = 0.0, di = 0.0;
+    for (int i = 0; i < 3; ++i) {
+      const double arm = sg[i] * (xk - P[3 * i + k]);
+      cr += arm * jc[i].x;
+      ci += arm * jc[i].y;
+      dr += arm * jsc[i].x;
+      di += arm * jsc[i].y;
+    }
+    const long o = p * ld + 6 * r + 2 * k;
+    *reinterpret_cast<double2*>(J + o) = make_double2(wq * cr, wq * ci);
+    if (js) *reinterpret_cast<double2*>(Js + o) = make_double2(wq * dr, wq * di);
+  }
+}
+
+// Partial sums of a slice of `ps` points (a multiple of 16) for 16 directions
+// and NG of the ng 16-column groups:
+// part[slice][tile][cos, sin][group][direction][column].  The columns of J
+// beyond 6 nr hold anything: a column only reaches itself.
+template <int NG, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ff_waves(NG))))
+void k_ff_sum(int P, int ndir, int ps, int ng, double kk, const double* __restrict__ dirs, const double* __restrict__ x,
+              const double* __restrict__ J, const double* __restrict__ Js, double* __restrict__ part) {
+  const int ld = 16 * ng, g0 = blockIdx.z * NG;
+  J += 16 * g0;
+  Js += 16 * g0;
+  __shared__ double red[2 * NG * 4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15;
+  const int d = min(blockIdx.x * kFfDirs + col, (unsigned)ndir - 1);
+  const double d0 = dirs[3 * d], d1 = dirs[3 * d + 1], d2 = dirs[3 * d + 2];
+  dbl4 ac[NG], as[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) ac[g] = as[g] = dbl4{0.0, 0.0, 0.0, 0.0};
+  const int p_end = min(P, (int)(blockIdx.y + 1) * ps);
+  // the operands of the next group are loaded while this one's phases and
+  // products run (a round trip to memory per group otherwise)
+  struct Operands {
+    double b[NG], bs[SPLIT ? NG : 1], x0, x1, x2;
+  };
+  auto load = [&](Operands& o, int p0) {
+    const long pc = min(p0 + (lane >> 4), P - 1);
+    o.x0 = x[3 * pc];
+    o.x1 = x[3 * pc + 1];
+    o.x2 = x[3 * pc + 2];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      o.b[g] = J[pc * ld + 16 * g + col];
+      if (SPLIT) o.bs[g] = Js[pc * ld + 16 * g + col];
+    }
+  };
+  auto products = [&](const Operands& o, int p0) {
+    const double ph = kk * (d0 * o.x0 + d1 * o.x1 + d2 * o.x2);
+    double sn, cs;
+    ff_sincos(ph, sn, cs);
+    double lc = cs;
+    if (SPLIT) {
+      double h, unused;
+      ff_sincos(0.5 * ph, h, unused);
+      lc = -2.0 * h * h;
+    }
+    if (p0 + (lane >> 4) >= p_end) sn = cs = lc = 0.0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      ac[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(lc, o.b[g], ac[g], 0, 0, 0);
+      as[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, o.b[g], as[g], 0, 0, 0);
+      if (SPLIT) {
+        ac[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(cs, o.bs[g], ac[g], 0, 0, 0);
+        as[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(sn, o.bs[g], as[g], 0, 0, 0);
+      }
+    }
+  };
+  Operands oa, ob;
+  int p0 = blockIdx.y * ps + 4 * w;
+  load(oa, p0);
+  for (; p0 < p_end; p0 += 32) {
+    load(ob, p0 + 16);
+    products(oa, p0);
+    load(oa, p0 + 32);
+    products(ob, p0 + 16);
+  }
+  // the four waves' sums, added in order; value v of lane l: direction
+  // 4 v + l / 16, column l % 16
+  for (int q = 1; q < 4; ++q) {
+    if (w == q)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          red[g * 4 + v][lane] = ac[g][v];
+          red[(NG + g) * 4 + v][lane] = as[g][v];
+        }
+    __syncthreads();
+    if (w == 0)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          ac[g][v] += red[g * 4 + v][lane];
+          as[g][v] += red[(NG + g) * 4 + v][lane];
+        }
+    __syncthreads();
+  }
+  if (w != 0) return;
+  double* o = part + ((long)blockIdx.y * gridDim.x + blockIdx.x) * (2 * ng * 256) + g0 * 256;
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      o[g * 256 + (4 * v + (lane >> 4)) * 16 + col] = ac[g][v];
+      o[(ng + g) * 256 + (4 * v + (lane >> 4)) * 16 + col] = as[g][v];
+    }
+}
+
+// The slices' sums in order (five interleaved sums, added in order), then
+// Re F = C_re + S_im, Im F = C_im - S_re (exp(-i t) = cos t - i sin t) and the
+// RCS.  One workgroup per 16 directions and right-hand side: threads
+// (part, cos or sin, direction, column).  F [nr][ndir_all][3], rcs
+// [nr][ndir_all] from direction dir0 on.
+constexpr int kFfParts = 5, kFfSums = 2 * kFfDirs * 6;
+__global__ __launch_bounds__(kFfParts * kFfSums) void k_ff_finish(int ndir, int ng, int nslice, double kk,
+                                                                  const double* __restrict__ dirs,
+                                                                  const double* __restrict__ part, long ndir_all,
+                                                                  long dir0, double2* __restrict__ F,
+                                                                  double* __restrict__ rcs) {
+  __shared__ double red[kFfParts][kFfSums];
+  const int t = threadIdx.x, q = t / kFfSums, e = t % kFfSums, r = blockIdx.y;
+  const int row = e / 6 % kFfDirs, b = e / (6 * kFfDirs), m = 6 * r + e % 6;  // column of the pass
+  const long stride = (long)gridDim.x * (2 * ng * 256);
+  const double* src = part + (long)blockIdx.x * (2 * ng * 256) + (b * ng + m / 16) * 256 + row * 16 + m % 16;
+  double v = 0.0;
+#pragma unroll 8
+  for (int u = q; u < nslice; u += kFfParts) v += src[u * stride];
+  red[q][e] = v;
+  __syncthreads();
+  if (q == 0)
+    for (int u = 1; u < kFfParts; ++u) v += red[u][e];
+  __syncthreads();
+  if (q == 0) red[0][e] = v;
+  __syncthreads();
+  const int d = blockIdx.x * kFfDirs + t;
+  if (t >= kFfDirs || d >= ndir) return;
+  const double* c = &red[0][6 * t];
+  const double* sn = &red[0][6 * (kFfDirs + t)];
+  double f[6];
+  for (int k = 0; k < 3; ++k) {
+    f[2 * k] = c[2 * k] + sn[2 * k + 1];
+    f[2 * k + 1] = c[2 * k + 1] - sn[2 * k];
+  }
+  const long o = (long)r * ndir_all + dir0 + d;
+  for (int k = 0; k < 3; ++k) F[3 * o + k] = make_double2(f[2 * k], f[2 * k + 1]);
+  if (rcs) {
+    const double dh[3] = {dirs[3 * d], dirs[3 * d + 1], dirs[3 * d + 2]};
+    const double pr = dh[0] * f[0] + dh[1] * f[2] + dh[2] * f[4];  // dhat . F
+    const double pi = dh[0] * f[1] + dh[1] * f[3] + dh[2] * f[5];
+    double s = 0.0;
+    for (int k = 0; k < 3; ++k) {
+      const double tr = f[2 * k] - dh[k] * pr, ti = f[2 * k + 1] - dh[k] * pi;
+      s += tr * tr + ti * ti;
+    }
+    rcs[o] = kk * kk / (4.0 * M_PI) * s;
+  }
+}
+
+template <int NG>
+void ff_launch(bool split, dim3 grid, hipStream_t s, int P, int ndir, int ps, int ng, double kk, const double* dirs,
+               const double* x, const double* J, const double* Js, double* part) {
+  if (split)
+    hipLaunchKernelGGL((k_ff_sum<NG, true>), grid, dim3(256), 0, s, P, ndir, ps, ng, kk, dirs, x, J, Js, part);
+  else
+    hipLaunchKernelGGL((k_ff_sum<NG, false>), grid, dim3(256), 0, s, P, ndir, ps, ng, kk, dirs, x, J, J, part);
+}
+
+}  // namespace
+
+rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrhs, const double* dirs, int ndir,
+                       double2* F, double* rcs, hipStream_t s) {
+  rfcmp_mesh m = op->mesh;
+  const int64_t C = m->h.C, N = m->h.N, P = C * kQ;
+  // right-hand sides per pass: all of them, fewer where the point currents
+  // would take more than 1 GB
+  const int64_t fit = std::max<int64_t>(1, (int64_t)(1 << 27) / (P * (js ? 2 : 1)) / 16 * 16 / 6);
+  const int per = (int)std::min<int64_t>({nrhs, 4096, fit});
+  // column groups per workgroup: the phases (about five groups' worth of
+  // products) are formed once per workgroup
+  const int need = (6 * per + 15) / 16;
+  int w = 1;
+  for (int c = 2; c <= 8; c *= 2)
+    if ((need + c - 1) / c * (5 + c) <= (need + w - 1) / w * (5 + w)) w = c;
+  const int nz = (need + w - 1) / w, ng = nz * w;
+  const int dmax = std::min(ndir, kFfDirChunk), tiles = (dmax + kFfDirs - 1) / kFfDirs;
+  const int64_t slices = std::max<int64_t>(1, std::min<int64_t>(256 * ff_waves(w) / (tiles * nz), P / (32 * (w + 1))));
+  const int ps = (int)(((P + slices - 1) / slices + 15) / 16 * 16);
+  const int ns = (int)((P + ps - 1) / ps);
+  const size_t nj = (size_t)P * 16 * ng, npart = (size_t)ns * tiles * 2 * ng * 256;
+  DevBuf buf;
+  RF_TRY(buf.alloc(sizeof(double) * (3 * (size_t)ndir + 3 * (size_t)P + nj * (js ? 2 : 1) + npart)));
+  double* part = buf.as<double>();
+  double* J = part + npart;
+  double* Js = J + nj;
+  double* x = J + nj * (js ? 2 : 1);
+  double* dd = x + 3 * P;
+  RF_HIP(hipMemcpyAsync(dd, dirs, sizeof(double) * 3 * ndir, hipMemcpyHostToDevice, s));
+  const auto sums = w == 1 ? ff_launch<1> : w == 2 ? ff_launch<2> : w == 4 ? ff_launch<4> : ff_launch<8>;
+  for (int r0 = 0; r0 < nrhs; r0 += per) {
+    const int nr = std::min(per, nrhs - r0);
+    const long tot = (long)P * nr;
+    hipLaunchKernelGGL(k_ff_current, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, (int)C, (int)N, nr, 16 * ng,
+                       m->d.cell_edge.as<int>(), m->d.sgn.as<float>(), m->d.vtx.as<double>(), rule_args(),
+                       j + (int64_t)r0 * N, js ? js + (int64_t)r0 * N : nullptr, x, J, Js);
+    for (int q0 = 0; q0 < ndir; q0 += kFfDirChunk) {
+      const int nd = std::min(kFfDirChunk, ndir - q0);
+      const unsigned nt = (unsigned)((nd + kFfDirs - 1) / kFfDirs);
+      sums(js != nullptr, dim3(nt, (unsigned)ns, (unsigned)nz), s, (int)P, nd, ps, ng, op->k, dd + 3L * q0, x, J, Js,
+           part);
+      hipLaunchKernelGGL(k_ff_finish, dim3(nt, (unsigned)nr), dim3(kFfParts * kFfSums), 0, s, nd, ng, ns, op->k,
+                         dd + 3L * q0, part, (long)ndir, (long)q0, F + (int64_t)r0 * ndir * 3,
+                         rcs ? rcs + (int64_t)r0 * ndir : nullptr);
+    }
+  }
+  RF_HIP(hipGetLastError());
+  RF_HIP(hipStreamSynchronize(s));
+  return RFCMP_OK;
+}
+
+}  // namespace rfcmp

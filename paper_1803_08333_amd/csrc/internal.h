@@ -300,6 +300,7 @@ rfcmp_status rhs_planewave_noalloc(rfcmp_op op, const double* khat, const double
                                    hipStream_t s);
 rfcmp_status rhs_gap(rfcmp_mesh m, const int32_t* edges, const double2* volts, int ngap, int nrhs, double2* e,
                      hipStream_t s);
+// farfield.hip
 // js != nullptr: j is the loop part and js the star part of the current
 rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrhs, const double* dirs, int ndir,
                        double2* F, double* rcs, hipStream_t s);
