@@ -202,10 +202,11 @@ typedef struct rfcmp_op_s* rfcmp_op;
  *   V[c,c']  = (A_c A_c')^-1 int_c int_c' G_k dS dS'     (complex64, C x C)
  * with G_k = exp(ikR)/(4 pi R), so T_Phi = Sigma V Sigma^T.  Far pairs use the
  * 7x7-point rule in FP32; near pairs (see rfcmp_mesh_near_pairs) extract the
- * 1/R singularity in closed form in FP64.  T_A is formed tile by tile from
- * the cell pairs of each pair of 64-edge tiles and stored whole (both
- * triangles, exactly symmetric); the assembly needs no scratch beyond its
- * near-pair blocks (complex64, 72 bytes per near pair).  On the first call
+ * 1/R singularity in closed form in FP64.  T_A is formed from the cell pairs
+ * of pairs of large edge tiles and stored whole (both triangles, exactly
+ * symmetric); the assembly's scratch (at most 192 MB, or one tile pair's blocks
+ * where those are larger, and complex64 near-pair blocks of 72 bytes per near
+ * pair) does not grow with the mesh.  On the first call
  * for a mesh the projectors (sparse FP64 Cholesky factors of
  * Sigma^T Sigma, G_ll and, for outer_star = 1, G_tp, or their dense FP64
  * inverses: see rfcmp_options.projector) are set up on the device and

@@ -21,6 +21,7 @@
 // IEEE TAP 1984; Graglia, IEEE TAP 1993), the bounded rest with 7 x 7 points,
 // the outer cell is the lower-indexed one and self blocks are symmetrised.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <mutex>
 #include <thread>
@@ -34,26 +35,195 @@ namespace rfcmp {
 
 namespace {
 
-// ---------------------------------------------------------------- T_A tiles
-// One workgroup per pair of edge tiles (I <= J, kEdgeTile consecutive edges
-// each) forms the T_A entries (m in I, n in J) straight from the cell pairs
-// of the cells the two tiles touch: T_A[m,n] sums the four blocks
-// B[(m+-), (n+-)], and each cell pair adds its B entries to the entries of
-// its edges that lie in the tiles.  The sums run in LDS in a fixed order
-// without atomics: t1 = B[m+,n+] + B[m-,n-], t2 = B[m+,n-] + B[m-,n+], the
-// contributions whose row cell is c+ added in a first phase and those whose
-// row cell is c- in a second (each entry of t1 or t2 has one contribution
-// per phase), and T_A = t1 + t2 -- the same pairing whatever the order of
-// the cell pairs.  A diagonal tile takes each unordered cell pair once and
-// adds it to (m, n) and (n, m) from the same registers, and every other tile
-// pair writes its transpose too: T_A is stored whole and exactly
-// symmetric.  Near cell pairs (the self pairs among them)
-// take their blocks from k_near_pairs (NB, FP64 singular extraction, run
-// first) instead of the far rule: a tile pair that has near cell pairs
-// (tile_near) looks each of its cell pairs up in the sorted near partners of
-// its row cell.  V[c, c'] = I_0 of a far pair is written by the one
-// workgroup whose tiles are the home tiles of c and c' (k_near_pairs writes
-// the near ones).
+// ------------------------------------------------------- cell pairs, dense T_A
+// The dense blocks are formed in two passes over pairs (s <= t) of large edge
+// tiles (asm_tile consecutive edges each).  k_cell_pairs forms the 3 x 3 block
+// B[(a,i),(b,j)] of every cell pair (a, b) that the two tiles touch, into
+// scratch, and k_gather_ta sums T_A[m,n] = (B[m+,n+] + B[m-,n-]) +
+// (B[m+,n-] + B[m-,n+]) from it, for m in s and n in t, and writes both
+// triangles: T_A is stored whole and exactly symmetric.  Between two different
+// 64-edge tiles the cell of the lower one is the first cell of every pair;
+// inside one tile the lower-indexed cell is, for (m, n) and (n, m) alike.
+//
+// A cell that two tiles touch is formed once for each, so the pass forms
+// 1.1-1.2 times the unordered cell pairs at 2048-edge tiles, where 64-edge tiles
+// (whose sums fit LDS, the form of k_assemble_list) take 1.9 on the spheres and
+// 2.3 on the 96 x 48 torus.  Bound: FP32 VALU, about 28 instructions and three
+// transcendentals per point pair and a fifth of that per cell pair for its
+// entries (about 14 ms of the 17.4 at level 5); k_gather_ta streams the
+// scratch, which is kept small so that it comes from the memory-side cache.
+// Both passes: level 5 26.3 -> 17.4 ms, the torus 6.3 -> 3.5, level 2 0.074 ->
+// 0.026.  One launch that formed a batch and summed the one before it was slower
+// (its waves of the second kind took the places of the first).
+//
+// Near cell pairs (the self pairs among them) take their blocks from
+// k_near_pairs (NB, FP64 singular extraction, run first) instead of the far
+// rule: a tile pair that has near cell pairs (tile_near) looks each of its cell
+// pairs up in the sorted near partners of its first cell.  V[c, c'] = I_0 of a
+// far pair is written, with its mirror, where the tiles are those of the two
+// cells' home edges and c is the first (k_near_pairs writes the near ones).
+struct PairArgs {
+  const int* st_ptr;    // cells of each tile: st_cell[st_ptr[t] ..], ascending
+  const int* st_cell;
+  const int* st_span;   // per entry of st_cell: lowest | highest << 16 of the 64-edge tiles of its edges in the tile
+  const int2* st_pos;   // [N]: the slot 3 c + i of each edge in its c+ and c-, c counted in its tile
+  const int* cell_home; // 64-edge tile of each cell's local edge 0
+  const int4* pair;     // tile pairs (s, t)
+  const long* off;      // their blocks in the scratch (entries)
+  const uint8_t* near;  // tile pair t (t + 1)/2 + s has near cell pairs
+  const int* np_ptr;
+  const int* np_other;
+  const int* np_code;
+  const float2* NB;
+  const double* cen;
+  const float4* qoff;
+  const float4* fvoff;
+  const float* sgn;
+  RuleArgs rule;
+  float kk;
+  int N;
+  int hshift;           // 64-edge tiles per tile, as a shift
+  int p0;               // first tile pair of the launch
+  int rows;             // first cells per wave
+};
+
+constexpr int64_t kAsmScratch = 3 << 23;  // complex64 entries of a batch's blocks (192 MB)
+constexpr int64_t kAsmBatch = 4096;                // tile pairs of a batch
+
+__global__ __launch_bounds__(256) void k_cell_pairs(const PairArgs g, float2* __restrict__ B, float2* __restrict__ Vm,
+                                                    long ldV) {
+  const int pi = g.p0 + blockIdx.z, bx = blockIdx.x, by = blockIdx.y;
+  const int4 pr = g.pair[pi];
+  const int s = pr.x, t = pr.y;
+  const int a0 = g.st_ptr[s], na = g.st_ptr[s + 1] - a0, b0 = g.st_ptr[t], nb = g.st_ptr[t + 1] - b0;
+  const int b = bx * 64 + (threadIdx.x & 63);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = (by * 4 + w) * g.rows, r1 = min(r0 + g.rows, na);
+  if (bx * 64 >= nb || r0 >= na) return;
+  float2* out = B + g.off[pi];
+  const long ld = 3L * nb;
+  const int cb = g.st_cell[b0 + min(b, nb - 1)];
+  float4 qb[kQ], fb[3];
+  float sb[3];
+  double xb[3];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) qb[q] = g.qoff[(long)cb * kQ + q];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    fb[i] = g.fvoff[(long)cb * 3 + i];
+    sb[i] = g.sgn[(long)cb * 3 + i];
+    xb[i] = g.cen[(long)cb * 3 + i];
+  }
+  const int hb = g.cell_home[cb];
+  const bool near = g.near[(long)t * (t + 1) / 2 + s] != 0;
+  const bool in = b < nb, home_b = hb >> g.hshift == t;
+  const int hi_b = g.st_span[b0 + min(b, nb - 1)] >> 16;
+  for (int r = r0; r < r1; ++r) {
+    const int ca = g.st_cell[a0 + r];
+    // inside one tile a pair whose first cell has the higher index serves only
+    // edges of a lower 64-edge tile with edges of a higher one
+    if (s == t && r > b && (g.st_span[a0 + r] & 0xFFFF) >= hi_b) continue;
+    float2* row = out + (3L * r) * ld + 3L * b;
+    int code = -1;
+    if (near) {  // binary search of cb among ca's near partners
+      int lo = g.np_ptr[ca], hi = g.np_ptr[ca + 1];
+      const int end = hi;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (g.np_other[mid] < cb)
+          lo = mid + 1;
+        else
+          hi = mid;
+      }
+      if (lo < end && g.np_other[lo] == cb) code = g.np_code[lo];
+    }
+    if (code >= 0) {
+      // near: B[(ca,i),(cb,j)] of the pair stored as (ca, cb) (code even) or (cb, ca)
+      const float2* nbk = g.NB + (long)(code >> 1) * 9;
+      if (in)
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int j = 0; j < 3; ++j) row[i * ld + j] = nbk[(code & 1) ? 3 * j + i : 3 * i + j];
+      continue;
+    }
+    const double* xa = g.cen + 3L * ca;
+    Moments M;
+    far_moments(g.qoff + (long)ca * kQ, qb, (float)(xa[0] - xb[0]), (float)(xa[1] - xb[1]), (float)(xa[2] - xb[2]),
+                g.rule, g.kk, M);
+    const int ha = g.cell_home[ca];
+    if (in && home_b && ha >> g.hshift == s && (ha < hb || (ha == hb && ca <= cb))) {
+      const float2 v = make_float2(M.i0r, M.i0i);
+      Vm[(long)ca * ldV + cb] = v;
+      Vm[(long)cb * ldV + ca] = v;
+    }
+    if (in)
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+          row[i * ld + j] = b_entry(M, g.fvoff[3L * ca + i], fb[j], g.sgn[3L * ca + i], sb[j]);
+  }
+}
+
+// One workgroup per pair of 64-edge tiles (I <= J) of a tile pair.  Workgroups
+// go round robin to the 8 XCDs: an XCD takes whole rows of 64-edge tiles, so
+// that the tiles that share B rows share an L2 (level 5: 6.4 -> 2.9 ms in all).
+__global__ __launch_bounds__(256) void k_gather_ta(const PairArgs g, const float2* __restrict__ Bs,
+                                                   float2* __restrict__ TA, long ldA) {
+  __shared__ float2 tile[kEdgeTile][kEdgeTile + 1];
+  const int per = 1 << (2 * g.hshift - 3), e0 = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int qi = g.p0 + blockIdx.y;
+  const int4 pr = g.pair[qi];
+  const int N = g.N;
+  const long m0 = ((long)(pr.x << g.hshift) + (e0 >> g.hshift)) * kEdgeTile;
+  const long n0 = ((long)(pr.y << g.hshift) + (e0 & ((1 << g.hshift) - 1))) * kEdgeTile;
+  if (m0 > n0 || n0 >= N) return;
+  const long ld = 3L * (g.st_ptr[pr.y + 1] - g.st_ptr[pr.y]);
+  const float2* B = Bs + g.off[qi];
+  const int2* pos = g.st_pos;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long n = n0 + lane;
+  const int2 c = pos[min(n, (long)N - 1)];
+  const bool diag = m0 == n0;
+  for (int u = 0; u < 16; u += 4) {
+    float2 pp[4], mm[4], pm[4], mp[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int2 r = pos[min(m0 + 16 * w + u + e, (long)N - 1)];
+      // the lower cell first inside one tile
+      auto at = [&](int a, int b) { return diag && a / 3 > b / 3 ? B[(long)b * ld + a] : B[(long)a * ld + b]; };
+      pp[e] = at(r.x, c.x);
+      mm[e] = at(r.y, c.y);
+      pm[e] = at(r.x, c.y);
+      mp[e] = at(r.y, c.x);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = 16 * w + u + e;
+      const float2 v = make_float2((pp[e].x + mm[e].x) + (pm[e].x + mp[e].x), (pp[e].y + mm[e].y) + (pm[e].y + mp[e].y));
+      if (m0 + row < N && n < N) TA[(m0 + row) * ldA + n] = v;
+      tile[row][lane] = v;
+    }
+  }
+  if (diag) return;
+  __syncthreads();
+  for (int row = w; row < kEdgeTile; row += 4)
+    if (n0 + row < N && m0 + lane < N) TA[(n0 + row) * ldA + m0 + lane] = tile[lane][row];
+}
+
+// ------------------------------------------- dense tiles of a compressed T_A
+// One workgroup per listed pair of 64-edge tiles (I <= J) forms the T_A entries
+// (m in I, n in J) straight from the cell pairs of the cells the two tiles
+// touch, and adds its B entries to the entries of its edges that lie in the
+// tiles.  The sums run in LDS in a fixed order without atomics: t1 = B[m+,n+] +
+// B[m-,n-], t2 = B[m+,n-] + B[m-,n+], the contributions whose row cell is c+
+// added in a first phase and those whose row cell is c- in a second (each entry
+// of t1 or t2 has one contribution per phase), and T_A = t1 + t2 -- the same
+// pairing whatever the order of the cell pairs.  A diagonal tile takes each
+// unordered cell pair once and adds it to (m, n) and (n, m) from the same
+// registers.  V entries of the home cells of I and J go into the block's own
+// dense V block.
 constexpr int kAsmThreads = 1024;
 struct CellL {
   float4 q[kQ];   // quadrature points minus centroid
@@ -65,7 +235,7 @@ struct CellL {
   int home;       // home tile
 };
 
-__global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* __restrict__ et_ptr,
+__global__ __launch_bounds__(kAsmThreads) void k_assemble_list(const int* __restrict__ et_ptr,
                                                              const int* __restrict__ et_cell,
                                                              const int* __restrict__ et_rows,
                                                              const int* __restrict__ cell_home,
@@ -73,30 +243,20 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* _
                                                              const float4* __restrict__ qoff,
                                                              const float4* __restrict__ fvoff,
                                                              const float* __restrict__ sgn, float kk,
-                                                             RuleArgs rule, const uint8_t* __restrict__ tile_near,
+                                                             RuleArgs rule,
                                                              const int* __restrict__ np_ptr,
                                                              const int* __restrict__ np_other,
                                                              const int* __restrict__ np_code,
                                                              const float2* __restrict__ NB,
-                                                             float2* __restrict__ TA, long ldA,
-                                                             float2* __restrict__ Vm, long ldV,
+                                                             float2* __restrict__ TA,
+                                                             float2* __restrict__ Vm,
                                                              const int2* __restrict__ lst,
                                                              const long* __restrict__ vdoff,
                                                              const int* __restrict__ cstart,
                                                              const int* __restrict__ ipc,
                                                              const float2* __restrict__ NV) {
   const long t = blockIdx.x;
-  int I, Jt;
-  if (lst) {  // list mode: the dense blocks of a compressed operator
-    I = lst[t].x;
-    Jt = lst[t].y;
-  } else {
-    long J = (long)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-    while (J * (J + 1) / 2 > t) --J;
-    while ((J + 1) * (J + 2) / 2 <= t) ++J;
-    I = (int)(t - J * (J + 1) / 2);
-    Jt = (int)J;
-  }
+  const int I = lst[t].x, Jt = lst[t].y;
   extern __shared__ __align__(16) unsigned char smem[];
   float2(*t1)[kEdgeTile] = reinterpret_cast<float2(*)[kEdgeTile]>(smem);
   float2(*t2)[kEdgeTile] = reinterpret_cast<float2(*)[kEdgeTile]>(smem + sizeof(float2) * kEdgeTile * kEdgeTile);
@@ -128,12 +288,8 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* _
   __syncthreads();
   const CellL* cI = cl;
   const CellL* cJ = diag ? cl : cl + nI;
-  const bool any_near = lst ? true : tile_near[t] != 0;
-  // list mode: V entries of the home cells of I and J, into the block's
-  // own dense V block (rows the cells homed in I, columns those in J)
-  const long vbase = lst ? vdoff[t] : 0;
-  const int vcI = lst ? cstart[I] : 0, vcJ = lst ? cstart[Jt] : 0;
-  const int vnJ = lst ? cstart[Jt + 1] - vcJ : 0;
+  const long vbase = vdoff[t];
+  const int vcI = cstart[I], vcJ = cstart[Jt], vnJ = cstart[Jt + 1] - vcJ;
   const int total = nI * nJ;
   for (int base = 0; base < total; base += kAsmThreads) {
     const int p = base + tid;
@@ -149,7 +305,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* _
       const CellL& Bc = cJ[b];
       self = A.gid == Bc.gid;
       int code = -1;
-      if (any_near) {  // binary search of Bc among A's near partners
+      {  // binary search of Bc among A's near partners
         int lo = np_ptr[A.gid], hi = np_ptr[A.gid + 1];
         while (lo < hi) {
           const int mid = (lo + hi) >> 1;
@@ -167,7 +323,7 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* _
         for (int i = 0; i < 3; ++i)
 #pragma unroll
           for (int j = 0; j < 3; ++j) bv[i][j] = nb[(code & 1) ? 3 * j + i : 3 * i + j];
-        if (lst && A.home == I && Bc.home == Jt) {
+        if (A.home == I && Bc.home == Jt) {
           const float2 v = NV[code >> 1];
           const int la = ipc[A.gid] - vcI, lb = ipc[Bc.gid] - vcJ;
           Vm[vbase + (long)la * vnJ + lb] = v;
@@ -179,14 +335,9 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* _
                         (float)(A.cen[2] - Bc.cen[2]), rule, kk, M);
         if (A.home == I && Bc.home == Jt) {
           const float2 v = make_float2(M.i0r, M.i0i);
-          if (lst) {
-            const int la = ipc[A.gid] - vcI, lb = ipc[Bc.gid] - vcJ;
-            Vm[vbase + (long)la * vnJ + lb] = v;
-            if (diag) Vm[vbase + (long)lb * vnJ + la] = v;
-          } else {
-            Vm[(long)A.gid * ldV + Bc.gid] = v;
-            Vm[(long)Bc.gid * ldV + A.gid] = v;
-          }
+          const int la = ipc[A.gid] - vcI, lb = ipc[Bc.gid] - vcJ;
+          Vm[vbase + (long)la * vnJ + lb] = v;
+          if (diag) Vm[vbase + (long)lb * vnJ + la] = v;
         }
 #pragma unroll
         for (int i = 0; i < 3; ++i)
@@ -230,27 +381,11 @@ __global__ __launch_bounds__(kAsmThreads) void k_assemble_ta(int N, const int* _
       __syncthreads();
     }
   }
-  if (lst) {  // the tile as it is (both triangles for a diagonal tile; zero beyond N)
-    float2* out = TA + t * (long)(kEdgeTile * kEdgeTile);
-    for (int e = tid; e < kEdgeTile * kEdgeTile; e += kAsmThreads) {
-      const int r = e / kEdgeTile, c = e % kEdgeTile;
-      out[e] = make_float2(t1[r][c].x + t2[r][c].x, t1[r][c].y + t2[r][c].y);
-    }
-    return;
-  }
+  // the tile as it is (both triangles for a diagonal tile; zero beyond N)
+  float2* out = TA + t * (long)(kEdgeTile * kEdgeTile);
   for (int e = tid; e < kEdgeTile * kEdgeTile; e += kAsmThreads) {
     const int r = e / kEdgeTile, c = e % kEdgeTile;
-    const long m = (long)I * kEdgeTile + r, n = (long)Jt * kEdgeTile + c;
-    if (m < N && n < N)
-      TA[m * ldA + n] = make_float2(t1[r][c].x + t2[r][c].x, t1[r][c].y + t2[r][c].y);
-  }
-  if (!diag) {  // the transpose: T_A is stored whole
-    for (int e = tid; e < kEdgeTile * kEdgeTile; e += kAsmThreads) {
-      const int c = e / kEdgeTile, r = e % kEdgeTile;
-      const long m = (long)I * kEdgeTile + r, n = (long)Jt * kEdgeTile + c;
-      if (m < N && n < N)
-        TA[n * ldA + m] = make_float2(t1[r][c].x + t2[r][c].x, t1[r][c].y + t2[r][c].y);
-    }
+    out[e] = make_float2(t1[r][c].x + t2[r][c].x, t1[r][c].y + t2[r][c].y);
   }
 }
 
@@ -312,98 +447,126 @@ __device__ Pot tri_potentials(const double P[3][3], const double r[3]) {
   return out;
 }
 
-// One thread per near pair (c <= c'): outer cell c, inner cell c'.
-__global__ __launch_bounds__(128) void k_near_pairs(long npairs, const int* __restrict__ pairs,
+// Near pairs (c <= c'): outer cell c, inner cell c'.  A workgroup takes
+// kNearPairs pairs: first one thread per (pair, outer point) forms the
+// closed-form potentials and one per (pair, point pair) the bounded part's
+// kernel, into LDS; then one thread per (pair, block entry) adds its terms in
+// the order of the points.  (One thread per pair doing all of it left a few
+// hundred waves on the chip, each a chain of 10^4 FP64 operations: 60 us at
+// level 2 and 124 at level 4, now 18 and 102.)  31 pairs fill the rounds of
+// every phase and leave room for three workgroups (level 4: 128 us with 15
+// pairs, 105 with 26, 117 with 36).
+constexpr int kNearPairs = 31;
+__global__ __launch_bounds__(256) void k_near_pairs(long npairs, const int* __restrict__ pairs,
                                                     const double* __restrict__ vtx,
                                                     const double* __restrict__ area,
                                                     const float* __restrict__ sgn, double kk,
                                                     RuleArgs rule, float2* __restrict__ NB,
                                                     float2* __restrict__ Vm, long ldV,
                                                     float2* __restrict__ NV) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= npairs) return;
-  const int c = pairs[2 * t], cp = pairs[2 * t + 1];
-  double Po[3][3], Pi[3][3];
-  for (int i = 0; i < 3; ++i)
-    for (int d = 0; d < 3; ++d) {
-      Po[i][d] = vtx[(long)c * 9 + 3 * i + d];
-      Pi[i][d] = vtx[(long)cp * 9 + 3 * i + d];
+  __shared__ double geo[kNearPairs][2][9];             // vertices of the outer and the inner cell
+  __shared__ double pts[kNearPairs][2][kQ][3];         // their quadrature points
+  __shared__ double pot[kNearPairs][kQ][4];            // S, W of the inner cell at the outer points
+  __shared__ double gk[kNearPairs][kQ * kQ][2];        // (exp(ikR) - 1)/R
+  __shared__ double blk[kNearPairs][9][2];
+  const long t0 = (long)blockIdx.x * kNearPairs;
+  const int np = (int)min((long)kNearPairs, npairs - t0), tid = threadIdx.x;
+  for (int e = tid; e < np * 18; e += 256) {
+    const int u = e / 18, k = e % 18, c = pairs[2 * (t0 + u) + k / 9];
+    geo[u][k / 9][k % 9] = vtx[(long)c * 9 + k % 9];
+  }
+  __syncthreads();
+  for (int e = tid; e < np * 2 * kQ * 3; e += 256) {
+    const int u = e / (2 * kQ * 3), side = e / (kQ * 3) % 2, q = e / 3 % kQ, d = e % 3;
+    const double* P = geo[u][side];
+    pts[u][side][q][d] = rule.bary[q][0] * P[d] + rule.bary[q][1] * P[3 + d] + rule.bary[q][2] * P[6 + d];
+  }
+  __syncthreads();
+  for (int e = tid; e < np * kQ; e += 256) {
+    const int u = e / kQ, p = e % kQ;
+    const Pot v = tri_potentials(reinterpret_cast<const double(*)[3]>(geo[u][1]), pts[u][0][p]);
+    pot[u][p][0] = v.S;
+    for (int d = 0; d < 3; ++d) pot[u][p][1 + d] = v.W[d];
+  }
+  // bounded part: (exp(ikR) - 1)/R = (-2 sin^2(kR/2) + i sin(kR))/R, ik at R = 0
+  for (int e = (tid + 128) % 256; e < np * kQ * kQ; e += 256) {
+    const int u = e / (kQ * kQ), p = e / kQ % kQ, q = e % kQ;
+    double rr[3];
+    for (int d = 0; d < 3; ++d) rr[d] = pts[u][0][p][d] - pts[u][1][q][d];
+    const double R = sqrt(rr[0] * rr[0] + rr[1] * rr[1] + rr[2] * rr[2]);
+    double gr, gi;
+    if (R > 0.0) {
+      const double sh = sin(0.5 * kk * R);
+      gr = -2.0 * sh * sh / R;
+      gi = sin(kk * R) / R;
+    } else {
+      gr = 0.0;
+      gi = kk;
     }
-  const double Ain = area[cp];
-  double xo[kQ][3], xi[kQ][3];
-  for (int q = 0; q < kQ; ++q)
-    for (int d = 0; d < 3; ++d) {
-      xo[q][d] = rule.bary[q][0] * Po[0][d] + rule.bary[q][1] * Po[1][d] + rule.bary[q][2] * Po[2][d];
-      xi[q][d] = rule.bary[q][0] * Pi[0][d] + rule.bary[q][1] * Pi[1][d] + rule.bary[q][2] * Pi[2][d];
-    }
-  double vr = 0.0, vi = 0.0;
-  double br[3][3] = {}, bi[3][3] = {};
-  for (int p = 0; p < kQ; ++p) {
-    const Pot pot = tri_potentials(Pi, xo[p]);
-    const double wp = rule.wd[p];
-    // singular part: int_c' (r' - r_j)/R = W + (x_p - r_j) S
-    vr += wp * pot.S / Ain;
-    double arm[3][3];  // x_p - r_i (outer)
-    for (int i = 0; i < 3; ++i)
-      for (int d = 0; d < 3; ++d) arm[i][d] = xo[p][d] - Po[i][d];
-    for (int j = 0; j < 3; ++j) {
-      double inner[3];
-      for (int d = 0; d < 3; ++d) inner[d] = pot.W[d] + (xo[p][d] - Pi[j][d]) * pot.S;
-      for (int i = 0; i < 3; ++i)
-        br[i][j] += wp * (arm[i][0] * inner[0] + arm[i][1] * inner[1] + arm[i][2] * inner[2]) / Ain;
-    }
-    // bounded part: (exp(ikR) - 1)/R = (-2 sin^2(kR/2) + i sin(kR))/R, ik at R = 0
-    for (int q = 0; q < kQ; ++q) {
-      double rr[3];
-      for (int d = 0; d < 3; ++d) rr[d] = xo[p][d] - xi[q][d];
-      const double R = sqrt(rr[0] * rr[0] + rr[1] * rr[1] + rr[2] * rr[2]);
-      double gr, gi;
-      if (R > 0.0) {
-        const double sh = sin(0.5 * kk * R);
-        gr = -2.0 * sh * sh / R;
-        gi = sin(kk * R) / R;
-      } else {
-        gr = 0.0;
-        gi = kk;
-      }
-      const double ww = wp * rule.wd[q];
-      vr += ww * gr;
-      vi += ww * gi;
-      for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
+    gk[u][p * kQ + q][0] = gr;
+    gk[u][p * kQ + q][1] = gi;
+  }
+  __syncthreads();
+  // entries 0..8: (i, j) = (e / 3, e % 3) of the block; entry 9: V
+  for (int f = tid; f < np * 10; f += 256) {
+    const int u = f / 10, e = f % 10, i = e / 3, j = e % 3;
+    const int c = pairs[2 * (t0 + u)], cp = pairs[2 * (t0 + u) + 1];
+    const double Ain = area[cp];
+    const double inv4pi = 0.25 / M_PI;
+    double ar = 0.0, ai = 0.0;
+    if (e < 9) {
+      const double* Po = geo[u][0] + 3 * i;
+      const double* Pi = geo[u][1] + 3 * j;
+      for (int p = 0; p < kQ; ++p) {
+        const double wp = rule.wd[p];
+        const double* xo = pts[u][0][p];
+        // singular part: int_c' (r' - r_j)/R = W + (x_p - r_j) S
+        double arm[3], inner[3];
+        for (int d = 0; d < 3; ++d) arm[d] = xo[d] - Po[d];
+        for (int d = 0; d < 3; ++d) inner[d] = pot[u][p][1 + d] + (xo[d] - Pi[d]) * pot[u][p][0];
+        ar += wp * (arm[0] * inner[0] + arm[1] * inner[1] + arm[2] * inner[2]) / Ain;
+        for (int q = 0; q < kQ; ++q) {
+          const double ww = wp * rule.wd[q];
           double dot = 0.0;
-          for (int d = 0; d < 3; ++d) dot += (xo[p][d] - Po[i][d]) * (xi[q][d] - Pi[j][d]);
-          br[i][j] += ww * dot * gr;
-          bi[i][j] += ww * dot * gi;
+          for (int d = 0; d < 3; ++d) dot += (xo[d] - Po[d]) * (pts[u][1][q][d] - Pi[d]);
+          ar += ww * dot * gk[u][p * kQ + q][0];
+          ai += ww * dot * gk[u][p * kQ + q][1];
         }
-    }
-  }
-  const double inv4pi = 0.25 / M_PI;
-  vr *= inv4pi;
-  vi *= inv4pi;
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      const double f = 0.25 * sgn[c * 3 + i] * sgn[cp * 3 + j] * inv4pi;
-      br[i][j] *= f;
-      bi[i][j] *= f;
-    }
-  if (c == cp) {
-    for (int i = 0; i < 3; ++i)
-      for (int j = i + 1; j < 3; ++j) {
-        const double mr = 0.5 * (br[i][j] + br[j][i]), mi = 0.5 * (bi[i][j] + bi[j][i]);
-        br[i][j] = br[j][i] = mr;
-        bi[i][j] = bi[j][i] = mi;
       }
+      const double s = 0.25 * sgn[c * 3 + i] * sgn[cp * 3 + j] * inv4pi;
+      blk[u][e][0] = ar * s;
+      blk[u][e][1] = ai * s;
+    } else {
+      for (int p = 0; p < kQ; ++p) {
+        const double wp = rule.wd[p];
+        ar += wp * pot[u][p][0] / Ain;
+        for (int q = 0; q < kQ; ++q) {
+          const double ww = wp * rule.wd[q];
+          ar += ww * gk[u][p * kQ + q][0];
+          ai += ww * gk[u][p * kQ + q][1];
+        }
+      }
+      ar *= inv4pi;
+      ai *= inv4pi;
+      const float2 v = make_float2((float)ar, (float)ai);
+      if (NV) {  // compressed operator: V of the pair, placed by the tile kernel
+        NV[t0 + u] = v;
+      } else {
+        Vm[(long)c * ldV + cp] = v;
+        Vm[(long)cp * ldV + c] = v;
+      }
+    }
   }
-  const float2 v = make_float2((float)vr, (float)vi);
-  if (NV) {  // compressed operator: V of the pair, placed by the tile kernel
-    NV[t] = v;
-  } else {
-    Vm[(long)c * ldV + cp] = v;
-    Vm[(long)cp * ldV + c] = v;
+  __syncthreads();
+  for (int f = tid; f < np * 9; f += 256) {
+    const int u = f / 9, e = f % 9, m = 3 * (e % 3) + e / 3;
+    double br = blk[u][e][0], bi = blk[u][e][1];
+    if (e != m && pairs[2 * (t0 + u)] == pairs[2 * (t0 + u) + 1]) {  // a self block is symmetrised
+      br = 0.5 * (br + blk[u][m][0]);
+      bi = 0.5 * (bi + blk[u][m][1]);
+    }
+    NB[(t0 + u) * 9 + e] = make_float2((float)br, (float)bi);
   }
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) NB[t * 9 + 3 * i + j] = make_float2((float)br[i][j], (float)bi[i][j]);
 }
 
 // ---------------------------------------------------------------- excitation
@@ -516,30 +679,32 @@ rfcmp_status mesh_upload(rfcmp_mesh m, hipStream_t s) {
   RF_TRY(up(d.ve_idx, h.vtx_edge_idx.data(), sizeof(int) * 2 * N));
   std::vector<float> vs(h.vtx_edge_sgn.begin(), h.vtx_edge_sgn.end());
   RF_TRY(up(d.ve_sgn, vs.data(), sizeof(float) * 2 * N));
-  std::vector<int> et_ptr, et_cell, et_rows, home;
-  int cmax = 0;
-  edge_tiles(h, et_ptr, et_cell, et_rows, home, cmax);
-  d.etiles = (int64_t)et_ptr.size() - 1;
-  d.et_cells_max = cmax;
-  RF_TRY(up(d.et_ptr, et_ptr.data(), sizeof(int) * et_ptr.size()));
-  RF_TRY(up(d.et_cell, et_cell.data(), sizeof(int) * et_cell.size()));
-  RF_TRY(up(d.et_rows, et_rows.data(), sizeof(int) * et_rows.size()));
+  AsmTiles at;
+  asm_tiles(h, at);
+  std::vector<int> home(C);
+  for (int64_t c = 0; c < C; ++c) home[c] = int(h.cell_edge[3 * c] / kEdgeTile);
+  d.asm_npair = (int64_t)at.off.size();
+  d.asm_batch = at.batch;
+  d.asm_scratch = at.scratch;
+  d.asm_cells_max = at.cmax;
+  RF_TRY(up(d.st_ptr, at.ptr.data(), sizeof(int) * at.ptr.size()));
+  RF_TRY(up(d.st_cell, at.cell.data(), sizeof(int) * at.cell.size()));
+  RF_TRY(up(d.st_span, at.span.data(), sizeof(int) * at.span.size()));
+  RF_TRY(up(d.st_pos, at.pos.data(), sizeof(int) * at.pos.size()));
+  RF_TRY(up(d.asm_pair, at.pair.data(), sizeof(int) * at.pair.size()));
+  RF_TRY(up(d.asm_off, at.off.data(), sizeof(long) * at.off.size()));
   RF_TRY(up(d.cell_home, home.data(), sizeof(int) * C));
   RF_HIP(hipStreamSynchronize(s));  // host staging vectors die here
   return RFCMP_OK;
 }
 
-rfcmp_status assemble_blocks(rfcmp_op op, hipStream_t s) {
+rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
   rfcmp_mesh m = op->mesh;
   const MeshHost& h = m->h;
   MeshDev& d = m->d;
   const int64_t N = h.N;
   const RuleArgs ra = rule_args();
   HmOp* hm = op->hm.get();
-  if (!hm) RF_HIP(hipMemsetAsync(op->Vb.p, 0, op->Vb.bytes, s));
-
-  const long nt = (long)d.etiles;
-  const long npairs_t = nt * (nt + 1) / 2;
   // the near pairs (computed on a host thread from mesh creation on): their
   // blocks first, which the T_A tiles read
   if (d.near_factor != op->opt.near_factor) {
@@ -573,7 +738,8 @@ rfcmp_status assemble_blocks(rfcmp_op op, hipStream_t s) {
   if (hm) RF_TRY(hm->NV.alloc(sizeof(float2) * std::max<long>(npairs, 1)));
   if (npairs > 0) {
     ProfScope prof("near_pairs", s);
-    hipLaunchKernelGGL(k_near_pairs, dim3((unsigned)((npairs + 127) / 128)), dim3(128), 0, s, npairs,
+    hipLaunchKernelGGL(k_near_pairs, dim3((unsigned)((npairs + kNearPairs - 1) / kNearPairs)), dim3(256), 0, s,
+                       npairs,
                        d.near.as<int>(), d.vtx.as<double>(), d.area.as<double>(), d.sgn.as<float>(), op->k, ra,
                        d.nearB.as<float2>(), hm ? nullptr : op->Vb.as<float2>(), (long)op->ldV,
                        hm ? hm->NV.as<float2>() : nullptr);
@@ -590,12 +756,12 @@ rfcmp_status assemble_blocks(rfcmp_op op, hipStream_t s) {
     if (nd > 0) {
       ProfScope prof("hm_dense", s);
       const size_t lds = 2 * sizeof(float2) * kEdgeTile * kEdgeTile + 2 * sizeof(CellL) * (size_t)H.t.et_cells_max;
-      hipLaunchKernelGGL(k_assemble_ta, dim3((unsigned)nd), dim3(kAsmThreads),
-                         lds, s, (int)N, H.et_ptr.as<int>(), H.et_cell.as<int>(), H.et_rows.as<int>(),
+      hipLaunchKernelGGL(k_assemble_list, dim3((unsigned)nd), dim3(kAsmThreads),
+                         lds, s, H.et_ptr.as<int>(), H.et_cell.as<int>(), H.et_rows.as<int>(),
                          H.home.as<int>(), d.cen.as<double>(), d.qoff.as<float4>(), d.fvoff.as<float4>(),
-                         d.sgn.as<float>(), (float)op->k, ra, (const uint8_t*)nullptr, d.np_ptr.as<int>(),
+                         d.sgn.as<float>(), (float)op->k, ra, d.np_ptr.as<int>(),
                          d.np_other.as<int>(), d.np_code.as<int>(), d.nearB.as<float2>(), hm->TAd.as<float2>(),
-                         (long)kEdgeTile, hm->Vd.as<float2>(), 0L, H.dense_ij.as<int2>(), H.vd_off.as<long>(),
+                         hm->Vd.as<float2>(), H.dense_ij.as<int2>(), H.vd_off.as<long>(),
                          H.cell_start.as<int>(), H.iperm_c.as<int>(), hm->NV.as<float2>());
       RF_HIP(hipGetLastError());
     }
@@ -603,58 +769,105 @@ rfcmp_status assemble_blocks(rfcmp_op op, hipStream_t s) {
     hm->dense_entries[1] = H.vd_total;
     return hm_aca(op, s);
   }
-  {
-    ProfScope prof("assemble_ta", s);
-    const size_t lds = 2 * sizeof(float2) * kEdgeTile * kEdgeTile + 2 * sizeof(CellL) * (size_t)d.et_cells_max;
-    hipLaunchKernelGGL(k_assemble_ta, dim3((unsigned)npairs_t), dim3(kAsmThreads),
-                       lds, s, (int)N, d.et_ptr.as<int>(), d.et_cell.as<int>(), d.et_rows.as<int>(),
-                       d.cell_home.as<int>(), d.cen.as<double>(), d.qoff.as<float4>(), d.fvoff.as<float4>(),
-                       d.sgn.as<float>(), (float)op->k, ra, d.tile_near.as<uint8_t>(), d.np_ptr.as<int>(),
-                       d.np_other.as<int>(), d.np_code.as<int>(), d.nearB.as<float2>(), op->TA.as<float2>(),
-                       (long)op->ldA, op->Vb.as<float2>(), (long)op->ldV, (const int2*)nullptr,
-                       (const long*)nullptr, (const int*)nullptr, (const int*)nullptr, (const float2*)nullptr);
+  if (d.asm_npair == 0) return RFCMP_OK;
+  const size_t need = sizeof(float2) * (size_t)d.asm_scratch;
+  if (scratch.bytes < need) RF_TRY(scratch.alloc(need));
+  ProfScope prof("assemble_ta", s);
+  PairArgs g;
+  g.st_ptr = d.st_ptr.as<int>();
+  g.st_cell = d.st_cell.as<int>();
+  g.cell_home = d.cell_home.as<int>();
+  g.pair = d.asm_pair.as<int4>();
+  g.off = d.asm_off.as<long>();
+  g.near = d.tile_near.as<uint8_t>();
+  g.np_ptr = d.np_ptr.as<int>();
+  g.np_other = d.np_other.as<int>();
+  g.np_code = d.np_code.as<int>();
+  g.NB = d.nearB.as<float2>();
+  g.cen = d.cen.as<double>();
+  g.qoff = d.qoff.as<float4>();
+  g.fvoff = d.fvoff.as<float4>();
+  g.sgn = d.sgn.as<float>();
+  g.rule = ra;
+  g.kk = (float)op->k;
+  g.st_span = d.st_span.as<int>();
+  g.st_pos = d.st_pos.as<int2>();
+  g.N = (int)N;
+  g.hshift = asm_shift(N);
+  const unsigned cmax = (unsigned)d.asm_cells_max, ncol = (cmax + 63) / 64;
+  for (size_t q = 0; q + 1 < d.asm_batch.size(); ++q) {
+    const unsigned np = (unsigned)(d.asm_batch[q + 1] - d.asm_batch[q]);
+    g.p0 = (int)d.asm_batch[q];
+    // first cells per wave: 2 once that leaves the launch 8192 waves (a wave's
+    // work is the launch's tail: level 5 17.4 ms with 2, 18.1 with 4)
+    g.rows = (long)ncol * cmax * np >= 16384 ? 2 : 1;
+    hipLaunchKernelGGL(k_cell_pairs, dim3(ncol, (cmax + 4 * g.rows - 1) / (4 * g.rows), np), dim3(256), 0, s, g,
+                       scratch.as<float2>(), op->Vb.as<float2>(), (long)op->ldV);
+    hipLaunchKernelGGL(k_gather_ta, dim3(1u << (2 * g.hshift), np), dim3(256), 0, s, g, scratch.as<float2>(),
+                       op->TA.as<float2>(), (long)op->ldA);
   }
   RF_HIP(hipGetLastError());
   return RFCMP_OK;
 }
 
-void edge_tiles(const MeshHost& h, std::vector<int>& ptr, std::vector<int>& cell, std::vector<int>& rows,
-                std::vector<int>& home, int& cmax) {
-  const int64_t N = h.N, C = h.C;
-  const int64_t nt = (N + kEdgeTile - 1) / kEdgeTile;
-  ptr.assign(nt + 1, 0);
-  cell.clear();
-  rows.clear();
-  home.assign(C, 0);
-  cmax = 0;
+// Edge tiles of the dense assembly: 2048 edges above 6144, 1024 and 512 below,
+// where a larger tile leaves too few pairs of tiles (level 5: 17.4 ms at 2048,
+// 18.1 at 1024, 19.8 at 512; level 2: 0.027 ms at 512, 0.040 at 2048).
+int asm_shift(int64_t N) { return N > 6144 ? 5 : N > 1536 ? 4 : 3; }
+
+void asm_tiles(const MeshHost& h, AsmTiles& out) {
+  const int64_t N = h.N, E = (int64_t)kEdgeTile << asm_shift(N), nt = (N + E - 1) / E;
+  out.ptr.assign(nt + 1, 0);
+  out.pos.resize(2 * N);
   std::vector<int> cells;
+  std::vector<int> local(h.C, 0);
   for (int64_t t = 0; t < nt; ++t) {
-    cells.clear();
-    for (int64_t e = t * kEdgeTile; e < std::min<int64_t>(N, (t + 1) * kEdgeTile); ++e)
-      for (int k = 0; k < 2; ++k) cells.push_back(h.edge_cell[2 * e + k]);
+    const int64_t e0 = t * E, e1 = std::min<int64_t>(N, e0 + E);
+    cells.assign(h.edge_cell.begin() + 2 * e0, h.edge_cell.begin() + 2 * e1);
     std::sort(cells.begin(), cells.end());
     cells.erase(std::unique(cells.begin(), cells.end()), cells.end());
+    for (size_t i = 0; i < cells.size(); ++i) local[cells[i]] = (int)i;
+    for (int64_t e = e0; e < e1; ++e)
+      for (int k = 0; k < 2; ++k) out.pos[2 * e + k] = 3 * local[h.edge_cell[2 * e + k]] + h.edge_local[2 * e + k];
+    out.cell.insert(out.cell.end(), cells.begin(), cells.end());
     for (int c : cells) {
-      int r3 = 0;
+      int lo = INT_MAX, hi = 0;
       for (int i = 0; i < 3; ++i) {
         const int64_t e = h.cell_edge[3 * c + i];
-        const int r = (e / kEdgeTile == t) ? int(e % kEdgeTile) : 0xFF;
-        r3 |= r << (8 * i);
+        if (e < e0 || e >= e1) continue;
+        lo = std::min(lo, (int)((e - e0) / kEdgeTile));
+        hi = std::max(hi, (int)((e - e0) / kEdgeTile));
       }
-      cell.push_back(c);
-      rows.push_back(r3);
+      out.span.push_back(lo | hi << 16);
     }
-    ptr[t + 1] = (int)cell.size();
-    cmax = std::max(cmax, (int)cells.size());
+    out.ptr[t + 1] = (int)out.cell.size();
+    out.cmax = std::max(out.cmax, (int)cells.size());
   }
-  for (int64_t c = 0; c < C; ++c) home[c] = int(h.cell_edge[3 * c] / kEdgeTile);
+  // tile pairs s <= t in batches whose blocks fit the scratch
+    int64_t used = 0;
+  out.batch.assign(1, 0);
+  for (int64_t t = 0; t < nt; ++t)
+    for (int64_t s = 0; s <= t; ++s) {
+      const int64_t need = 9 * (int64_t)(out.ptr[s + 1] - out.ptr[s]) * (out.ptr[t + 1] - out.ptr[t]);
+      const int64_t p = (int64_t)out.off.size();
+      if (used > 0 && (used + need > kAsmScratch || p - out.batch.back() >= kAsmBatch)) {
+        out.batch.push_back(p);
+        used = 0;
+      }
+      const int q[4] = {(int)s, (int)t, 0, 0};
+      out.pair.insert(out.pair.end(), q, q + 4);
+      out.off.push_back((long)used);
+      used += need;
+      out.scratch = std::max(out.scratch, used);
+    }
+  if (!out.off.empty()) out.batch.push_back((int64_t)out.off.size());
 }
 
 void near_data(const MeshHost& h, double factor, NearData& out) {
   near_pairs(h, factor, out.pairs);
   const int64_t np = (int64_t)out.pairs.size() / 2, C = h.C, N = h.N;
   const int32_t* pr = out.pairs.data();
-  const int64_t nt = (N + kEdgeTile - 1) / kEdgeTile;
+  const int64_t E = (int64_t)kEdgeTile << asm_shift(N), nt = (N + E - 1) / E;
   const size_t ntp = (size_t)(nt * (nt + 1) / 2);
   // Contiguous chunks of the pair list on a few threads.  Pass 1 counts each
   // chunk's occurrences of every cell; pass 2 places them, chunk by chunk in
@@ -695,8 +908,8 @@ void near_data(const MeshHost& h, double factor, NearData& out) {
     for (int64_t p = p0; p < p1; ++p) {
       int64_t ta[3], tb[3];
       for (int i = 0; i < 3; ++i) {
-        ta[i] = h.cell_edge[3 * pr[2 * p] + i] / kEdgeTile;
-        tb[i] = h.cell_edge[3 * pr[2 * p + 1] + i] / kEdgeTile;
+        ta[i] = h.cell_edge[3 * pr[2 * p] + i] / E;
+        tb[i] = h.cell_edge[3 * pr[2 * p + 1] + i] / E;
       }
       for (int i = 0; i < 3; ++i)
         for (int j = 0; j < 3; ++j) {

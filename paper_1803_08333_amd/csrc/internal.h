@@ -143,8 +143,9 @@ struct SpDevice;     // sparse Cholesky factor, device (spchol.h)
 // The near pairs of one factor (c <= c', self pairs included) and what the
 // T_A assembly looks them up with (assemble.hip): the near partners of each
 // cell, ascending (ptr/other), with code 2 p + t for pair p (t = 1: the
-// pair is stored with the partner first), and per pair of edge tiles
-// (I <= J, index J (J + 1)/2 + I) whether any of its cell pairs is near.
+// pair is stored with the partner first), and per pair of the dense
+// assembly's edge tiles (s <= t, index t (t + 1)/2 + s) whether any of its cell
+// pairs is near.
 struct NearData {
   std::vector<int32_t> pairs, ptr, other, code;
   std::vector<uint8_t> tile_near;
@@ -180,13 +181,12 @@ struct MeshDev {
   DevBuf Gll_inv;    // double [ldG][ldG]
   DevBuf Gtp_inv;    // double [ldT][ldT]
   std::unique_ptr<SplitMatrix> Lp16, Gll16, Gtp16;  // BF16x3 planes, built on demand
-  // assembly edge tiles (kEdgeTile consecutive edges each) and the cells
-  // each tile touches: et_cell[et_ptr[t] ..] ascending, et_rows the rows in
-  // the tile of each such cell's three local edges (8 bits each, 0xFF: not in
-  // the tile), cell_home the tile of each cell's local edge 0
-  int64_t etiles = 0;
-  int et_cells_max = 0;
-  DevBuf et_ptr, et_cell, et_rows, cell_home;
+  // edge tiles of the dense assembly (AsmTiles) and the 64-edge tile of each
+  // cell's local edge 0
+  DevBuf st_ptr, st_cell, st_span, st_pos, asm_pair, asm_off, cell_home;
+  std::vector<int64_t> asm_batch;
+  int64_t asm_npair = 0, asm_scratch = 0;
+  int asm_cells_max = 0;
   double near_factor = -1.0;  // factor of the cached near-pair list
   int64_t npairs = 0;
   DevBuf near;       // int [npairs][2]
@@ -281,17 +281,30 @@ namespace rfcmp {
 rfcmp_status build_mesh_host(const double* xyz, int64_t nv, const int32_t* tri, int64_t nc, MeshHost& h);
 void near_pairs(const MeshHost& h, double factor, std::vector<int32_t>& out);
 void near_data(const MeshHost& h, double factor, NearData& out);
-// Edge tiles of the T_A assembly (kEdgeTile consecutive edges): the cells
-// of each tile (ptr/cell, ascending), the rows in the tile of their local
-// edges (rows, 8 bits each, 0xFF outside), the tile of each cell's local edge
-// 0 (home) and the most cells of a tile (cmax).
-void edge_tiles(const MeshHost& h, std::vector<int>& ptr, std::vector<int>& cell, std::vector<int>& rows,
-                std::vector<int>& home, int& cmax);
 void build_cell_nb(MeshHost& h);
 
 // assemble.hip
 rfcmp_status mesh_upload(rfcmp_mesh m, hipStream_t s);
-rfcmp_status assemble_blocks(rfcmp_op op, hipStream_t s);
+// Edge tiles of the dense assembly (kEdgeTile << asm_shift(N) consecutive
+// edges): the cells of each tile (ptr/cell, ascending, at most cmax) with the
+// lowest and highest 64-edge tile, counted in the tile, of their edges in it
+// (span, lowest | highest << 16), the slot
+// 3 c + i of every edge in its c+ and c- (pos [N][2], c counted in the edge's
+// tile), the tile pairs (pair, int4) with the offsets of their blocks in the
+// scratch, in batches batch[q] .. batch[q + 1], and the scratch they need
+// (complex64 entries).
+struct AsmTiles {
+  std::vector<int> ptr, cell, span, pos, pair;
+  std::vector<long> off;
+  std::vector<int64_t> batch;
+  int64_t scratch = 0;
+  int cmax = 0;
+};
+int asm_shift(int64_t N);
+void asm_tiles(const MeshHost& h, AsmTiles& out);
+// scratch: the cell-pair blocks of a batch, grown as needed, shared by
+// assemblies queued on one stream
+rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s);
 // sv != nullptr: the split excitation e = Sigma sv + e (sv [nrhs][C], e the
 // plane wave less its static part)
 rfcmp_status rhs_planewave(rfcmp_op op, const double* khat, const double* pol, int nrhs,

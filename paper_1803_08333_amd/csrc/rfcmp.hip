@@ -1521,6 +1521,7 @@ rfcmp_status rfcmp_op_create_many(rfcmp_mesh m, const double* k, int32_t nk, con
   m->device = dev;
   const int64_t N = m->h.N, C = m->h.C, V = m->h.V;
   std::vector<std::unique_ptr<rfcmp_op_s>> ops(nk);
+  DevBuf asm_scratch;  // given back when every assembly is done
   // Every operator's blocks first: their assembly runs beside the projector
   // builds of a new mesh, which the scalings then wait for.
   for (int32_t i = 0; i < nk; ++i) {
@@ -1541,7 +1542,7 @@ rfcmp_status rfcmp_op_create_many(rfcmp_mesh m, const double* k, int32_t nk, con
     }
     RF_TRY(ensure_work(op.get(), 4));
     RF_TRY(op->symv_scratch.alloc(symv_scratch_bytes(N, 4) + symv_scratch_bytes(C, 4) + symv_scratch_bytes(V, 4)));
-    RF_TRY(assemble_blocks(op.get(), s));
+    RF_TRY(assemble_blocks(op.get(), asm_scratch, s));
   }
   for (int32_t i = 0; i < nk; ++i) RF_TRY(ready_projectors(ops[i].get(), s));
   for (int32_t i = 0; i < nk; ++i) {
@@ -1604,26 +1605,14 @@ rfcmp_status rfcmp_op_set_scalings(rfcmp_op op, double a, double b, double g) {
   return RFCMP_OK;
 }
 
-// D [n][n] = the symmetric M stored as the upper triangle of tri-wide
-// blocks (entries with k < tri floor(i / tri) read transposed).
-__global__ void k_export_tri(const float2* __restrict__ M, long n, long ld, long tri, float2* __restrict__ D) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * n) return;
-  const long i = t / n, k = t % n;
-  D[t] = k < (i / tri) * tri ? M[k * ld + i] : M[i * ld + k];
-}
-
 rfcmp_status rfcmp_op_export(rfcmp_op op, void* TA, void* V, void* stream) {
   RF_ARG(op, "op is NULL");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int64_t N = op->mesh->h.N, C = op->mesh->h.C;
   if (op->hm) return hm_export(op, static_cast<float2*>(TA), static_cast<float2*>(V), s);
-  if (TA && N > 0) {
-    const long tot = (long)N * N;
-    hipLaunchKernelGGL(k_export_tri, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, op->TA.as<float2>(),
-                       (long)N, (long)op->ldA, (long)kTriBlock, static_cast<float2*>(TA));
-    RF_HIP(hipGetLastError());
-  }
+  if (TA && N > 0)  // stored whole
+    RF_HIP(hipMemcpy2DAsync(TA, sizeof(float2) * N, op->TA.p, sizeof(float2) * op->ldA, sizeof(float2) * N, N,
+                            hipMemcpyDeviceToDevice, s));
   if (V)
     RF_HIP(hipMemcpy2DAsync(V, sizeof(float2) * C, op->Vb.p, sizeof(float2) * op->ldV, sizeof(float2) * C, C,
                             hipMemcpyDeviceToDevice, s));
