@@ -150,6 +150,7 @@ __global__ __launch_bounds__(1024) void k_comb_mean(int C, const double* __restr
   double2 mb = make_double2(0.0, 0.0);
   if (b) {
     double br = 0.0, bi = 0.0;
+#pragma unroll 8
     for (int i = t; i < C; i += 1024) {
       br += b[r * C + i].x;
       bi += b[r * C + i].y;
@@ -158,6 +159,7 @@ __global__ __launch_bounds__(1024) void k_comb_mean(int C, const double* __restr
     mb = make_double2(tb.x / C, tb.y / C);
   }
   double ar = 0.0, ai = 0.0;
+#pragma unroll 8
   for (int i = t; i < C; i += 1024) {
     double2 v = a ? cscale(fa, a[r * C + i]) : make_double2(0.0, 0.0);
     if (b) v = cadd(v, cscale(fb, csub(b[r * C + i], mb)));
@@ -169,6 +171,7 @@ __global__ __launch_bounds__(1024) void k_comb_mean(int C, const double* __restr
   if (!out2) return;
   const double2 to = block_sum_1024(ar, ai, sr, si);
   const double2 m1 = make_double2(to.x / C, to.y / C);
+#pragma unroll 8
   for (int i = t; i < C; i += 1024) out2[r * C + i] = cscale(f2, csub(out1[r * C + i], m1));
 }
 
@@ -382,6 +385,7 @@ __global__ __launch_bounds__(1024) void k_power_next(int N, int C, const int* __
     }
     return;
   }
+#pragma unroll 8
   for (int n = threadIdx.x; n < N; n += 1024) {
     const double2 zd = csub(z[edge_cell[2 * n]], z[edge_cell[2 * n + 1]]);
     const double2 v = r < 2 ? csub(w[(long)r * N + n], zd) : zd;
@@ -391,6 +395,7 @@ __global__ __launch_bounds__(1024) void k_power_next(int N, int C, const int* __
   const double2 t = block_sum_1024(a, 0.0, sr, si);
   const double sc = 1.0 / sqrt(t.x);
   if (threadIdx.x == 0) nrm2[r] = make_double2(t.x, 0.0);
+#pragma unroll 8
   for (int n = threadIdx.x; n < N; n += 1024) o[n] = cscale(sc, o[n]);
 }
 
