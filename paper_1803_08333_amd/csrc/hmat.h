@@ -72,10 +72,12 @@ struct HmLr {
   int r0, m, c0, n;
 };
 
-// A tile list entry of one operator, resolved once its ranks are known:
-// a low-rank entry's factor (U for the rows, V for the columns), the first
-// row it covers in the permuted order, its length and rank, and the offset
-// of its projections; the list code (4 b + kind) for every entry.
+// A tile list entry of one operator, resolved once its ranks are known.  A
+// low-rank entry (code 4 b + 2 or 3): its factor (U for the rows, V for the
+// columns), the first row it covers in the permuted order, its length and rank,
+// and the offset of its projections.  A dense one (4 b, or 4 b + 1 for its
+// transpose): the block, the first position and the number of its input rows
+// (start, k) and the entries between its stored rows (len).
 struct HmEnt {
   const float2* F;
   long zb;

@@ -16,12 +16,13 @@
 // of its block's factors, so the only values it reads from other threads are
 // the pivots, staged in LDS after a barrier.
 //
-// Product y = M x (M = T_A or V, x [nr][n] complex128, FP64 accumulation):
-// the input in the permuted order; per low-rank block z = V^T x_cols and
-// w = U^T x_rows (k_hm_proj); per tile of output rows the sum, in a fixed
-// order, of its dense blocks (and the transposes of those it is the column
-// of), U z of the low-rank blocks it is a row of and V w of those it is a
-// column of (k_hm_tile), written back in the mesh's numbering.
+// Product y = M x (M = T_A or V, x [nr][n] complex128, FP64 accumulation on the
+// FP64 matrix cores, 8 right-hand sides at a time): the input in the permuted
+// order; per low-rank block z = V^T x_cols and w = U^T x_rows (k_hm_proj); per
+// tile of output rows the sum, in a fixed order, of its dense blocks (and the
+// transposes of those it is the column of), U z of the low-rank blocks it is a
+// row of and V w of those it is a column of (k_hm_tile), written back in the
+// mesh's numbering.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -327,359 +328,225 @@ __global__ __launch_bounds__(256) void k_aca_compact(int b0, const HmLr* blk, co
   for (long e = threadIdx.x; e < nv; e += 256) dv[e] = sv[e];
 }
 
-// xp[r][p] = x[r][perm[p]]
+// The product's vectors in the permuted order hold kHmR = 8 right-hand sides
+// per position, real and imaginary parts apart: 16 doubles, the columns of one
+// FP64 matrix-core operand (v_mfma_f64_16x16x4; right-hand sides beyond the
+// call's are zero).  A complex matrix times such a block takes two products,
+// P = Re(M) X and Q = Im(M) X, combined once at the end: Re Y = P_re - Q_im,
+// Im Y = P_im + Q_re, with Q negated for conj(M).
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+constexpr int kHmCols = 2 * kHmR;
+static_assert(kHmCols == 16, "one operand of 16 columns");
+
+// Operand entries: rows i = lane % 16, columns (and X rows) lane / 16 of each
+// step of four.
+struct HmAcc {
+  dbl4 p = dbl4{0.0, 0.0, 0.0, 0.0}, q = dbl4{0.0, 0.0, 0.0, 0.0};
+  __device__ inline void add(float2 m, double x) {
+    p = __builtin_amdgcn_mfma_f64_16x16x4f64((double)m.x, x, p, 0, 0, 0);
+    q = __builtin_amdgcn_mfma_f64_16x16x4f64((double)m.y, x, q, 0, 0, 0);
+  }
+};
+// Four neighbouring entries (8-byte aligned) in two loads.
+__device__ inline void hm_load4(const float2* p, float2 (&m)[4]) {
+  typedef float vf4 __attribute__((ext_vector_type(4), aligned(8)));
+  const vf4 a = *reinterpret_cast<const vf4*>(p), b = *reinterpret_cast<const vf4*>(p + 2);
+  m[0] = make_float2(a.x, a.y);
+  m[1] = make_float2(a.z, a.w);
+  m[2] = make_float2(b.x, b.y);
+  m[3] = make_float2(b.z, b.w);
+}
+// Value v of lane l: row 4 v + l / 16, column l % 16; the real (even) and
+// imaginary (odd) columns exchange their Q.
+__device__ inline double hm_combine(double p, double q, int lane, double sgn) {
+  const double other = __shfl_xor(q, 1);
+  return (lane & 1) ? p + sgn * other : p - sgn * other;
+}
+
+// xp[p][r] = x[r][perm[p]]
 __global__ void k_hm_gather(int n, int nr, const int* __restrict__ perm, const double2* __restrict__ x,
                             double2* __restrict__ xp) {
   const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (long)n * nr) return;
-  const int r = (int)(e / n), p = (int)(e % n);
-  xp[e] = x[(long)r * n + perm[p]];
+  if (e >= (long)n * kHmR) return;
+  const int r = (int)(e % kHmR), p = (int)(e / kHmR);
+  xp[e] = r < nr ? x[(long)r * n + perm[p]] : make_double2(0.0, 0.0);
 }
 
-// z = V^T x_cols and w = U^T x_rows of every low-rank block (conj: of the
-// conjugated factors), nr <= R <= kHmR right-hand sides: a small GEMM per
-// block (k x len times len x nr) over chunks of rows, the factor chunk
-// (k x rows <= 4096 entries) and the input chunk (rows x R <= 1024) staged in
-// LDS so that each is read from memory once.  The k R outputs are spread over
-// the workgroup: with fewer than 256, G = 256 / (k R) threads (at most 8)
-// share an output, thread group g taking the rows jj = g, g + G, ... of each
-// chunk in two alternating sums, and the G partial sums are added in order at
-// the end; with more, thread t takes outputs t, t + 256, ...  Every sum runs
-// in a fixed order.
-constexpr int kProjFactor = 4096;   // complex64 entries of a staged factor chunk
-constexpr int kProjInput = 1024;    // complex128 entries of a staged input chunk
-template <int R>
-__global__ __launch_bounds__(256) void k_hm_proj(const HmLr* __restrict__ blk, const int* __restrict__ rank,
+// z = V^T x_cols (part 0) and w = U^T x_rows (part 1) of every low-rank block
+// (conj: of the conjugated factors): 16 factor columns at a time are the
+// operand's rows, four waves take every fourth chunk of 16 positions, a lane
+// four neighbouring ones, and their sums are added in order.  Bound: memory,
+// the factors once and 128 bytes of input per position and block (level 6, tol
+// 1e-4: T_A 0.55 ms, V 0.24, where sums of FP64 FMAs over staged chunks took 1.5
+// and 0.7).  Nontemporal loads of the factors were slower (0.59 against 0.46 on
+// the mean of both).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+void k_hm_proj(const HmLr* __restrict__ blk, const int* __restrict__ rank,
                                                  float2* const* __restrict__ Up, float2* const* __restrict__ Vp,
-                                                 const long* __restrict__ zoff, const double2* __restrict__ xp,
-                                                 int n, int nr, int conj, double2* __restrict__ zw) {
-  __shared__ float2 sm[kProjFactor];
-  __shared__ double2 sx[kProjInput];
-  const int b = blockIdx.x;
+                                                 const long* __restrict__ zoff, const double* __restrict__ xp,
+                                                 double sgn, double* __restrict__ zw) {
+  __shared__ double red[3][8][64];
+  const int b = blockIdx.x, part = blockIdx.y;
   const int k = rank[b];
-  if (k == 0) return;
   const HmLr B = blk[b];
-  const int tid = threadIdx.x;
-  const float sgn = conj ? -1.f : 1.f;
-  constexpr int kOut = (kHmKmax * R + 255) / 256;  // outputs per thread at most
-  const int nout = k * R;
-  const int G = nout >= 256 ? 1 : min(8, 256 / nout);
-  const int g = tid / (nout < 256 ? nout : 256);   // row group (G > 1 only)
-  const int ob = tid % (nout < 256 ? nout : 256);  // first output of this thread
-  const bool act = g < G;
-  // rows per chunk: a multiple of 32, at most 256
-  const int cr = max(32, min(256, min(kProjFactor / k, kProjInput / R)) / 32 * 32);
-  double2* z = zw + zoff[b];
-  for (int part = 0; part < 2; ++part) {     // 0: z from V and the columns, 1: w from U and the rows
-    const float2* M = part == 0 ? Vp[b] : Up[b];
-    const int len = part == 0 ? B.n : B.m, off = part == 0 ? B.c0 : B.r0;
-    double2* out = z + (long)part * k * kHmR;
-    double ar[kOut], ai[kOut];
+  const float2* M = part == 0 ? Vp[b] : Up[b];
+  const int len = part == 0 ? B.n : B.m, off = part == 0 ? B.c0 : B.r0;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, col = lane & 15;
+  double* out = zw + (zoff[b] + (long)part * k * kHmR) * 2;
+  for (int l0 = 0; l0 < k; l0 += 16) {
+    const float2* row = M + (long)min(l0 + col, k - 1) * len;
+    HmAcc acc;
+    int j0 = 16 * w;
+#pragma unroll 4
+    for (; j0 + 16 <= len; j0 += 64) {
+      const int j = j0 + 4 * g;
+      float2 m[4];
+      double x[4];
+      hm_load4(row + j, m);
 #pragma unroll
-    for (int q = 0; q < kOut; ++q) ar[q] = ai[q] = 0.0;
-    for (int j0 = 0; j0 < len; j0 += cr) {
-      const int nj = min(cr, len - j0);
-      for (int e = tid; e < k * cr; e += 256) {
-        const int l = e / cr, jj = e % cr;
-        float2 v = jj < nj ? M[(long)l * len + j0 + jj] : make_float2(0.f, 0.f);
-        v.y *= sgn;
-        sm[e] = v;
-      }
-      for (int e = tid; e < cr * R; e += 256) {
-        const int jj = e / R, r = e % R;
-        sx[e] = (jj < nj && r < nr) ? xp[(long)r * n + off + j0 + jj] : make_double2(0.0, 0.0);
-      }
-      __syncthreads();
-      if (act) {
+      for (int e = 0; e < 4; ++e) x[e] = xp[(long)(off + j + e) * kHmCols + col];
 #pragma unroll
-        for (int q = 0; q < kOut; ++q) {
-          const int o = ob + 256 * q;
-          if (o < nout) {
-            const int l = o / R, r = o % R;
-            const float2* mrow = sm + l * cr;
-            double s0r = 0.0, s0i = 0.0, s1r = 0.0, s1i = 0.0;
-            int jj = g;
-            for (; jj + G < nj; jj += 2 * G) {
-              const float2 m0 = mrow[jj], m1 = mrow[jj + G];
-              const double2 x0 = sx[jj * R + r], x1 = sx[(jj + G) * R + r];
-              s0r += (double)m0.x * x0.x - (double)m0.y * x0.y;
-              s0i += (double)m0.x * x0.y + (double)m0.y * x0.x;
-              s1r += (double)m1.x * x1.x - (double)m1.y * x1.y;
-              s1i += (double)m1.x * x1.y + (double)m1.y * x1.x;
-            }
-            if (jj < nj) {
-              const float2 m0 = mrow[jj];
-              const double2 x0 = sx[jj * R + r];
-              s0r += (double)m0.x * x0.x - (double)m0.y * x0.y;
-              s0i += (double)m0.x * x0.y + (double)m0.y * x0.x;
-            }
-            ar[q] += s0r + s1r;
-            ai[q] += s0i + s1i;
-          }
+      for (int e = 0; e < 4; ++e) acc.add(m[e], x[e]);
+    }
+    if (j0 < len) {  // the last, short chunk
+      const int j = j0 + 4 * g;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int je = min(j + e, len - 1);
+        float2 m = row[je];
+        if (j + e >= len) m = make_float2(0.f, 0.f);
+        acc.add(m, xp[(long)(off + je) * kHmCols + col]);
+      }
+    }
+    if (w > 0)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        red[w - 1][v][lane] = acc.p[v];
+        red[w - 1][4 + v][lane] = acc.q[v];
+      }
+    __syncthreads();
+    if (w == 0)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double p = acc.p[v], q = acc.q[v];
+        for (int u = 0; u < 3; ++u) {
+          p += red[u][v][lane];
+          q += red[u][4 + v][lane];
         }
+        const int l = l0 + 4 * v + g;
+        const double z = hm_combine(p, q, lane, sgn);
+        if (l < k) out[(long)l * kHmCols + col] = z;
       }
-      __syncthreads();
-    }
-    if (G > 1) {  // the row groups' partial sums, added in order of g
-      double2* red = reinterpret_cast<double2*>(sm);  // [G][nout], 256 entries at most
-      static_assert(sizeof(sm) >= 256 * sizeof(double2), "partials fit the staging buffer");
-      if (act) red[g * nout + ob] = make_double2(ar[0], ai[0]);
-      __syncthreads();
-      if (g == 0) {
-        double sr = 0.0, si = 0.0;
-        for (int q = 0; q < G; ++q) {
-          sr += red[q * nout + ob].x;
-          si += red[q * nout + ob].y;
-        }
-        ar[0] = sr;
-        ai[0] = si;
-      }
-      __syncthreads();
-    }
-    if (g == 0) {
-#pragma unroll
-      for (int q = 0; q < kOut; ++q) {
-        const int o = ob + 256 * q;
-        if (o < nout && o % R < nr) out[(o / R) * kHmR + o % R] = make_double2(ar[q], ai[q]);
-      }
-    }
+    __syncthreads();
   }
 }
 
 struct TileArgs {
-  int n;                       // N or C
-  const int* perm;             // position -> mesh index
-  const int* row0;             // KIND 1: cell_start (rows of tile T: [row0[T], row0[T + 1]))
+  int n;                // N or C
+  const int* perm;      // position -> mesh index
+  const int* row0;      // KIND 1: cell_start (rows of tile T: [row0[T], row0[T + 1]))
   const int* list_ptr;
-  const HmEnt* ent;            // the list entries, resolved
-  const int2* dense_ij;
-  const float2* D;             // dense blocks
-  const long* doff;            // KIND 1: offsets of the dense blocks (KIND 0: b * 4096)
-  const HmLr* blk;
-  const int* rank;
-  float2* const* Up;
-  float2* const* Vp;
-  const long* zoff;
-  const double2* zw;
-  const double2* xp;
-  int nr, conj;
-  double2* y;
+  const HmEnt* ent;     // the list entries, resolved
+  const double* zw;
+  const double* xp;
+  int nr;
+  double sgn;
 };
 
+// One wave per 16 output rows of a tile (four waves a workgroup): it walks the
+// tile's list and adds each block's rows times its input, straight from memory
+// (the four waves share the input through L1), into the same two accumulators;
+// nothing is staged and no wave waits for another.  Entries: a dense block as
+// it is (kind 0) or transposed (1), or the rows of a low-rank block's factor
+// (2, 3) times its projections.  Eight waves a SIMD hold every wave of level 6
+// at once.  Bound: memory, dense blocks twice and the factor rows once (level 6,
+// tol 1e-4: T_A 0.81 ms = 3.5 TB/s, V 0.48, where blocks staged in LDS took 2.20
+// and 1.45).
 template <int KIND>
-__device__ inline int tile_row0(const TileArgs& a, int T) {
-  return KIND == 0 ? T * kEdgeTile : a.row0[T];
-}
-template <int KIND>
-__device__ inline int tile_rows(const TileArgs& a, int T) {
-  return KIND == 0 ? min(kEdgeTile, a.n - T * kEdgeTile) : a.row0[T + 1] - a.row0[T];
-}
-
-// One workgroup per tile of output rows; thread (row i, quarter g) keeps
-// the sums of its row for every right-hand side.  Each block of the tile's
-// list is staged in LDS with coalesced loads (all threads, many loads in
-// flight), then used from there: a dense block (64 x 64, rows padded) with
-// the input of its partner tile, or up to 32 factor columns of the rows of
-// consecutive low-rank blocks with their projections (a block of rank above
-// 32 in chunks of 32).  A dense V block larger than 64 x 64 (a tile homing
-// more than 64 cells) is read directly instead.
-constexpr int kTileLd = kEdgeTile + 1;  // padded row of a staged dense block
-template <int KIND, int R>
-__global__ __launch_bounds__(256) void k_hm_tile(const TileArgs a) {
-  __shared__ float2 smat[kEdgeTile * kTileLd];   // dense block [r][c], or factor rows [l][i] (32 x 64)
-  __shared__ double2 sx[kEdgeTile][kHmR];         // partner input [c][r], or projections [l][r]
-  __shared__ int s_nent, s_cols, s_colent[32], s_coll[32], s_len[32], s_o[32];
-  __shared__ const float2* s_F[32];
-  __shared__ const double2* s_zb[32];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+void k_hm_tile(const TileArgs a, double* __restrict__ y) {
   const int T = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int p0 = tile_row0<KIND>(a, T), nrow = tile_rows<KIND>(a, T);
-  const int lane = tid & 63, g = tid >> 6;
-  const float sgn = a.conj ? -1.f : 1.f;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), g = lane >> 4, col = lane & 15;
+  const int p0 = KIND == 0 ? T * kEdgeTile : a.row0[T];
+  const int nrow = KIND == 0 ? min(kEdgeTile, a.n - p0) : a.row0[T + 1] - p0;
   const int e0 = a.list_ptr[T], e1 = a.list_ptr[T + 1];
-  for (int base = 0; base < nrow; base += 64) {
-    const int i = base + lane;
-    const bool valid = i < nrow;
-    const int nb = min(64, nrow - base);   // rows of this pass
-    double ar[R], ai[R];
+  for (int base = 16 * w; base < nrow; base += 64) {
+    const int i = min(base + col, nrow - 1);
+    HmAcc acc;
+    HmEnt next = a.ent[min(e0, e1 - 1)];
+    for (int e = e0; e < e1; ++e) {
+      const HmEnt E = next;
+      next = a.ent[min(e + 1, e1 - 1)];
+      const int kind = E.code & 3, k = E.k;
+      if (kind < 2) {  // k input rows from position `start` on; `len` entries between the block's rows
+        const float2* D = E.F + (kind == 0 ? (long)i * E.len : (long)i);
+        const double* x0 = a.xp + (long)E.start * kHmCols + col;
+        int c0 = 0;
+        if (kind == 0) {
+#pragma unroll 2
+          for (; c0 + 16 <= k; c0 += 16) {
+            const int c = c0 + 4 * g;
+            float2 m[4];
+            double x[4];
+            hm_load4(D + c, m);
 #pragma unroll
-    for (int r = 0; r < R; ++r) ar[r] = ai[r] = 0.0;
-    auto fma_x = [&](float2 mv, const double2* x) {
-      const double mx = mv.x, my = sgn * mv.y;
+            for (int u = 0; u < 4; ++u) x[u] = x0[(c + u) * kHmCols];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double2 v = x[r];
-        ar[r] += mx * v.x - my * v.y;
-        ai[r] += mx * v.y + my * v.x;
-      }
-    };
-    int e = e0;
-    while (e < e1) {
-      __syncthreads();   // every wave is done with the previous batch's descriptors
-      // wave 0: the next entries that form a batch of low-rank blocks with at
-      // most 32 factor columns in all (their descriptors into LDS)
-      if (g == 0) {
-        const int ej = e + lane;
-        HmEnt E{nullptr, 0, 0, 0, 0, 0};
-        if (ej < e1) E = a.ent[ej];
-        const int cd = E.code;
-        const bool lr = ej < e1 && (cd & 3) >= 2;
-        const int kj = lr ? E.k : 0;
-        int cum = kj;
-        for (int o = 1; o < 64; o <<= 1) {
-          const int t = __shfl_up(cum, o);
-          if (lane >= o) cum += t;
-        }
-        const unsigned long long nonlr = __ballot(!lr);
-        const int first_non = nonlr ? (int)__builtin_ctzll(nonlr) : 64;
-        const bool ok = lane < first_non && lane < 32 && cum <= 32;
-        const int nent = __popcll(__ballot(ok));
-        const int cols = __shfl(cum, nent > 0 ? nent - 1 : 0);
-        if (lane == 0) {
-          s_nent = nent;
-          s_cols = nent > 0 ? cols : 0;
-        }
-        if (ok) {
-          s_F[lane] = E.F;
-          s_len[lane] = E.len;
-          s_o[lane] = p0 + base - E.start;
-          s_zb[lane] = a.zw + E.zb;
-          for (int c = cum - kj; c < cum; ++c) {
-            s_colent[c] = lane;
-            s_coll[c] = c - (cum - kj);
+            for (int u = 0; u < 4; ++u) acc.add(m[u], x[u]);
           }
-        }
-      }
-      __syncthreads();
-      const int nbatch = s_nent;
-      if (nbatch > 0) {
-        const int cols = s_cols;
-        for (int q = tid; q < 32 * 64; q += 256) {
-          const int c = q / 64, ii = q % 64;
-          float2 v = make_float2(0.f, 0.f);
-          if (c < cols && ii < nb) {
-            const int j = s_colent[c];
-            v = s_F[j][(long)s_coll[c] * s_len[j] + s_o[j] + ii];
-          }
-          smat[c * 64 + ii] = v;
-        }
-        {
-          const int c = tid / kHmR, r = tid % kHmR;   // 32 x 8 = 256 entries
-          sx[c][r] = (c < cols && r < a.nr) ? s_zb[s_colent[c]][(long)s_coll[c] * kHmR + r] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-        if (valid)
-          for (int c = g; c < cols; c += 4) fma_x(smat[c * 64 + lane], sx[c]);
-        e += nbatch;
-        continue;
-      }
-      const HmEnt E = a.ent[e];
-      const int kind = E.code & 3, bi = E.code >> 2;
-      ++e;
-      if (kind < 2) {
-        const int I = a.dense_ij[bi].x, J = a.dense_ij[bi].y;
-        int qI, nI, qJ, nJ;
-        const float2* D;
-        if (KIND == 0) {
-          qI = I * kEdgeTile;
-          qJ = J * kEdgeTile;
-          nI = min(kEdgeTile, a.n - qI);
-          nJ = min(kEdgeTile, a.n - qJ);
-          D = a.D + (long)bi * kEdgeTile * kEdgeTile;
         } else {
-          qI = a.row0[I];
-          nI = a.row0[I + 1] - qI;
-          qJ = a.row0[J];
-          nJ = a.row0[J + 1] - qJ;
-          D = a.D + a.doff[bi];
-        }
-        const int ld = KIND == 0 ? kEdgeTile : nJ;
-        // the partner's rows: columns of D (kind 0) or its rows (kind 1)
-        const int qp = kind == 0 ? qJ : qI, np = kind == 0 ? nJ : nI;
-        if (nI > 64 || nJ > 64) {  // direct reads (only a V block of a tile homing > 64 cells)
-          if (valid) {
-            if (kind == 0) {
-              for (int c = g; c < nJ; c += 4) {
-                double2 xv[R];
+#pragma unroll 2
+          for (; c0 + 16 <= k; c0 += 16) {
+            const int c = c0 + 4 * g;
+            float2 m[4];
+            double x[4];
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                  xv[r] = r < a.nr ? a.xp[(long)r * a.n + qJ + c] : make_double2(0.0, 0.0);
-                fma_x(D[(long)i * ld + c], xv);
-              }
-            } else {
-              for (int rr = g; rr < nI; rr += 4) {
-                double2 xv[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                  xv[r] = r < a.nr ? a.xp[(long)r * a.n + qI + rr] : make_double2(0.0, 0.0);
-                fma_x(D[(long)rr * ld + i], xv);
-              }
+            for (int u = 0; u < 4; ++u) {
+              m[u] = D[(c + u) * (long)E.len];
+              x[u] = x0[(c + u) * kHmCols];
             }
-          }
-          continue;
-        }
-        for (int q = tid; q < kEdgeTile * kEdgeTile; q += 256) {
-          const int r = q / kEdgeTile, c = q % kEdgeTile;
-          smat[r * kTileLd + c] = (r < nI && c < nJ) ? D[(long)r * ld + c] : make_float2(0.f, 0.f);
-        }
-        for (int q = tid; q < kEdgeTile * kHmR; q += 256) {
-          const int c = q / kHmR, r = q % kHmR;
-          sx[c][r] = (c < np && r < a.nr) ? a.xp[(long)r * a.n + qp + c] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-        if (valid) {
-          if (kind == 0) {
-            for (int c = 16 * g; c < 16 * g + 16; ++c) fma_x(smat[(i - base) * kTileLd + c], sx[c]);
-          } else {
-            for (int rr = 16 * g; rr < 16 * g + 16; ++rr) fma_x(smat[rr * kTileLd + (i - base)], sx[rr]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc.add(m[u], x[u]);
           }
         }
-        __syncthreads();
+        if (c0 < k) {  // the last, short chunk
+          const int c = c0 + 4 * g;
+          const long step = kind == 0 ? 1 : E.len;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int cu = min(c + u, k - 1);
+            float2 m = D[cu * step];
+            if (c + u >= k) m = make_float2(0.f, 0.f);
+            acc.add(m, x0[cu * kHmCols]);
+          }
+        }
       } else {
-        const int k = E.k;
-        const double2* zb = a.zw + E.zb;
-        const float2* F = E.F;
-        const int len = E.len;
-        const int o = p0 + base - E.start;   // first row of this pass in the factor
-        for (int l0 = 0; l0 < k; l0 += 32) {
-          const int nl = min(32, k - l0);
-          for (int q = tid; q < 32 * 64; q += 256) {
-            const int l = q / 64, ii = q % 64;
-            smat[l * 64 + ii] = (l < nl && ii < nb) ? F[(long)(l0 + l) * len + o + ii] : make_float2(0.f, 0.f);
+        const float2* F = E.F + (p0 + i - E.start);
+        const double* z = a.zw + E.zb * 2 + col;
+        for (int l0 = 0; l0 < k; l0 += 16) {
+          float2 m[4];
+          double x[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int l = min(l0 + 4 * u + g, k - 1);
+            m[u] = F[(long)l * E.len];
+            x[u] = z[(long)l * kHmCols];
           }
-          {
-            const int l = tid / kHmR, r = tid % kHmR;   // 32 x 8 = 256 entries
-            sx[l][r] = (l < nl && r < a.nr) ? zb[(long)(l0 + l) * kHmR + r] : make_double2(0.0, 0.0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (l0 + 4 * u >= k) break;
+            if (l0 + 4 * u + g >= k) m[u] = make_float2(0.f, 0.f);
+            acc.add(m[u], x[u]);
           }
-          __syncthreads();
-          if (valid)
-            for (int l = g; l < nl; l += 4) fma_x(smat[l * 64 + lane], sx[l]);
-          __syncthreads();
         }
       }
     }
-    __syncthreads();   // the last batch's reads of smat are done
-    // the four quarters' sums in order, through LDS (smat reused)
-    double2* red = reinterpret_cast<double2*>(smat);   // [3][64][kHmR] (quarters 1..3)
-    static_assert(sizeof(smat) >= 3 * 64 * kHmR * sizeof(double2), "reduction fits the staging buffer");
-    if (g > 0)
 #pragma unroll
-      for (int r = 0; r < R; ++r) red[((g - 1) * 64 + lane) * kHmR + r] = make_double2(ar[r], ai[r]);
-    __syncthreads();
-    if (g == 0 && valid) {
-      const int dst = a.perm[p0 + i];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (r >= a.nr) break;
-        double sr = ar[r], si = ai[r];
-        for (int q = 0; q < 3; ++q) {
-          sr += red[(q * 64 + lane) * kHmR + r].x;
-          si += red[(q * 64 + lane) * kHmR + r].y;
-        }
-        a.y[(long)r * a.n + dst] = make_double2(sr, si);
-      }
+    for (int v = 0; v < 4; ++v) {
+      const double s = hm_combine(acc.p[v], acc.q[v], lane, a.sgn);
+      const int row = base + 4 * v + g;
+      if (row < nrow && (col >> 1) < a.nr) y[((long)(col >> 1) * a.n + a.perm[p0 + row]) * 2 + (col & 1)] = s;
     }
-    __syncthreads();
   }
 }
 
@@ -820,6 +687,12 @@ rfcmp_status hm_aca(rfcmp_op op, hipStream_t s) {
   P.unconverged = 0;
   std::vector<long> zoff_all[2];
   int64_t zw_need = 0;
+  std::vector<long> vd_off(t.dense_I.size());  // offsets of the dense V blocks
+  for (size_t b = 0, o = 0; b < vd_off.size(); ++b) {
+    vd_off[b] = (long)o;
+    o += (size_t)(t.cell_start[t.dense_I[b] + 1] - t.cell_start[t.dense_I[b]]) *
+         (size_t)(t.cell_start[t.dense_J[b] + 1] - t.cell_start[t.dense_J[b]]);
+  }
   for (int kind = 0; kind < 2; ++kind) {
     std::vector<HmLr> blk(nlr);
     for (int64_t b = 0; b < nlr; ++b) {
@@ -947,6 +820,16 @@ rfcmp_status hm_aca(rfcmp_op op, hipStream_t s) {
         E.len = rows ? blk[b].m : blk[b].n;
         E.k = hr[b];
         E.zb = zo[b] + (rows ? 0 : (long)hr[b] * kHmR);
+      } else {
+        const bool rows = (code & 3) == 0;   // else its transpose
+        const int I = t.dense_I[b], J = t.dense_J[b];
+        const int qI = kind == 0 ? I * kEdgeTile : t.cell_start[I], qJ = kind == 0 ? J * kEdgeTile : t.cell_start[J];
+        const int nI = kind == 0 ? (int)std::min<int64_t>(kEdgeTile, t.N - qI) : t.cell_start[I + 1] - qI;
+        const int nJ = kind == 0 ? (int)std::min<int64_t>(kEdgeTile, t.N - qJ) : t.cell_start[J + 1] - qJ;
+        E.F = kind == 0 ? P.TAd.as<float2>() + (long)b * kEdgeTile * kEdgeTile : P.Vd.as<float2>() + vd_off[b];
+        E.start = rows ? qJ : qI;
+        E.k = rows ? nJ : nI;
+        E.len = kind == 0 ? kEdgeTile : nJ;
       }
       ent[e] = E;
     }
@@ -980,38 +863,23 @@ rfcmp_status hm_matvec(rfcmp_op op, int which, bool conj, const double2* x, doub
   ta.row0 = H.cell_start.as<int>();
   ta.list_ptr = H.list_ptr.as<int>();
   ta.ent = which == 0 ? P.entA.as<HmEnt>() : P.entV.as<HmEnt>();
-  ta.dense_ij = H.dense_ij.as<int2>();
-  ta.D = which == 0 ? P.TAd.as<float2>() : P.Vd.as<float2>();
-  ta.doff = H.vd_off.as<long>();
-  ta.blk = which == 0 ? H.lrA.as<HmLr>() : H.lrV.as<HmLr>();
-  ta.rank = which == 0 ? P.rankA.as<int>() : P.rankV.as<int>();
-  ta.Up = which == 0 ? P.uA.as<float2*>() : P.uV.as<float2*>();
-  ta.Vp = which == 0 ? P.vA.as<float2*>() : P.vV.as<float2*>();
-  ta.zoff = which == 0 ? P.zwA.as<long>() : P.zwV.as<long>();
-  ta.zw = P.zw.as<double2>();
-  ta.xp = P.xp.as<double2>();
-  ta.conj = conj ? 1 : 0;
+  ta.zw = P.zw.as<double>();
+  ta.xp = P.xp.as<double>();
+  ta.sgn = conj ? -1.0 : 1.0;
+  const long tot = (long)n * kHmR;
   for (int r0 = 0; r0 < nr; r0 += kHmR) {
-    const int rr = std::min(kHmR, nr - r0);
-    const long tot = (long)n * rr;
-    hipLaunchKernelGGL(k_hm_gather, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, n, rr, ta.perm,
+    ta.nr = std::min(kHmR, nr - r0);
+    hipLaunchKernelGGL(k_hm_gather, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, n, ta.nr, ta.perm,
                        x + (long)r0 * n, P.xp.as<double2>());
-    // kernels for 1, 2, 4 or 8 right-hand sides: the smallest that holds rr
-    const int R = rr <= 1 ? 1 : (rr <= 2 ? 2 : (rr <= 4 ? 4 : 8));
-    typedef void (*Proj)(const HmLr*, const int*, float2* const*, float2* const*, const long*, const double2*, int,
-                         int, int, double2*);
-    typedef void (*Tile)(const TileArgs);
-    const Proj proj = R == 1 ? k_hm_proj<1> : (R == 2 ? k_hm_proj<2> : (R == 4 ? k_hm_proj<4> : k_hm_proj<8>));
-    const Tile tile = which == 0 ? (R == 1 ? k_hm_tile<0, 1> : (R == 2 ? k_hm_tile<0, 2> : (R == 4 ? k_hm_tile<0, 4>
-                                                                                                    : k_hm_tile<0, 8>)))
-                                 : (R == 1 ? k_hm_tile<1, 1> : (R == 2 ? k_hm_tile<1, 2> : (R == 4 ? k_hm_tile<1, 4>
-                                                                                                    : k_hm_tile<1, 8>)));
     if (nlr > 0)
-      hipLaunchKernelGGL(proj, dim3((unsigned)nlr), dim3(256), 0, s, ta.blk, ta.rank, ta.Up, ta.Vp, ta.zoff,
-                         P.xp.as<double2>(), n, rr, ta.conj, P.zw.as<double2>());
-    ta.nr = rr;
-    ta.y = y + (long)r0 * n;
-    hipLaunchKernelGGL(tile, dim3((unsigned)t.ntiles), dim3(256), 0, s, ta);
+      hipLaunchKernelGGL(k_hm_proj, dim3((unsigned)nlr, 2), dim3(256), 0, s,
+                         which == 0 ? H.lrA.as<HmLr>() : H.lrV.as<HmLr>(),
+                         which == 0 ? P.rankA.as<int>() : P.rankV.as<int>(),
+                         which == 0 ? P.uA.as<float2*>() : P.uV.as<float2*>(),
+                         which == 0 ? P.vA.as<float2*>() : P.vV.as<float2*>(),
+                         which == 0 ? P.zwA.as<long>() : P.zwV.as<long>(), ta.xp, ta.sgn, P.zw.as<double>());
+    void (*tile)(const TileArgs, double*) = which == 0 ? k_hm_tile<0> : k_hm_tile<1>;
+    hipLaunchKernelGGL(tile, dim3((unsigned)t.ntiles), dim3(256), 0, s, ta, reinterpret_cast<double*>(y + (long)r0 * n));
     RF_HIP(hipGetLastError());
   }
   return RFCMP_OK;
