@@ -1541,7 +1541,7 @@ rfcmp_status rfcmp_op_create_many(rfcmp_mesh m, const double* k, int32_t nk, con
       RF_TRY(op->Vb.alloc(sizeof(float2) * C * op->ldV));
     }
     RF_TRY(ensure_work(op.get(), 4));
-    RF_TRY(op->symv_scratch.alloc(symv_scratch_bytes(N, 4) + symv_scratch_bytes(C, 4) + symv_scratch_bytes(V, 4)));
+    RF_TRY(op->symv_scratch.alloc(symv_scratch_bytes(N, 8) + symv_scratch_bytes(C, 8) + symv_scratch_bytes(V, 8)));
     RF_TRY(assemble_blocks(op.get(), asm_scratch, s));
   }
   for (int32_t i = 0; i < nk; ++i) RF_TRY(ready_projectors(ops[i].get(), s));

@@ -37,7 +37,7 @@ struct SymvJob {
   int nrhs = 0;          // job 1 of a pair: 1 of 2 right-hand sides, or 0 = all
 };
 
-// Bytes of scratch one job of size n needs (partial sums, up to 4
+// Bytes of scratch one job of size n needs (partial sums, up to 8
 // right-hand sides per pass); jobs launched together need the sum.
 size_t symv_scratch_bytes(int64_t n, int nrhs);
 

@@ -41,6 +41,7 @@ namespace {
 
 typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef double vd2 __attribute__((ext_vector_type(2)));
+typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 // rows per sub-tile for block size S: the sub-tile is 4 KB of pairs per 256 threads
@@ -50,11 +51,24 @@ constexpr int rows_sub() { return S == 128 ? 32 : 16; }
 // (two at S = 128), so rows are padded to start 128 bytes apart in the banks.
 template <int S>
 constexpr int tile_ld() { return S / 2 + 8; }
-constexpr int kMaxNR = 4;      // right-hand sides per pass
 
 // Entry e (0, 1) of a 16-byte column pair, widened to FP64 (re, im).
 struct C64 {
   typedef vf4 Pair;
+  static constexpr bool kComplex = true;
+  // operand h of the transposed sums for column e of a load: (im, re) of its
+  // rows 2 h, 2 h + 1, by an exchange of the odd rows of lanes of im with the
+  // even ones of re
+  __device__ static inline double col_operand(const Pair& v, int e, int h) {
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(e ? v.w : v.y), __float_as_uint(e ? v.z : v.x),
+                                                    false, false);
+    return (double)__uint_as_float(t[h]);
+  }
+  typedef float Row;
+  __device__ static inline void mac(double ar, double ai, const double2& x, double& re, double& im) {
+    re = fma(ar, x.x, fma(-ai, x.y, re));
+    im = fma(ar, x.y, fma(ai, x.x, im));
+  }
   __device__ static inline Pair first_only(Pair v) {
     v.z = 0.0f;
     v.w = 0.0f;
@@ -69,6 +83,13 @@ struct C64 {
 };
 struct F64 {
   typedef vd2 Pair;
+  static constexpr bool kComplex = false;
+  __device__ static inline double col_operand(const Pair& v, int e, int) { return e ? v.y : v.x; }
+  typedef double Row;
+  __device__ static inline void mac(double ar, double, const double2& x, double& re, double& im) {
+    re = fma(ar, x.x, re);
+    im = fma(ar, x.y, im);
+  }
   __device__ static inline Pair first_only(Pair v) {
     v.y = 0.0;
     return v;
@@ -107,6 +128,8 @@ struct JobsArg {
   JobArg j[2];
   int nblk0;
   int nsb0;
+  int nr;   // right-hand sides of job 0
+  int nr1;  // of job 1
 };
 
 // DPP move of a double: lane i takes the value of the lane CTRL selects
@@ -173,13 +196,19 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
   }
   SYMV_LOAD(ra, 0)
   SYMV_LOAD(rb, 1)
-  for (int t = tid; t < 2 * NR * S; t += kThreads) {
-    const int side = t / (NR * S), r = (t / S) % NR, i = t % S;
+#pragma unroll
+  for (int t = tid; t < 2 * S; t += kThreads) {
+    const int side = t / S, i = t % S;
     const int g = (side == 0 ? P : Q) * S + i;
     // x_Q is stored even columns first, then odd ones, so that the row sums
     // (neighbouring threads, neighbouring pairs) read it without bank conflicts
     const int slot = side ? (i & 1) * (S / 2) + (i >> 1) : i;
-    xs[side][r][slot] = (!EDGE || g < n) ? input_entry(in, r, g) : make_double2(0.0, 0.0);
+    double2 v[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) v[r] = make_double2(0.0, 0.0);
+    if (!EDGE || g < n) input_entries(in, 0, NR, g, v);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) xs[side][r][slot] = v[r];
   }
 
   double cr[2][NR], ci[2][NR];  // transposed sums of the two columns
@@ -199,9 +228,7 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
           double ar, ai;                                                                           \
           T::template entry<CONJ>(REG[q], e, ar, ai);                                              \
           _Pragma("unroll") for (int r = 0; r < NR; ++r) {                                         \
-            const double2 xv = xs[0][r][lr];                                                       \
-            cr[e][r] = fma(ar, xv.x, fma(-ai, xv.y, cr[e][r]));                                    \
-            ci[e][r] = fma(ar, xv.y, fma(ai, xv.x, ci[e][r]));                                     \
+            T::mac(ar, ai, xs[0][r][lr], cr[e][r], ci[e][r]);                                      \
           }                                                                                        \
         }                                                                                          \
       }                                                                                            \
@@ -219,9 +246,7 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
         double ar, ai;                                                                             \
         T::template entry<CONJ>(v, e, ar, ai);                                                     \
         _Pragma("unroll") for (int r = 0; r < NR; ++r) {                                           \
-          const double2 xv = xs[1][r][e * (S / 2) + pc];                                           \
-          rr[r] = fma(ar, xv.x, fma(-ai, xv.y, rr[r]));                                            \
-          ri[r] = fma(ar, xv.y, fma(ai, xv.x, ri[r]));                                             \
+          T::mac(ar, ai, xs[1][r][e * (S / 2) + pc], rr[r], ri[r]);                                \
         }                                                                                          \
       }                                                                                            \
     }                                                                                              \
@@ -302,6 +327,275 @@ __global__ __launch_bounds__(kThreads) void k_symv(const JobsArg args) {
   }
 }
 
+// ---- three to eight right-hand sides: the FP64 matrix cores
+//
+// With several right-hand sides the vector form above is bound by its LDS
+// reads of x (three 16-byte reads per right-hand side and matrix pair).  Here
+// both sums of a block are products with a 16-column operand, 8 right-hand
+// sides by (re, im), on v_mfma_f64_16x16x4, which adds its four terms to the
+// accumulator as a chain of fused multiply-adds in the order k = 0..3.  Each
+// chain of the vector form (a row group of a column, a thread's pairs of a
+// row) is therefore kept as the K dimension of an accumulator of its own, and
+// the chains meet in the same tree: a right-hand side has the same bits
+// whichever others go with it.
+//
+// A workgroup of four waves owns a block.  It walks stages of 32 KB (32 rows at
+// S = 128, 16 at S = 256), two in flight: a wave loads its S / 4 columns (four
+// rows a load, in operand order: lane l takes column pair l % 16 of row
+// l / 16), takes the transposed sums M^T x_P straight from the registers
+// (tiles of 16 columns by G row groups), and stores the stage to LDS, from where it forms four of the
+// chains of 16 rows of M x_Q.  For complex64 K holds (im, re) of two entries;
+// in the transposed sums an exchange between neighbouring rows of 16 lanes
+// turns a load into the operands of its first and its last two rows.  x sits
+// in LDS as [entry][right-hand side][re, im], the right-hand sides of an entry
+// exchanged by its number, so that neither the stores nor the operand reads
+// meet in a bank.
+constexpr int kMfmaNR = 8;  // right-hand sides per pass
+template <class T>
+constexpr int kMfmaMinNR = T::kComplex ? 5 : 3;
+template <int S>
+struct MfmaLds {
+  static constexpr int kRows = 4096 / S;  // rows per stage: 32 KB
+  static constexpr int kQuads = S / 64;   // groups of four chains of a row
+  struct Work {
+    vf4 tile[kRows][S / 2 + 1];        // rows start 16 bytes apart in the banks
+    double2 rowsum[kQuads][kRows][9];  // chains summed by fours
+    double2 xp[kRows][kMfmaNR];        // x_P of a stage, grouped by row % G
+    double2 xq[S][kMfmaNR];
+  };
+  union {
+    Work wk;
+    double2 col[S][9];  // transposed sums on their way out
+  };
+};
+
+__device__ inline double xor_sign(double v, unsigned mask) {
+  return __hiloint2double(__double2hiint(v) ^ (int)mask, __double2loint(v));
+}
+
+template <class T, int S, bool CONJ, bool EDGE>
+__device__ void symv_block_mfma(const char* __restrict__ strip, int n, int ldp, int P, int Q, int nr,
+                                const SymvInput& in, double2* __restrict__ part, int nsb, MfmaLds<S>& lds) {
+  typedef typename T::Pair Pair;
+  constexpr bool kComplex = T::kComplex;
+  constexpr int kQuads = MfmaLds<S>::kQuads;
+  constexpr int G = kThreads / (S / 2);          // row groups of the transposed sums
+  constexpr int TPR = kThreads / rows_sub<S>();  // chains of a row
+  constexpr int kRows = MfmaLds<S>::kRows;
+  constexpr int ML = kRows / (4 * G);            // loads per row group, column pair and stage
+  constexpr int NST = S / kRows;
+  constexpr int NP = S / 128;                    // column pairs per lane
+  constexpr int RT = kRows / 16;                 // row tiles per stage
+  static_assert(ML == 2 && kQuads * RT == 4, "a wave forms four chains of 16 rows");
+  static_assert(TPR == 4 * kQuads && S / 2 == 8 * TPR, "four chains of eight pairs a wave");
+  const bool diag = (P == Q);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, k = lane >> 4;
+  // row of a load's lane group: complex rows 1 and 2 change places for the
+  // lane exchange
+  const int kr = kComplex ? ((k & 1) << 1 | k >> 1) : k;
+
+  const int gc = Q * S + 32 * NP * w + 2 * li;  // first pair; the second 32 columns on
+  const unsigned ldb = (unsigned)ldp * 16u;
+  const unsigned off0 = (unsigned)(G * kr) * ldb + (unsigned)(gc >> 1) * 16u;
+  Pair ra[G][ML][NP];
+  auto load = [&](Pair(&reg)[G][ML][NP], int st) {
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          const int row = st * kRows + 4 * G * m + g;
+          const Pair* a = reinterpret_cast<const Pair*>(strip + off0 + (unsigned)row * ldb) + 16 * q;
+          if (EDGE) {
+            const int c = gc + 32 * q;
+            Pair v = zero_pair<T>();
+            if (P * S + row + G * kr < n && c < n) v = __builtin_nontemporal_load(a);
+            reg[g][m][q] = c + 1 < n ? v : T::first_only(v);
+          } else {
+            reg[g][m][q] = __builtin_nontemporal_load(a);
+          }
+        }
+  };
+  load(ra, 0);
+  // x_Q goes to LDS whole; x_P stays with the thread of its row until the
+  // stage before its own
+  double2 xr[kMfmaNR];
+  auto form = [&](int g) {
+#pragma unroll
+    for (int r0 = 0; r0 < kMfmaNR; r0 += 4) {
+      double2 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = make_double2(0.0, 0.0);
+      if ((!EDGE || g < n) && r0 < nr) input_entries(in, r0, nr, g, v);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) xr[r0 + u] = v[u];
+    }
+  };
+  auto put = [&](double2(*dst)[kMfmaNR], int slot) {
+#pragma unroll
+    for (int r = 0; r < kMfmaNR; ++r) dst[slot][r ^ (slot & 7)] = xr[r];
+  };
+  const int xi = tid % S;
+  if (S == kThreads || tid >= S) {
+    form(Q * S + xi);
+    put(lds.wk.xq, xi);
+  }
+  if (S == kThreads || tid < S) form(P * S + xi);
+  auto put_xp = [&](int st) {
+    if (tid / kRows == st) put(lds.wk.xp, (xi % G) * (kRows / G) + (xi % kRows) / G);
+  };
+  put_xp(0);
+
+  // operand columns: right-hand side li / 2, its re or im by li & 1; against
+  // an imaginary part (complex, even k) the other part of x with its sign
+  const bool im_k = kComplex && !(k & 1);
+  const int rr = li >> 1, cc = im_k ? (li & 1) ^ 1 : li & 1;
+  const unsigned sgn = im_k && (li & 1) == (CONJ ? 1 : 0) ? 0x80000000u : 0u;
+  // the entry this lane holds of an operand of the transposed sums, ...
+  const int kx = kComplex ? k >> 1 : k;
+  const char* xp = reinterpret_cast<const char*>(&lds.wk.xp[kx][0]) + cc * 8;
+  const int xp_rot = (rr ^ kx) << 4;
+  // ... and of the rows (pair kp, column ke of it): the wave forms chains
+  // 4 quad .. + 3 of rows 16 rt .. + 15
+  const int quad = w / RT, rt = w % RT;
+  const int ke = kComplex ? k >> 1 : k & 1, kp = kComplex ? 0 : k >> 1;
+  const char* xq = reinterpret_cast<const char*>(&lds.wk.xq[2 * (4 * quad + TPR * kp) + ke][0]) + cc * 8;
+  const int xq_rot = (rr ^ ke) << 4;
+  const char* at = reinterpret_cast<const char*>(&lds.wk.tile[16 * rt + li][4 * quad + TPR * kp]) +
+                   (kComplex ? (k ^ 1) * 4 : (k & 1) * 8);
+
+  dbl4 col[G][2 * NP];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < 2 * NP; ++e) col[g][e] = dbl4{0.0, 0.0, 0.0, 0.0};
+  __syncthreads();  // x ready
+
+  constexpr int kH = kComplex ? 2 : 1;  // operands per load
+  auto columns = [&](const Pair(&reg)[G][ML][NP]) {
+    double b[ML][kH][G];
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+      for (int h = 0; h < kH; ++h) {
+        // slot of the lane's entry: a multiple of 8, + 4 m + 2 h + kx
+        const char* xm = xp + (4 * m + 2 * h) * 128 + (xp_rot ^ ((4 * m + 2 * h) << 4));
+#pragma unroll
+        for (int g = 0; g < G; ++g) b[m][h][g] = *reinterpret_cast<const double*>(xm + g * (kRows / G) * 128);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+      for (int h = 0; h < kH; ++h)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < 2 * NP; ++e)
+            col[g][e] = __builtin_amdgcn_mfma_f64_16x16x4f64(T::col_operand(reg[g][m][e / 2], e & 1, h),
+                                                             xor_sign(b[m][h][g], sgn), col[g][e], 0, 0, 0);
+  };
+  auto rows = [&]() {
+    dbl4 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = dbl4{0.0, 0.0, 0.0, 0.0};
+    constexpr int kStep = kComplex ? 1 : 2;  // pairs of a chain per operand
+    typename T::Row a[2][4];
+    double b[2][4];
+    auto operands = [&](int u) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        a[u & 1][j] = *reinterpret_cast<const typename T::Row*>(at + (TPR * kStep * u + j) * 16);
+        b[u & 1][j] =
+            *reinterpret_cast<const double*>(xq + 2 * (TPR * kStep * u + j) * 128 + (xq_rot ^ (2 * j << 4)));
+      }
+    };
+    operands(0);
+#pragma unroll
+    for (int u = 0; u < 8 / kStep; ++u) {
+      if (u + 1 < 8 / kStep) operands(u + 1);  // leave LDS while this step's products run
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[u & 1][j], xor_sign(b[u & 1][j], sgn), acc[j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    double* out = &lds.wk.rowsum[quad][16 * rt + k][0].x + li;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out[4 * v * 18] = (acc[0][v] + acc[1][v]) + (acc[2][v] + acc[3][v]);
+  };
+  // the sums of four chains meet across the waves: (Q1 + Q0), at S = 256
+  // (Q3 + Q2) + (Q1 + Q0)
+  auto finish_rows = [&](int st) {
+    const int r = tid / kRows, i = tid % kRows;
+    if (r >= nr) return;
+    const double2 a0 = lds.wk.rowsum[0][i][r], a1 = lds.wk.rowsum[1][i][r];
+    double2 t = make_double2(a1.x + a0.x, a1.y + a0.y);
+    if (kQuads == 4) {
+      const double2 a2 = lds.wk.rowsum[kQuads - 2][i][r], a3 = lds.wk.rowsum[kQuads - 1][i][r];
+      t = make_double2((a3.x + a2.x) + t.x, (a3.y + a2.y) + t.y);
+    }
+    part[(((long)P * nsb + Q) * nr + r) * S + st * kRows + i] = t;
+  };
+  auto stage = [&](Pair(&reg)[G][ML][NP], int st, auto more) {
+    if (!diag) columns(reg);
+    __syncthreads();  // the rows of the stage before are done with the tile, their sums are in LDS
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          *reinterpret_cast<Pair*>(&lds.wk.tile[G * (4 * m + kr) + g][16 * (NP * w + q) + li]) = reg[g][m][q];
+    if (more) load(reg, st + 1);
+    put_xp(st + 1);
+    if (st > 0) finish_rows(st - 1);
+    __syncthreads();
+    rows();
+  };
+#pragma unroll 1
+  for (int st = 0; st < NST - 1; ++st) stage(ra, st, std::true_type());
+  stage(ra, NST - 1, std::false_type());
+  __syncthreads();
+  finish_rows(NST - 1);
+  if (diag) return;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2 * NP; ++e)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double t = 0.0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) t += col[g][e][v];
+      (&lds.col[32 * (NP * w + e / 2) + 2 * (4 * v + k) + (e & 1)][0].x)[li] = t;
+    }
+  __syncthreads();
+  for (int t = tid; t < S * nr; t += kThreads)
+    part[(((long)Q * nsb + P) * nr + t / S) * S + t % S] = lds.col[t % S][t / S];
+}
+
+template <class T, int S, bool CONJ>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_symv_mfma(const JobsArg args) {
+  const int job = (int)blockIdx.x < args.nblk0 ? 0 : 1;
+  const JobArg& ja = args.j[job];
+  const int n = ja.n, nsb = ja.nsb;
+  int P = 0, rem = (int)blockIdx.x - (job ? args.nblk0 : 0);
+  while (rem >= nsb - P) {
+    rem -= nsb - P;
+    ++P;
+  }
+  const int Q = P + rem;
+  __shared__ MfmaLds<S> lds;
+  const char* strip = static_cast<const char*>(ja.M) + (size_t)P * S * (size_t)ja.ldp * 16;
+  if ((Q + 1) * S <= n)
+    symv_block_mfma<T, S, CONJ, false>(strip, n, (int)ja.ldp, P, Q, args.nr, ja.in, ja.part, nsb, lds);
+  else
+    symv_block_mfma<T, S, CONJ, true>(strip, n, (int)ja.ldp, P, Q, args.nr, ja.in, ja.part, nsb, lds);
+}
+
 // y[r][K S + i] = sum over L (in order) of part[K][L][r][i].  Workgroup
 // (K, r): eight threads per row each add an eighth of the slots (all loads
 // issued before the adds, so they overlap), then the eighths are added in
@@ -309,14 +603,14 @@ __global__ __launch_bounds__(kThreads) void k_symv(const JobsArg args) {
 // job 1.
 template <int S>
 constexpr int red_parts() { return 1024 / S; }
-template <int S, int NR0, int NR1>
+template <int S>
 __global__ __launch_bounds__(1024) void k_symv_reduce(const JobsArg args) {
   constexpr int kRedParts = red_parts<S>();
   __shared__ double2 q8[kRedParts][S];
   const int job = (int)blockIdx.x < args.nsb0 ? 0 : 1;
   const JobArg& ja = args.j[job];
   const int n = ja.n, nsb = ja.nsb;
-  const int NR = job ? NR1 : NR0;
+  const int NR = job ? args.nr1 : args.nr;
   const int K = (int)blockIdx.x - (job ? args.nsb0 : 0), r = blockIdx.y;
   if (r >= NR) return;
   const int i = threadIdx.x % S, qt = threadIdx.x / S;
@@ -354,20 +648,51 @@ constexpr int kSmax = 256, kSmin = 128;
 
 // The product kernel is timed under `tag` (one right-hand side) or
 // "<tag>_nr<k>" (k right-hand sides), the slot sums under "symv_reduce".
-template <class T, int S, int NR0, int NR1, bool CONJ>
-void launch(const JobsArg& a, int nblk, int nsbsum, hipStream_t s, const char* tag) {
+template <int S, class F>
+void launch(const JobsArg& a, int nsbsum, hipStream_t s, const char* tag, F product) {
   {
-    ProfScope prof(NR0 == 1 ? tag : profile_tag_suffix(tag, NR0), s);
-    hipLaunchKernelGGL((k_symv<T, S, NR0, NR1, CONJ>), dim3((unsigned)nblk), dim3(kThreads), 0, s, a);
+    ProfScope prof(a.nr == 1 ? tag : profile_tag_suffix(tag, a.nr), s);
+    product();
   }
   ProfScope prof("symv_reduce", s);
-  constexpr int NRM = NR0 > NR1 ? NR0 : NR1;
-  hipLaunchKernelGGL((k_symv_reduce<S, NR0, NR1>), dim3((unsigned)nsbsum, NRM), dim3(1024), 0, s, a);
+  hipLaunchKernelGGL(k_symv_reduce<S>, dim3((unsigned)nsbsum, (unsigned)a.nr), dim3(1024), 0, s, a);
+}
+template <class T, int S, int NR0, int NR1, bool CONJ>
+void launch_vec(const JobsArg& a, int nblk, hipStream_t s) {
+  hipLaunchKernelGGL((k_symv<T, S, NR0, NR1, CONJ>), dim3((unsigned)nblk), dim3(kThreads), 0, s, a);
+}
+template <class T, int S, bool CONJ>
+void launch_any(const JobsArg& a, int nblk, int nsbsum, hipStream_t s, const char* tag) {
+  launch<S>(a, nsbsum, s, tag, [&] {
+    if (a.nr >= kMfmaMinNR<T>) {
+      hipLaunchKernelGGL((k_symv_mfma<T, S, CONJ>), dim3((unsigned)nblk), dim3(kThreads), 0, s, a);
+    } else if (a.nr == 1) {
+      launch_vec<T, S, 1, 1, CONJ>(a, nblk, s);
+    } else if (a.nr == 2) {
+      if (a.nr1 == 1)
+        launch_vec<T, S, 2, 1, CONJ>(a, nblk, s);
+      else
+        launch_vec<T, S, 2, 2, CONJ>(a, nblk, s);
+    } else if constexpr (T::kComplex) {
+      if (a.nr == 3)
+        launch_vec<T, S, 3, 3, CONJ>(a, nblk, s);
+      else
+        launch_vec<T, S, 4, 4, CONJ>(a, nblk, s);
+    }
+  });
 }
 
 // Block size: 256 x 256 blocks (longer streams per workgroup, fewer slots)
 // once they still give the grid a few hundred workgroups, else 128 x 128.
 constexpr int kMinBlocks256 = 400;
+long blocks_of(int64_t n, int S) {
+  const long nb = (n + S - 1) / S;
+  return nb * (nb + 1) / 2;
+}
+size_t part_bytes(int64_t n, int nr, int S) {
+  const int64_t nsb = (n + S - 1) / S;
+  return sizeof(double2) * (size_t)(nsb * nsb * nr * S);
+}
 
 // Advance every source pointer of an input by r0 right-hand sides.
 SymvInput shift_input(SymvInput in, int r0) {
@@ -384,38 +709,37 @@ rfcmp_status symv_any(const SymvJob* jobs, int njobs, int nrhs, void* scratch, s
     return RFCMP_E_ARG;
   }
   if (nrhs <= 0) return RFCMP_OK;
-  // right-hand sides of each job: nrhs, or fewer for job 1 (a product riding
-  // along with fewer columns; then nrhs <= kMaxNR)
+  // right-hand sides of each job: nrhs, or 1 of 2 for job 1 (a product riding
+  // along with fewer columns)
   int jn[2] = {nrhs, nrhs};
   if (njobs == 2 && jobs[1].nrhs > 0 && jobs[1].nrhs < nrhs) {
-    if (nrhs > kMaxNR || !(nrhs == 2 && jobs[1].nrhs == 1)) {
+    if (!(nrhs == 2 && jobs[1].nrhs == 1)) {
       set_error("symv: job 1 with %d of %d right-hand sides is not supported", jobs[1].nrhs, nrhs);
       return RFCMP_E_ARG;
     }
     jn[1] = jobs[1].nrhs;
   }
-  size_t need = 0;
+  long blocks_big = 0;
   for (int q = 0; q < njobs; ++q) {
     if (jobs[q].n <= 0 || jobs[q].ld % 2 != 0 || jobs[q].ld < jobs[q].n) {
       set_error("symv: job %d has n = %lld, ld = %lld", q, (long long)jobs[q].n, (long long)jobs[q].ld);
       return RFCMP_E_ARG;
     }
-    need += symv_scratch_bytes(jobs[q].n, std::min(jn[q], kMaxNR));
+    blocks_big += blocks_of(jobs[q].n, kSmax);
   }
+  const int S = blocks_big >= kMinBlocks256 ? kSmax : kSmin;
+  size_t need = 0;
+  for (int q = 0; q < njobs; ++q) need += part_bytes(jobs[q].n, std::min(jn[q], kMfmaNR), S);
   if (need > scratch_bytes) {
     set_error("symv: needs %zu bytes of scratch, %zu given", need, scratch_bytes);
     return RFCMP_E_ARG;
   }
-  long blocks_big = 0;
-  for (int q = 0; q < njobs; ++q) {
-    const long nb = (jobs[q].n + kSmax - 1) / kSmax;
-    blocks_big += nb * (nb + 1) / 2;
-  }
-  const int S = blocks_big >= kMinBlocks256 ? kSmax : kSmin;
-  for (int r0 = 0; r0 < nrhs; r0 += kMaxNR) {
-    const int nr = std::min(kMaxNR, nrhs - r0);
+  for (int r0 = 0, nr = 0; r0 < nrhs; r0 += nr) {
+    nr = std::min(kMfmaNR, nrhs - r0);
     const bool split = jn[1] != nrhs;  // job 1: one column (nr == 2 here)
     JobsArg a{};
+    a.nr = nr;
+    a.nr1 = split ? 1 : nr;
     char* sp = static_cast<char*>(scratch);
     int nblk = 0, nsbsum = 0;
     for (int q = 0; q < njobs; ++q) {
@@ -428,7 +752,7 @@ rfcmp_status symv_any(const SymvJob* jobs, int njobs, int nrhs, void* scratch, s
       ja.in = shift_input(jb.in, r0);
       ja.part = reinterpret_cast<double2*>(sp);
       ja.y = jb.y + (long)r0 * jb.n;
-      sp += symv_scratch_bytes(jb.n, q == 1 && split ? 1 : nr);
+      sp += part_bytes(jb.n, q == 1 ? a.nr1 : nr, S);
       if (q == 0) {
         a.nblk0 = ja.nsb * (ja.nsb + 1) / 2;
         a.nsb0 = ja.nsb;
@@ -436,23 +760,10 @@ rfcmp_status symv_any(const SymvJob* jobs, int njobs, int nrhs, void* scratch, s
       nblk += ja.nsb * (ja.nsb + 1) / 2;
       nsbsum += ja.nsb;
     }
-#define RF_SYMV_NR(SV)                                                          \
-  if (split) {                                                                  \
-    launch<T, SV, 2, 1, CONJ>(a, nblk, nsbsum, s, tag);                         \
-  } else {                                                                      \
-    switch (nr) {                                                               \
-      case 1: launch<T, SV, 1, 1, CONJ>(a, nblk, nsbsum, s, tag); break;        \
-      case 2: launch<T, SV, 2, 2, CONJ>(a, nblk, nsbsum, s, tag); break;        \
-      case 3: launch<T, SV, 3, 3, CONJ>(a, nblk, nsbsum, s, tag); break;        \
-      default: launch<T, SV, 4, 4, CONJ>(a, nblk, nsbsum, s, tag); break;       \
-    }                                                                           \
-  }
-    if (S == kSmax) {
-      RF_SYMV_NR(kSmax)
-    } else {
-      RF_SYMV_NR(kSmin)
-    }
-#undef RF_SYMV_NR
+    if (S == kSmax)
+      launch_any<T, kSmax, CONJ>(a, nblk, nsbsum, s, tag);
+    else
+      launch_any<T, kSmin, CONJ>(a, nblk, nsbsum, s, tag);
   }
   RF_HIP(hipGetLastError());
   return RFCMP_OK;
@@ -461,10 +772,9 @@ rfcmp_status symv_any(const SymvJob* jobs, int njobs, int nrhs, void* scratch, s
 }  // namespace
 
 size_t symv_scratch_bytes(int64_t n, int nrhs) {
-  // the smaller block size needs the most slots
-  const int64_t nsb = (n + kSmin - 1) / kSmin;
-  const int nr = std::min(std::max(nrhs, 1), kMaxNR);
-  return sizeof(double2) * (size_t)(nsb * nsb * nr * kSmin);
+  // the smaller block size needs the most slots; a matrix that fills the chip
+  // with the larger one alone never takes it
+  return part_bytes(n, std::min(std::max(nrhs, 1), kMfmaNR), blocks_of(n, kSmax) >= kMinBlocks256 ? kSmax : kSmin);
 }
 
 rfcmp_status symv_form_input(const SymvInput& in, int64_t n, int nrhs, double2* out, hipStream_t s) {
