@@ -22,7 +22,8 @@
 // takes pairs s, s + 8, ..., so a row's threads read adjacent LDS words; the
 // eight partial sums meet through DPP lane moves).
 // Two sub-tiles are in flight per workgroup: the loads of sub-tile t + 2 are
-// issued as soon as sub-tile t sits in LDS.  Products are formed
+// issued as soon as sub-tile t sits in LDS, without a condition, so that the
+// wait for a sub-tile leaves the other one in flight.  Products are formed
 // and accumulated in FP64 (complex64 entries are widened), x and y are
 // complex128.
 //
@@ -32,6 +33,10 @@
 // needs, reading a few source entries per entry from L2.  One launch can
 // carry two products of the same element type (their blocks side by side in
 // the grid), so a small matrix rides along with a large one.
+//
+// Bound: the stream, together with the partial sums written beside it.  T_A at
+// N = 30720 takes 650 us (5.8 TB/s) with one right-hand side; the same blocks
+// read without any sums take 545 us, with the 59 MB of slot writes alone 650.
 #include "symv.h"
 #include "symv_input.h"
 
@@ -177,21 +182,25 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
   const int p = tid % PP, g0 = tid / PP;
   const int gc = Q * S + 2 * p;  // first global column of the pair
   const bool c0 = gc < n, c1 = gc + 1 < n;
-  const unsigned off0 = ((unsigned)g0 * (unsigned)ldp + (unsigned)(gc >> 1)) * 16u;
-  const unsigned rowstep = (unsigned)G * (unsigned)ldp * 16u;
-  const unsigned substep = (unsigned)kRowsSub * (unsigned)ldp * 16u;
+  const unsigned ldb = (unsigned)ldp * 16u;
+  const unsigned offc = (unsigned)((!EDGE || c0 ? gc : 0) >> 1) * 16u;
   Pair ra[LPT], rb[LPT];  // two sub-tiles in flight
 
+  // The loads are never conditional, so that a wait for one sub-tile leaves
+  // the other in flight: EDGE blocks read what lies beyond the matrix from a
+  // place inside it, and SYMV_MASK clears it once it is used.
 #define SYMV_LOAD(REG, SUB)                                                                        \
   _Pragma("unroll") for (int q = 0; q < LPT; ++q) {                                                \
-    const Pair* a = reinterpret_cast<const Pair*>(strip + off0 + (SUB) * substep + q * rowstep);   \
-    if (EDGE) {                                                                                    \
-      const int gr = P * S + (SUB) * kRowsSub + g0 + G * q;                                        \
-      Pair v = zero_pair<T>();                                                                     \
-      if (gr < n && c0) v = __builtin_nontemporal_load(a);                                         \
+    const int lr = (SUB) * kRowsSub + g0 + G * q;                                                  \
+    const unsigned row = EDGE ? (unsigned)min(lr, n - 1 - P * S) : (unsigned)lr;                   \
+    REG[q] = __builtin_nontemporal_load(reinterpret_cast<const Pair*>(strip + offc + row * ldb));  \
+  }
+#define SYMV_MASK(REG, SUB)                                                                        \
+  if (EDGE) {                                                                                      \
+    _Pragma("unroll") for (int q = 0; q < LPT; ++q) {                                              \
+      const bool in = P * S + (SUB) * kRowsSub + g0 + G * q < n && c0;                             \
+      const Pair v = in ? REG[q] : zero_pair<T>();                                                 \
       REG[q] = c1 ? v : T::first_only(v);                                                          \
-    } else {                                                                                       \
-      REG[q] = __builtin_nontemporal_load(a);                                                      \
     }                                                                                              \
   }
   SYMV_LOAD(ra, 0)
@@ -219,8 +228,9 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
   const int rrow = tid / TPR, seg = tid % TPR;  // row-sum layout
   __syncthreads();  // xs ready
 
-#define SYMV_CONSUME(REG, SUB)                                                                     \
+#define SYMV_CONSUME(REG, SUB, MORE)                                                               \
   {                                                                                                \
+    SYMV_MASK(REG, SUB)                                                                            \
     if (!diag) {                                                                                   \
       _Pragma("unroll") for (int q = 0; q < LPT; ++q) {                                            \
         const int lr = (SUB) * kRowsSub + g0 + G * q;                                              \
@@ -235,7 +245,7 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
     }                                                                                              \
     __syncthreads(); /* the previous row sums are done with the tile */                            \
     _Pragma("unroll") for (int q = 0; q < LPT; ++q) tile[g0 + G * q][p] = REG[q];                  \
-    if ((SUB) + 2 < NSUB) { SYMV_LOAD(REG, (SUB) + 2) }                                            \
+    if (MORE) { SYMV_LOAD(REG, (SUB) + 2) }                                                        \
     __syncthreads();                                                                               \
     double rr[NR], ri[NR];                                                                         \
     _Pragma("unroll") for (int r = 0; r < NR; ++r) rr[r] = ri[r] = 0.0;                            \
@@ -255,22 +265,28 @@ __device__ void symv_block(const char* __restrict__ strip, int n, int ldp, int P
       ri[r] = sum_lanes<TPR>(ri[r]);                                                               \
     }                                                                                              \
     if (seg == TPR - 4) {                                                                          \
-      const int i = (SUB) * kRowsSub + rrow;                                                       \
-      _Pragma("unroll") for (int r = 0; r < NR; ++r)                                               \
-        part[(((long)P * nsb + Q) * NR + r) * S + i] = make_double2(rr[r], ri[r]);                 \
+      const int i = (SUB) * kRowsSub + rrow; /* x_P of these rows has been read */                 \
+      _Pragma("unroll") for (int r = 0; r < NR; ++r) xs[0][r][i] = make_double2(rr[r], ri[r]);     \
     }                                                                                              \
   }
 #pragma unroll 1
-  for (int sub = 0; sub < NSUB; sub += 2) {
-    SYMV_CONSUME(ra, sub)
-    SYMV_CONSUME(rb, sub + 1)
+  for (int sub = 0; sub < NSUB - 2; sub += 2) {
+    SYMV_CONSUME(ra, sub, true)
+    SYMV_CONSUME(rb, sub + 1, true)
   }
+  SYMV_CONSUME(ra, NSUB - 2, false)
+  SYMV_CONSUME(rb, NSUB - 1, false)
 #undef SYMV_CONSUME
+#undef SYMV_MASK
 #undef SYMV_LOAD
 
+  // The row sums leave at the end: a store between the loads of a sub-tile
+  // would have to be complete before later loads count as arrived.
+  __syncthreads();
+  for (int t = tid; t < S * NR; t += kThreads)
+    part[(((long)P * nsb + Q) * NR + t / S) * S + t % S] = xs[0][t / S][t % S];
   if (!diag) {
     // reduce the transposed sums over the G row groups through LDS
-    __syncthreads();
     double2* red = reinterpret_cast<double2*>(&tile[0][0]);  // [G][S][NR]
     static_assert(sizeof(double2) * G * S * NR <= sizeof(Pair) * kRowsSub * tile_ld<S>(), "reduction fits the tile");
 #pragma unroll
@@ -350,7 +366,18 @@ __global__ __launch_bounds__(kThreads) void k_symv(const JobsArg args) {
 // in LDS as [entry][right-hand side][re, im], the right-hand sides of an entry
 // exchanged by its number, so that neither the stores nor the operand reads
 // meet in a bank.
+//
+// Bound: with FP64 entries the stream (8 right-hand sides do 32 flops a byte
+// at half the rate of the matrix cores), with complex64 the matrix cores,
+// which do 8 columns' work for 5.  At n = 9216 with 8 right-hand sides FP64
+// 100 us (two vector passes 210), with 4 90 us (102); complex64 with 7 135 us
+// (two passes 175).  At n <= 2000, where a product is one block's latency,
+// 4 right-hand sides 12-16 us (21-27), most of it the inputs, which are
+// gathered for all columns at once.
 constexpr int kMfmaNR = 8;  // right-hand sides per pass
+// From three FP64 columns on one pass here is the faster one (n = 9216: 86 us
+// to 95); a complex64 block needs two operands where FP64 needs one, so up to
+// four columns the vector form is (n = 9216: 117 us to 140).
 template <class T>
 constexpr int kMfmaMinNR = T::kComplex ? 5 : 3;
 template <int S>
@@ -397,7 +424,6 @@ __device__ void symv_block_mfma(const char* __restrict__ strip, int n, int ldp, 
 
   const int gc = Q * S + 32 * NP * w + 2 * li;  // first pair; the second 32 columns on
   const unsigned ldb = (unsigned)ldp * 16u;
-  const unsigned off0 = (unsigned)(G * kr) * ldb + (unsigned)(gc >> 1) * 16u;
   Pair ra[G][ML][NP];
   auto load = [&](Pair(&reg)[G][ML][NP], int st) {
 #pragma unroll
@@ -406,16 +432,23 @@ __device__ void symv_block_mfma(const char* __restrict__ strip, int n, int ldp, 
       for (int g = 0; g < G; ++g)
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
-          const int row = st * kRows + 4 * G * m + g;
-          const Pair* a = reinterpret_cast<const Pair*>(strip + off0 + (unsigned)row * ldb) + 16 * q;
-          if (EDGE) {
-            const int c = gc + 32 * q;
-            Pair v = zero_pair<T>();
-            if (P * S + row + G * kr < n && c < n) v = __builtin_nontemporal_load(a);
-            reg[g][m][q] = c + 1 < n ? v : T::first_only(v);
-          } else {
-            reg[g][m][q] = __builtin_nontemporal_load(a);
-          }
+          const int lr = st * kRows + 4 * G * m + g + G * kr, c = gc + 32 * q;
+          const unsigned row = EDGE ? (unsigned)min(lr, n - 1 - P * S) : (unsigned)lr;
+          const unsigned off = row * ldb + (unsigned)((EDGE && c >= n ? 0 : c) >> 1) * 16u;
+          reg[g][m][q] = __builtin_nontemporal_load(reinterpret_cast<const Pair*>(strip + off));
+        }
+  };
+  auto mask = [&](Pair(&reg)[G][ML][NP], int st) {  // clears what lies beyond the matrix
+#pragma unroll
+    for (int m = 0; m < ML; ++m)
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+          const int c = gc + 32 * q;
+          const bool in = P * S + st * kRows + 4 * G * m + g + G * kr < n && c < n;
+          const Pair v = in ? reg[g][m][q] : zero_pair<T>();
+          reg[g][m][q] = c + 1 < n ? v : T::first_only(v);
         }
   };
   load(ra, 0);
@@ -540,6 +573,7 @@ __device__ void symv_block_mfma(const char* __restrict__ strip, int n, int ldp, 
     part[(((long)P * nsb + Q) * nr + r) * S + st * kRows + i] = t;
   };
   auto stage = [&](Pair(&reg)[G][ML][NP], int st, auto more) {
+    if (EDGE) mask(reg, st);
     if (!diag) columns(reg);
     __syncthreads();  // the rows of the stage before are done with the tile, their sums are in LDS
 #pragma unroll
