@@ -40,19 +40,18 @@ __device__ inline double2 cfma(double a, double2 v, double2 acc) {
   return make_double2(fma(a, v.x, acc.x), fma(a, v.y, acc.y));
 }
 
-// Order the wave's LDS and global accesses: everything the wave wrote is
-// visible to all its lanes afterwards.
+// Order the LDS accesses of a wave, or of a workgroup.  Nothing that a step
+// writes to memory is read again before the kernel ends (the top) or the
+// subtree's next height begins (the bottom, behind __syncthreads), so neither
+// waits for stores or for loads under way.
 __device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-
-template <int TEAM>
 __device__ inline void team_sync() {
-  if (TEAM == 64)
-    wave_sync();
-  else
-    __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Sum over the 64 lanes of a wave, in a fixed order.
@@ -155,7 +154,7 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
       v[p * R + r] = val;
     }
   }
-  team_sync<TEAM>();
+  team_sync();
   {  // y_i = (L_ss^-1 v)_i: columns j <= i
     const Lanes L = lanes_of(t, TEAM, R, ncol);
     const double* M = A.linv + d1.y;
@@ -169,7 +168,7 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
       }
     }
   }
-  team_sync<TEAM>();
+  team_sync();
   {  // u_q = v_(ncol + q) - (L_21 y)_q
     const Lanes L = lanes_of(t, TEAM, R, nstr);
     const double* M = A.l21 + d1.z;
@@ -183,7 +182,7 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
       }
     }
   }
-  team_sync<TEAM>();
+  team_sync();
 }
 
 // Backward step of a supernode: x_s = L_ss^-T (y - L_21^T x_struct).
@@ -202,7 +201,7 @@ __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, in
     for (int q = t / R; q < nstr; q += TEAM / R)
       xs[q * R + r] = rg < NR ? x[(long)A.str[so + q] * NR + rg] : make_double2(0.0, 0.0);
   }
-  team_sync<TEAM>();
+  team_sync();
   {  // z_j = y_j - (L_21^T x_struct)_j
     const Lanes L = lanes_of(t, TEAM, R, ncol);
     const double* M = A.l21t + d1.z;  // (q, j) at M[q * ncol + j]
@@ -216,7 +215,7 @@ __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, in
       }
     }
   }
-  team_sync<TEAM>();
+  team_sync();
   {  // x_i = (L_ss^-T z)_i: rows j >= i
     const Lanes L = lanes_of(t, TEAM, R, ncol);
     const double* M = A.linvt + d1.y;  // (i, j) of L_ss^-T at M[j * ncol + i]
@@ -228,7 +227,7 @@ __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, in
       if (i < ncol && L.g == 0 && rg < NR) x[(long)(c0 + i) * NR + rg] = acc;
     }
   }
-  team_sync<TEAM>();
+  team_sync();
 }
 
 constexpr int kSpThreads = 1024;
@@ -330,89 +329,156 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_output(const SpArgs args) {
 }
 
 // A bottom supernode is solved by one wave from LDS (staged) when its blocks
-// hold at most kSpStageMax entries and its gather indices at most kSpIdxMax:
-// the wave issues the loads of the indices, its entries of the vector and
-// the blocks (512 entries per round) together, then those of the update
-// entries of its children (or, backward, the entries of its struct rows),
-// eight per lane per round, and forms both products from LDS, so a step
-// costs a few round trips to memory instead of one per row.
+// hold at most kSpStageMax entries and its gather indices at most kSpIdxMax.
+// What does not depend on other supernodes, the blocks, the gather indices and
+// the node's entries of the vector, is in registers before the step begins: it
+// is loaded while the supernode before is solved (SpStage), so that a step
+// waits for memory only once, for the update entries of its children (or,
+// backward, the entries of its struct rows).  The products read LDS some
+// columns ahead of their chains of sums.
 // A supernode that cannot be staged, and its ancestors, belong to the top.
+//
+// Bound: latency, a step after a step.  At level 5 with 64 right-hand sides
+// (n = 20480, 128 subtrees of up to 9 steps a wave) the forward sweep takes
+// 65 us and the backward one 48 (75 and 75 with the blocks loaded at the start
+// of their own step and every ordering of LDS waiting for the stores); at level
+// 6 with 8 right-hand sides 200 and 184 (250 and 214).
 constexpr int kSpStageMax = 1024;
 constexpr int kSpIdxMax = 256;
 __host__ __device__ inline bool sp_staged(int ncol, int nstr, int K) {
   return ncol * (ncol + nstr) <= kSpStageMax && (ncol + nstr) * K <= kSpIdxMax;
 }
 
-// Forward step of a staged supernode (descriptor record d0 = {col0, ncol,
-// str_off, nstr}, d1 = {front_off, blk_off, 0, 0}) on one wave (lane 0..63,
-// R right-hand sides from r0; a lane holds rows p0 + P a, a < ROWS, of the
-// node's columns: P ROWS >= ncol).  lds: the wave's slice, the front [m][R] first; F: the
-// blocks (L_ss^-1, then L_21, both column-major, as stored contiguously per
-// staged supernode at blk + blk_off); S: the gather indices.
 template <int ROWS>
-__device__ void wave_forward(const SpArg& A, int4 d0, int4 d1, int lane, int R, int r0, double2* lds, double* F,
-                             int* S, bool leaf) {
+struct SpStage {
+  double f[kSpStageMax / 64];  // the blocks, L_ss^-1 then L_21, column-major
+  int g[kSpIdxMax / 64];       // forward: sources of the front; backward: struct rows
+  double2 x[ROWS];             // the node's entries of the vector, rows p0 + P a
+};
+
+// Loads of a supernode's stage (descriptor record d0 = {col0, ncol, str_off,
+// nstr}, d1 = {front_off, blk_off, 0, 0}), R right-hand sides from r0.  None is
+// conditional on a lane: what lies beyond repeats the last entry.
+template <int ROWS, bool backward>
+__device__ inline void stage_load(SpStage<ROWS>& st, const SpArg& A, int4 d0, int4 d1, int lane, int R, int r0) {
+  const int ncol = d0.y, nstr = d0.w, m = ncol + nstr, nf = ncol * m;
+  const double* B = A.blk + d1.y;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) st.f[i] = B[min(lane + 64 * i, nf - 1)];
+  if (nf > 512) {
+#pragma unroll
+    for (int i = 8; i < kSpStageMax / 64; ++i) st.f[i] = B[min(lane + 64 * i, nf - 1)];
+  }
+  const int ni = backward ? nstr : m * A.fr_k;
+  const int* G = backward ? A.str + d0.z : A.fr_src + (long)d1.x * A.fr_k;
+  if (ni > 0) {
+#pragma unroll
+    for (int i = 0; i < kSpIdxMax / 64; ++i) st.g[i] = G[min(lane + 64 * i, ni - 1)];
+  }
+  const int p0 = lane / R, P = 64 / R, rg = min(r0 + (lane & (R - 1)), A.nrhs - 1);
+#pragma unroll
+  for (int a = 0; a < ROWS; ++a) st.x[a] = A.scratch[(long)(d0.x + min(p0 + P * a, ncol - 1)) * A.nrhs + rg];
+}
+// ... and into the wave's slice: F the blocks, S the indices.
+template <int ROWS>
+__device__ inline void stage_store(const SpStage<ROWS>& st, int nf, int ni, int lane, double* F, int* S) {
+#pragma unroll
+  for (int i = 0; i < kSpStageMax / 64; ++i)
+    if (lane + 64 * i < nf) F[lane + 64 * i] = st.f[i];
+#pragma unroll
+  for (int i = 0; i < kSpIdxMax / 64; ++i)
+    if (lane + 64 * i < ni) S[lane + 64 * i] = st.g[i];
+}
+
+// acc[a] += sum over j < n of F[j sj + min(p0 + P a, rows - 1) si] v[j R] where
+// keep(j, p0 + P a), j ascending, the next columns read ahead of the sums.
+template <int ROWS, class Keep>
+__device__ inline void lds_chain(double2 (&acc)[ROWS], const double* F, int sj, int si, int rows, const double2* v,
+                                 int R, int n, int p0, int P, Keep keep) {
+  int off[ROWS];
+#pragma unroll
+  for (int a = 0; a < ROWS; ++a) off[a] = min(p0 + P * a, rows - 1) * si;
+  constexpr int B = ROWS < 4 ? 4 : 2;  // columns ahead: what the registers hold
+  int j = 0;
+  for (; j + B <= n; j += B) {
+    double2 vj[B];
+    double f[B][ROWS];
+#pragma unroll
+    for (int e = 0; e < B; ++e) {
+      vj[e] = v[(j + e) * R];
+#pragma unroll
+      for (int a = 0; a < ROWS; ++a) f[e][a] = F[(j + e) * sj + off[a]];
+    }
+#pragma unroll
+    for (int e = 0; e < B; ++e)
+#pragma unroll
+      for (int a = 0; a < ROWS; ++a)
+        if (keep(j + e, p0 + P * a)) acc[a] = cfma(f[e][a], vj[e], acc[a]);
+  }
+  for (; j < n; ++j) {
+    const double2 vj = v[j * R];
+#pragma unroll
+    for (int a = 0; a < ROWS; ++a)
+      if (keep(j, p0 + P * a)) acc[a] = cfma(F[j * sj + off[a]], vj, acc[a]);
+  }
+}
+
+// Forward step of a staged supernode on one wave (lane 0..63, R right-hand
+// sides from r0; a lane holds rows p0 + P a, a < ROWS, of the node's columns:
+// P ROWS >= ncol).  lds: the wave's slice, the front [m][R] first.  `next`
+// issues the loads of the wave's next supernode.
+template <int ROWS, class Next>
+__device__ void wave_forward(const SpArg& A, const SpStage<ROWS>& st, int4 d0, double2 mu, int lane, int R, int r0,
+                             double2* lds, double* F, int* S, bool leaf, Next next) {
   const int NR = A.nrhs, K = A.fr_k;
   double2* x = A.scratch;
   double2* u = A.u();
-  const int c0 = d0.x, ncol = d0.y, so = d0.z, nstr = d0.w, fo = d1.x;
-  const double* B = A.blk + d1.y;
-  const int m = ncol + nstr, nn = ncol * ncol, nf = nn + ncol * nstr, nidx = leaf ? 0 : m * K;
+  const int c0 = d0.x, ncol = d0.y, so = d0.z, nstr = d0.w;
+  const int m = ncol + nstr, nn = ncol * ncol, nf = nn + ncol * nstr;
   const int r = lane & (R - 1), rg = r0 + r, P = 64 / R, p0 = lane / R;
   const bool live = rg < NR;
+  const int rgc = min(rg, NR - 1);
   const double2 zero = make_double2(0.0, 0.0);
   double2* v = lds;
-  // the blocks, the gather indices and the node's entries of the vector (the
-  // Laplacian's input mean taken off), all issued before any is used
-  int g[kSpIdxMax / 64];
-#pragma unroll
-  for (int i = 0; i < kSpIdxMax / 64; ++i) {
-    const int e = lane + 64 * i;
-    g[i] = e < nidx ? A.fr_src[(long)fo * K + e] : -1;
-  }
-  const double2 mu = (A.grounded && live) ? A.mean(0)[rg] : zero;
-  double2 xv[ROWS];
+  stage_store(st, nf, leaf ? 0 : m * K, lane, F, S);
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) {
     const int p = p0 + P * a;
-    xv[a] = (p < ncol && live) ? x[(long)(c0 + p) * NR + rg] : zero;
-  }
-  for (int e0 = lane; e0 < nf; e0 += 512) {
-    double f[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = e0 + 64 * i < nf ? B[e0 + 64 * i] : 0.0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (e0 + 64 * i < nf) F[e0 + 64 * i] = f[i];
-  }
-#pragma unroll
-  for (int i = 0; i < kSpIdxMax / 64; ++i)
-    if (lane + 64 * i < nidx) S[lane + 64 * i] = g[i];
-#pragma unroll
-  for (int a = 0; a < ROWS; ++a) {
-    const int p = p0 + P * a;
-    if (p < ncol) v[p * R + r] = make_double2(xv[a].x - mu.x, xv[a].y - mu.y);
+    if (p < ncol) v[p * R + r] = make_double2((live ? st.x[a].x : 0.0) - mu.x, (live ? st.x[a].y : 0.0) - mu.y);
   }
   for (int p = p0; p < m; p += P)
     if (p >= ncol) v[p * R + r] = zero;
   wave_sync();
   // the children's update entries, added per front entry in child order
-  if (!leaf) {
-    const int nw = ((m - p0 + P - 1) / P) * K;
-    for (int w0 = 0; w0 < nw; w0 += 8) {
+  if (leaf) {
+    next();
+  } else {
+    const int na = (m - p0 + P - 1) / P, nwave = (m + P - 1) / P * K;  // entries of this lane; sources of any
+    int a0 = 0, k0 = 0;  // the next entry p0 + P a0 and its source k0
+    for (int w0 = 0; w0 < nwave; w0 += 8) {
+      int g[8];
       double2 t[8];
+      int a = a0, k = k0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int w = w0 + i;
-        const int q = w < nw ? S[(p0 + P * (w / K)) * K + w % K] : -1;
-        t[i] = (q >= 0 && live) ? u[(long)q * NR + rg] : zero;
+        g[i] = a < na ? S[(p0 + P * a) * K + k] : -1;
+        t[i] = u[(long)max(g[i], 0) * NR + rgc];
+        if (++k == K) {
+          k = 0;
+          ++a;
+        }
       }
+      if (w0 == 0) next();
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int w = w0 + i;
-        if (w < nw) {
-          double2* vp = v + (p0 + P * (w / K)) * R + r;
-          *vp = cadd(*vp, t[i]);
+        if (a0 < na) {
+          const bool in = g[i] >= 0 && live;
+          double2* vp = v + (p0 + P * a0) * R + r;
+          *vp = cadd(*vp, make_double2(in ? t[i].x : 0.0, in ? t[i].y : 0.0));
+        }
+        if (++k0 == K) {
+          k0 = 0;
+          ++a0;
         }
       }
     }
@@ -422,15 +488,7 @@ __device__ void wave_forward(const SpArg& A, int4 d0, int4 d1, int lane, int R, 
   double2 y[ROWS];
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) y[a] = zero;
-#pragma unroll 2
-  for (int j = 0; j < ncol; ++j) {
-    const double2 vj = v[j * R + r];
-#pragma unroll
-    for (int a = 0; a < ROWS; ++a) {
-      const int i = p0 + P * a;
-      if (i < ncol && j <= i) y[a] = cfma(F[j * ncol + i], vj, y[a]);
-    }
-  }
+  lds_chain(y, F, ncol, 1, ncol, v + r, R, ncol, p0, P, [](int j, int i) { return j <= i; });
   wave_sync();
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) {
@@ -442,22 +500,14 @@ __device__ void wave_forward(const SpArg& A, int4 d0, int4 d1, int lane, int R, 
   }
   wave_sync();
   // u = v_struct - L_21 y
-  for (int q0 = p0; q0 < nstr; q0 += ROWS * P) {
+  for (int q0 = 0; q0 < nstr; q0 += ROWS * P) {
     double2 acc[ROWS];
 #pragma unroll
     for (int b = 0; b < ROWS; ++b) acc[b] = zero;
-#pragma unroll 2
-    for (int j = 0; j < ncol; ++j) {
-      const double2 yj = v[j * R + r];
-#pragma unroll
-      for (int b = 0; b < ROWS; ++b) {
-        const int q = q0 + P * b;
-        if (q < nstr) acc[b] = cfma(F[nn + j * nstr + q], yj, acc[b]);
-      }
-    }
+    lds_chain(acc, F + nn, nstr, 1, nstr, v + r, R, ncol, q0 + p0, P, [](int, int) { return true; });
 #pragma unroll
     for (int b = 0; b < ROWS; ++b) {
-      const int q = q0 + P * b;
+      const int q = q0 + p0 + P * b;
       if (q < nstr && live) {
         const double2 w = v[(ncol + q) * R + r];
         u[(long)(so + q) * NR + rg] = make_double2(w.x - acc[b].x, w.y - acc[b].y);
@@ -469,55 +519,37 @@ __device__ void wave_forward(const SpArg& A, int4 d0, int4 d1, int lane, int R, 
 
 // Backward step of a staged supernode on one wave: z = y - L_21^T x_struct,
 // x = L_ss^-T z, from the same blocks as the forward step.
-template <int ROWS>
-__device__ void wave_backward(const SpArg& A, int4 d0, int4 d1, int lane, int R, int r0, double2* lds, double* F,
-                              int* S) {
+template <int ROWS, class Next>
+__device__ void wave_backward(const SpArg& A, const SpStage<ROWS>& st, int4 d0, int lane, int R, int r0, double2* lds,
+                              double* F, int* S, Next next) {
   const int NR = A.nrhs;
   double2* x = A.scratch;
-  const int c0 = d0.x, ncol = d0.y, so = d0.z, nstr = d0.w;
-  const double* B = A.blk + d1.y;
+  const int c0 = d0.x, ncol = d0.y, nstr = d0.w;
   const int nn = ncol * ncol, nf = nn + ncol * nstr;
   const int r = lane & (R - 1), rg = r0 + r, P = 64 / R, p0 = lane / R;
   const bool live = rg < NR;
+  const int rgc = min(rg, NR - 1);
   const double2 zero = make_double2(0.0, 0.0);
   double2* xs = lds;             // x_struct [nstr][R]
   double2* z = lds + nstr * R;   // z [ncol][R]
-  int g[kSpIdxMax / 64];
-#pragma unroll
-  for (int i = 0; i < kSpIdxMax / 64; ++i) {
-    const int e = lane + 64 * i;
-    g[i] = e < nstr ? A.str[so + e] : 0;
-  }
+  stage_store(st, nf, nstr, lane, F, S);
   double2 yv[ROWS];  // the forward step's y
 #pragma unroll
-  for (int a = 0; a < ROWS; ++a) {
-    const int j = p0 + P * a;
-    yv[a] = (j < ncol && live) ? x[(long)(c0 + j) * NR + rg] : zero;
-  }
-  for (int e0 = lane; e0 < nf; e0 += 512) {
-    double f[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) f[i] = e0 + 64 * i < nf ? B[e0 + 64 * i] : 0.0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (e0 + 64 * i < nf) F[e0 + 64 * i] = f[i];
-  }
-#pragma unroll
-  for (int i = 0; i < kSpIdxMax / 64; ++i)
-    if (lane + 64 * i < nstr) S[lane + 64 * i] = g[i];
+  for (int a = 0; a < ROWS; ++a) yv[a] = make_double2(live ? st.x[a].x : 0.0, live ? st.x[a].y : 0.0);
   wave_sync();
   // x_struct: the solution on the struct rows
-  for (int q0 = p0; q0 < nstr; q0 += 8 * P) {
+  if (nstr == 0) next();
+  for (int q0 = 0; q0 < nstr; q0 += 8 * P) {
     double2 t[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int q = q0 + P * i;
-      t[i] = (q < nstr && live) ? x[(long)S[q] * NR + rg] : zero;
+      t[i] = x[(long)S[min(q0 + p0 + P * i, nstr - 1)] * NR + rgc];
     }
+    if (q0 == 0) next();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int q = q0 + P * i;
-      if (q < nstr) xs[q * R + r] = t[i];
+      const int q = q0 + p0 + P * i;
+      if (q < nstr) xs[q * R + r] = make_double2(live ? t[i].x : 0.0, live ? t[i].y : 0.0);
     }
   }
   wave_sync();
@@ -525,15 +557,7 @@ __device__ void wave_backward(const SpArg& A, int4 d0, int4 d1, int lane, int R,
   double2 acc[ROWS];
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) acc[a] = zero;
-#pragma unroll 2
-  for (int q = 0; q < nstr; ++q) {
-    const double2 xq = xs[q * R + r];
-#pragma unroll
-    for (int a = 0; a < ROWS; ++a) {
-      const int j = p0 + P * a;
-      if (j < ncol) acc[a] = cfma(F[nn + j * nstr + q], xq, acc[a]);
-    }
-  }
+  lds_chain(acc, F + nn, 1, nstr, ncol, xs + r, R, nstr, p0, P, [](int, int) { return true; });
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) {
     const int j = p0 + P * a;
@@ -543,15 +567,7 @@ __device__ void wave_backward(const SpArg& A, int4 d0, int4 d1, int lane, int R,
   // x_i = (L_ss^-T z)_i = sum over j >= i of (L_ss^-1)_ji z_j
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) acc[a] = zero;
-#pragma unroll 2
-  for (int j = 0; j < ncol; ++j) {
-    const double2 zj = z[j * R + r];
-#pragma unroll
-    for (int a = 0; a < ROWS; ++a) {
-      const int i = p0 + P * a;
-      if (i <= j) acc[a] = cfma(F[i * ncol + j], zj, acc[a]);
-    }
-  }
+  lds_chain(acc, F, 1, ncol, ncol, z + r, R, ncol, p0, P, [](int j, int i) { return i <= j; });
 #pragma unroll
   for (int a = 0; a < ROWS; ++a) {
     const int i = p0 + P * a;
@@ -569,42 +585,75 @@ constexpr int kSpBottomWaves = 8;
 constexpr int kSpBottomMinWaves = 3;
 constexpr int kSpBottomTarget = 512;
 __host__ __device__ inline int sp_slice(int R, int vec, int fac, int idx) { return vec * R + fac / 2 + idx / 4; }
-template <int ROWS>
+template <int ROWS, bool backward>
 __global__ void __launch_bounds__(64 * kSpBottomWaves)
-    k_sp_bottom(const SpArgs args, int backward, int R, int vec, int fac, int idx) {
+    k_sp_bottom(const SpArgs args, int R, int vec, int fac, int idx) {
   const SpArg& A = args.a[blockIdx.z];
   const int b = blockIdx.x, r0 = blockIdx.y * R;
   if (b >= A.nsub || r0 >= A.nrhs) return;
   extern __shared__ double2 lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), W = blockDim.x >> 6;
   const int slice = sp_slice(R, vec, fac, idx);
   double2* mine = lds + (long)wave * slice;
   double* F = reinterpret_cast<double*>(mine + vec * R);
   int* S = reinterpret_cast<int*>(F + fac);
   const int l0 = A.sub_ptr[b], nl = A.sub_ptr[b + 1] - l0 - 1;
-  for (int q = 0; q < nl; ++q) {
-    const int l = backward ? nl - 1 - q : q;
-    // the wave's supernodes of this height, each one's descriptor record
-    // loaded while the previous supernode is solved
-    const int kend = A.sub_lvl[l0 + l + 1];
-    int k = A.sub_lvl[l0 + l] + wave;
-    int4 d0 = make_int4(0, 0, 0, 0), d1 = d0;
-    if (k < kend) {
-      d0 = A.sub_desc[2 * k];
-      d1 = A.sub_desc[2 * k + 1];
+  const int* lvl = A.sub_lvl + l0;
+  // the wave's supernodes in order: the q-th height's, W apart
+  struct Cursor {
+    int q, k;
+  };
+  auto settle = [&](Cursor c) {  // c.k beyond its height: the next height that has one for this wave
+    while (c.q < nl && c.k >= lvl[(backward ? nl - 1 - c.q : c.q) + 1]) {
+      ++c.q;
+      if (c.q < nl) c.k = lvl[backward ? nl - 1 - c.q : c.q] + wave;
     }
-    for (; k < kend; k += W) {
-      int4 n0 = make_int4(0, 0, 0, 0), n1 = n0;
-      if (k + W < kend) {
-        n0 = A.sub_desc[2 * (k + W)];
-        n1 = A.sub_desc[2 * (k + W) + 1];
-      }
-      if (backward)
-        wave_backward<ROWS>(A, d0, d1, lane, R, r0, mine, F, S);
+    return c;
+  };
+  auto after = [&](Cursor c) {
+    c.k += W;
+    return settle(c);
+  };
+  int4 d0 = make_int4(0, 0, 0, 0), d1 = d0, n0 = d0, n1 = d0;
+  SpStage<ROWS> st;
+  Cursor cur = settle({0, nl > 0 ? lvl[backward ? nl - 1 : 0] + wave : 0});
+  if (cur.q < nl) {
+    d0 = A.sub_desc[2 * cur.k];
+    d1 = A.sub_desc[2 * cur.k + 1];
+    stage_load<ROWS, backward>(st, A, d0, d1, lane, R, r0);
+  }
+  Cursor nxt = cur.q < nl ? after(cur) : cur;
+  if (nxt.q < nl) {
+    n0 = A.sub_desc[2 * nxt.k];
+    n1 = A.sub_desc[2 * nxt.k + 1];
+  }
+  double2 mu = make_double2(0.0, 0.0);
+  const int rg = r0 + (lane & (R - 1));
+  if (!backward && A.grounded && rg < A.nrhs) mu = A.mean(0)[rg];
+  for (int q = 0; q < nl; ++q) {
+    while (cur.q == q) {
+      // the next supernode's stage, and the descriptor of the one after it
+      Cursor third = nxt;
+      int4 t0 = n0, t1 = n1;
+      auto next = [&] {
+        if (nxt.q >= nl) return;
+        stage_load<ROWS, backward>(st, A, n0, n1, lane, R, r0);
+        third = after(nxt);
+        if (third.q < nl) {
+          t0 = A.sub_desc[2 * third.k];
+          t1 = A.sub_desc[2 * third.k + 1];
+        }
+      };
+      if constexpr (backward)
+        wave_backward<ROWS>(A, st, d0, lane, R, r0, mine, F, S, next);
       else
-        wave_forward<ROWS>(A, d0, d1, lane, R, r0, mine, F, S, l == 0);
+        wave_forward<ROWS>(A, st, d0, mu, lane, R, r0, mine, F, S, q == 0, next);
+      cur = nxt;
       d0 = n0;
       d1 = n1;
+      nxt = third;
+      n0 = t0;
+      n1 = t1;
     }
     __syncthreads();
   }
@@ -738,21 +787,20 @@ rfcmp_status spsolve_jobs(const SpSolveJob* jobs, int njobs, int nrhs, hipStream
   hipLaunchKernelGGL(k_sp_input, tiles, dim3(kSpThreads), 0, s, args);
   if (grounded) hipLaunchKernelGGL(k_sp_mean, dim3(nrt, 1, nj), dim3(kSpThreads), 0, s, args, 0);
   const dim3 bgrid((unsigned)nsub, (unsigned)((nrhs + Rb - 1) / Rb), nj);
-  auto bottom = [&](int bwd) -> rfcmp_status {
-    const size_t lds = (size_t)(W * slice) * sizeof(double2);
-    switch (rows) {
-      case 1: hipLaunchKernelGGL(k_sp_bottom<1>, bgrid, dim3(64 * W), lds, s, args, bwd, Rb, blds, bfac, bidx); break;
-      case 2: hipLaunchKernelGGL(k_sp_bottom<2>, bgrid, dim3(64 * W), lds, s, args, bwd, Rb, blds, bfac, bidx); break;
-      case 4: hipLaunchKernelGGL(k_sp_bottom<4>, bgrid, dim3(64 * W), lds, s, args, bwd, Rb, blds, bfac, bidx); break;
-      case 8: hipLaunchKernelGGL(k_sp_bottom<8>, bgrid, dim3(64 * W), lds, s, args, bwd, Rb, blds, bfac, bidx); break;
-      default:
-        set_error("spsolve: %d rows per lane", rows);
-        return RFCMP_E_STATE;
+  auto bottom = [&](auto bwd) -> rfcmp_status {
+    constexpr bool B = decltype(bwd)::value;
+    const auto kernel = rows == 1 ? k_sp_bottom<1, B> : rows == 2 ? k_sp_bottom<2, B> : rows == 4 ? k_sp_bottom<4, B>
+                                                                                              : k_sp_bottom<8, B>;
+    if (rows > 8) {
+      set_error("spsolve: %d rows per lane", rows);
+      return RFCMP_E_STATE;
     }
+    hipLaunchKernelGGL(kernel, bgrid, dim3(64 * W), (size_t)(W * slice) * sizeof(double2), s, args, Rb, blds, bfac,
+                       bidx);
     return RFCMP_OK;
   };
   if (nsub > 0)
-    RF_TRY(bottom(0));
+    RF_TRY(bottom(std::false_type()));
   auto top = [&](int l, int bwd) {
     hipLaunchKernelGGL(k_sp_top, dim3((unsigned)nodes[l], (unsigned)((nrhs + Rt[l] - 1) / Rt[l]), nj), dim3(kSpThreads),
                        (size_t)need[l] * Rt[l] * sizeof(double2), s, args, l, bwd, Rt[l]);
@@ -766,7 +814,7 @@ rfcmp_status spsolve_jobs(const SpSolveJob* jobs, int njobs, int nrhs, hipStream
   if (fused) top(ntop - 1, 2);
   for (int l = ntop - 1 - fused; l >= 0; --l) top(l, 1);
   if (nsub > 0)
-    RF_TRY(bottom(1));
+    RF_TRY(bottom(std::true_type()));
   if (grounded) {
     hipLaunchKernelGGL(k_sp_colsum, tiles, dim3(kSpThreads), 0, s, args);
     hipLaunchKernelGGL(k_sp_mean, dim3(nrt, 1, nj), dim3(kSpThreads), 0, s, args, 1);
