@@ -90,11 +90,11 @@ __global__ __launch_bounds__(256) void k_ff_current(int C, int N, int nr, int ld
                                                     RuleArgs rule, const double2* __restrict__ j,
                                                     const double2* __restrict__ js, double* __restrict__ x,
                                                     double* __restrict__ J, double* __restrict__ Js) {
-  const long t = (long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (long)C * kQ * nr) return;
-  const int r = (int)(t % nr);
-  const long p = t / nr;
-  const int c = (int)(p / kQ), q = (int)(p % kQ);
+  const unsigned t = blockIdx.x * 256u + threadIdx.x;  // 7 C nr < 2^27 (1 GB of point currents)
+  if (t >= (unsigned)C * kQ * (unsigned)nr) return;
+  const int r = (int)(t % (unsigned)nr), pt = (int)(t / (unsigned)nr);
+  const long p = pt;
+  const int c = pt / kQ, q = pt % kQ;
   double P[9];
   for (int k = 0; k < 9; ++k) P[k] = vtx[(long)c * 9 + k];
   double2 jc[3], jsc[3];
@@ -290,15 +290,29 @@ rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrh
   // would take more than 1 GB
   const int64_t fit = std::max<int64_t>(1, (int64_t)(1 << 27) / (P * (js ? 2 : 1)) / 16 * 16 / 6);
   const int per = (int)std::min<int64_t>({nrhs, 4096, fit});
-  // column groups per workgroup: the phases (about five groups' worth of
-  // products) are formed once per workgroup
+  // column groups per workgroup (w): the phases, about five groups' worth of
+  // products, are formed once per workgroup, so wide ones do the least work;
+  // but a small body gives few of them (a slice holds 32 (w + 1) points at
+  // least), each as long as its slice, at about half the rate of a full chip.
+  // The w whose larger bound is least: at 972 cells with 10 directions and 37
+  // currents w = 2, 58 us a call (66 with the w = 8 of the least work), at 20480
+  // cells with 100 directions and 20 currents w = 8 by both bounds, 259 us.
   const int need = (6 * per + 15) / 16;
-  int w = 1;
-  for (int c = 2; c <= 8; c *= 2)
-    if ((need + c - 1) / c * (5 + c) <= (need + w - 1) / w * (5 + w)) w = c;
-  const int nz = (need + w - 1) / w, ng = nz * w;
   const int dmax = std::min(ndir, kFfDirChunk), tiles = (dmax + kFfDirs - 1) / kFfDirs;
-  const int64_t slices = std::max<int64_t>(1, std::min<int64_t>(256 * ff_waves(w) / (tiles * nz), P / (32 * (w + 1))));
+  int w = 1;
+  int64_t slices = 1;
+  double least = 0.0;
+  for (int c = 1; c <= 8; c *= 2) {
+    const int64_t groups = (int64_t)tiles * ((need + c - 1) / c);
+    const int64_t sl = std::max<int64_t>(1, std::min<int64_t>(256 * ff_waves(c) / groups, P / (32 * (c + 1))));
+    const double cost = (5.0 + c) * (double)P * std::max(groups / 256.0, 2.0 / (double)sl);
+    if (c == 1 || cost <= least) {
+      least = cost;
+      w = c;
+      slices = sl;
+    }
+  }
+  const int nz = (need + w - 1) / w, ng = nz * w;
   const int ps = (int)(((P + slices - 1) / slices + 15) / 16 * 16);
   const int ns = (int)((P + ps - 1) / ps);
   const size_t nj = (size_t)P * 16 * ng, npart = (size_t)ns * tiles * 2 * ng * 256;
