@@ -204,9 +204,9 @@ typedef struct rfcmp_op_s* rfcmp_op;
  * 7x7-point rule in FP32; near pairs (see rfcmp_mesh_near_pairs) extract the
  * 1/R singularity in closed form in FP64.  T_A is formed from the cell pairs
  * of pairs of large edge tiles and stored whole (both triangles, exactly
- * symmetric); the assembly's scratch (at most 192 MB, or one tile pair's blocks
- * where those are larger, and complex64 near-pair blocks of 72 bytes per near
- * pair) does not grow with the mesh.  On the first call
+ * symmetric).  The assembly's scratch holds at most 192 MB (or one tile pair's
+ * blocks where those are larger); beside it stand complex64 blocks of 72 bytes
+ * per near pair, about 18 pairs per cell.  On the first call
  * for a mesh the projectors (sparse FP64 Cholesky factors of
  * Sigma^T Sigma, G_ll and, for outer_star = 1, G_tp, or their dense FP64
  * inverses: see rfcmp_options.projector) are set up on the device and
