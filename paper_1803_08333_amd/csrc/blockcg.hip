@@ -1,12 +1,17 @@
 // Tall-skinny complex products of the block CG (see blockcg.h).
 //
 // Gram: a fixed grid of workgroups, each summing its rows in chunks of 32
-// (both blocks staged in LDS, rows fastest, so a wave reads its X entry as a
-// broadcast and neighbouring lanes neighbouring Y entries), thread t owning
-// the outputs (i, j) = (t / 64 + 4 q, t % 64); the partials of the
-// workgroups are added in a fixed order by a second kernel.
+// (both blocks staged in LDS, their rows 16 bytes apart in the banks, so that
+// the stores, rows fastest, meet in none), thread t owning the U x U outputs
+// (t / 16 + 16 p, t % 16 + 16 q), U the least that covers the columns; the
+// partials of the workgroups are added in a fixed order by a second kernel.
+// Bound: LDS, two operand reads per U outputs (64 columns, N = 30720: 72 us,
+// 78 with 16 reads for 16 outputs of one column and unpadded rows); with few
+// columns latency (4 columns, N = 2000: 2-5 us, 6-10 with all 64 formed).
 // Update: one thread per row and group of 8 output columns, the small
 // matrix in LDS.
+#include <algorithm>
+
 #include "blockcg.h"
 
 namespace rfcmp {
@@ -15,42 +20,55 @@ namespace {
 constexpr int kGramRows = 32;
 constexpr int kGramGroups = 240;  // workgroups of the first pass (fixed: the sum order does not depend on N)
 
+template <int U>
 __global__ __launch_bounds__(256) void k_gram_part(const double2* __restrict__ X, int a, const double2* __restrict__ Y,
                                                    int b, long N, double2* __restrict__ part) {
-  __shared__ double2 sX[kGramRows][kBlockMax];
-  __shared__ double2 sY[kGramRows][kBlockMax];
-  const int tid = threadIdx.x;
-  const int j = tid % 64;
-  double cr[16], ci[16];
+  constexpr int W = 16 * U;
+  __shared__ double2 sX[kGramRows][W + 1];
+  __shared__ double2 sY[kGramRows][W + 1];
+  const int tid = threadIdx.x, ti = tid / 16, tj = tid % 16;
+  double cr[U][U], ci[U][U];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) cr[q] = ci[q] = 0.0;
+  for (int p = 0; p < U; ++p)
+#pragma unroll
+    for (int q = 0; q < U; ++q) cr[p][q] = ci[p][q] = 0.0;
   const long per = (N + gridDim.x - 1) / gridDim.x;
   const long n0 = (long)blockIdx.x * per, n1 = min(N, n0 + per);
   for (long c0 = n0; c0 < n1; c0 += kGramRows) {
     const int nr = (int)min((long)kGramRows, n1 - c0);
-    for (int e = tid; e < kGramRows * kBlockMax; e += 256) {
+#pragma unroll
+    for (int e = tid; e < kGramRows * W; e += 256) {
       const int col = e / kGramRows, rr = e % kGramRows;
       sX[rr][col] = (col < a && rr < nr) ? X[(long)col * N + c0 + rr] : make_double2(0.0, 0.0);
       sY[rr][col] = (col < b && rr < nr) ? Y[(long)col * N + c0 + rr] : make_double2(0.0, 0.0);
     }
     __syncthreads();
     for (int rr = 0; rr < nr; ++rr) {
-      const double2 y = sY[rr][j];
+      double2 x[U], y[U];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const double2 x = sX[rr][tid / 64 + 4 * q];
-        cr[q] += x.x * y.x + x.y * y.y;
-        ci[q] += x.x * y.y - x.y * y.x;
+      for (int p = 0; p < U; ++p) {
+        x[p] = sX[rr][ti + 16 * p];
+        y[p] = sY[rr][tj + 16 * p];
       }
+#pragma unroll
+      for (int p = 0; p < U; ++p)
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+          // the product that is rounded is named, so that every U rounds alike
+          cr[p][q] += fma(x[p].x, y[q].x, x[p].y * y[q].y);
+          ci[p][q] += fma(x[p].x, y[q].y, -(x[p].y * y[q].x));
+        }
     }
     __syncthreads();
   }
   double2* out = part + (long)blockIdx.x * kBlockMax * kBlockMax;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int i = tid / 64 + 4 * q;
-    out[i * kBlockMax + j] = make_double2(cr[q], ci[q]);
-  }
+  for (int p = 0; p < U; ++p)
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int i = ti + 16 * p, j = tj + 16 * q;
+      if (i < a && j < b) out[i * kBlockMax + j] = make_double2(cr[p][q], ci[p][q]);
+    }
 }
 
 // One wave per output: lane l adds the partials of workgroups l, l + 64, ...
@@ -129,7 +147,9 @@ rfcmp_status gram_c128(const double2* X, int a, const double2* Y, int b, int64_t
   }
   double2* part = static_cast<double2*>(scratch);
   ProfScope prof("block_gram", s);
-  hipLaunchKernelGGL(k_gram_part, dim3(kGramGroups), dim3(256), 0, s, X, a, Y, b, (long)N, part);
+  const int cols = std::max(a, b);
+  const auto kernel = cols <= 16 ? k_gram_part<1> : cols <= 32 ? k_gram_part<2> : k_gram_part<4>;
+  hipLaunchKernelGGL(kernel, dim3(kGramGroups), dim3(256), 0, s, X, a, Y, b, (long)N, part);
   hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)((a * b + 3) / 4)), dim3(256), 0, s, a, b, kGramGroups, part, C);
   RF_HIP(hipGetLastError());
   return RFCMP_OK;
