@@ -180,10 +180,10 @@ TRAFFIC = {
     "icosphere5_64rhs": {
         "gemm_ta": {"source": "paper_1803_08333_amd/csrc/gemm.hip",
                     "sha256": "3a9a7ba3393dd629b05455a8cc041999b61ce68e136862d80d6a7ab277421e29",
-                    "kib": (3757129.2, 30720.0)},
+                    "kib": (3757058.1, 30720.0)},
         "zgemm_ta_nr32": {"source": "paper_1803_08333_amd/csrc/zgemm.hip",
-                          "sha256": "6c2552a624e26ee57abf050493d1670743d56309a031422a97aaa2522169ef24",
-                          "kib": (3979426.9, 122880.0)},
+                          "sha256": "b5f856e59a01fc02f110ca81f0a7fd3222a02a45e215f68d6185ebfe4d609512",
+                          "kib": (3822829.9, 137082.6)},
     },
 }
 
