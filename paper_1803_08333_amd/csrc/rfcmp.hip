@@ -140,6 +140,20 @@ rfcmp_status ensure_work(rfcmp_op op, int R) {
   return ensure_sp_scratch(op);
 }
 
+// Scratch of the symmetric streaming products, for the launches this operator
+// runs (they never overlap): T_A with V where they are dense, L^+ with
+// G_ll^-1 or G_tp^-1 where the projectors are.  It grows as N^2 (level 7: 188
+// GB), so a compressed operator with sparse projectors, which runs neither,
+// has none.
+rfcmp_status alloc_symv_scratch(rfcmp_op op) {
+  const MeshHost& h = op->mesh->h;
+  const size_t blocks = op->hm ? 0 : symv_scratch_bytes(h.N, 8) + symv_scratch_bytes(h.C, 8);
+  const size_t inverses = op->opt.projector == kProjSparse
+                              ? 0
+                              : symv_scratch_bytes(h.C, 8) + symv_scratch_bytes(std::max(h.C, h.V), 8);
+  return op->symv_scratch.alloc(std::max(blocks, inverses));
+}
+
 // ------------------------------------------------------------------ dense products
 // The five dense matrices of the operator.  In complex64/FP64 each product is
 // a symmetric streaming pass (<= 4 right-hand sides per pass) whose input is
@@ -1519,7 +1533,7 @@ rfcmp_status rfcmp_op_create_many(rfcmp_mesh m, const double* k, int32_t nk, con
   }
   RF_TRY(ensure_mesh_device(m, o.outer_star == 1, o.projector == kProjDense, s));
   m->device = dev;
-  const int64_t N = m->h.N, C = m->h.C, V = m->h.V;
+  const int64_t N = m->h.N, C = m->h.C;
   std::vector<std::unique_ptr<rfcmp_op_s>> ops(nk);
   DevBuf asm_scratch;  // given back when every assembly is done
   // Every operator's blocks first: their assembly runs beside the projector
@@ -1541,7 +1555,7 @@ rfcmp_status rfcmp_op_create_many(rfcmp_mesh m, const double* k, int32_t nk, con
       RF_TRY(op->Vb.alloc(sizeof(float2) * C * op->ldV));
     }
     RF_TRY(ensure_work(op.get(), 4));
-    RF_TRY(op->symv_scratch.alloc(symv_scratch_bytes(N, 8) + symv_scratch_bytes(C, 8) + symv_scratch_bytes(V, 8)));
+    RF_TRY(alloc_symv_scratch(op.get()));
     RF_TRY(assemble_blocks(op.get(), asm_scratch, s));
   }
   for (int32_t i = 0; i < nk; ++i) RF_TRY(ready_projectors(ops[i].get(), s));
