@@ -205,8 +205,11 @@ typedef struct rfcmp_op_s* rfcmp_op;
  * 1/R singularity in closed form in FP64.  T_A is formed from the cell pairs
  * of pairs of large edge tiles and stored whole (both triangles, exactly
  * symmetric).  The assembly's scratch holds at most 192 MB (or one tile pair's
- * blocks where those are larger); beside it stand complex64 blocks of 72 bytes
- * per near pair, about 18 pairs per cell.  On the first call
+ * blocks where those are larger: 0.7 GB for the level-5 sphere's cells in
+ * random order), in the operator's product scratch where that is large enough;
+ * where there is no memory for it, smaller tiles in at most 12 MB (16 MB in
+ * random order) give the same bits.  Beside it stand complex64 blocks of 72
+ * bytes per near pair, about 18 pairs per cell.  On the first call
  * for a mesh the projectors (sparse FP64 Cholesky factors of
  * Sigma^T Sigma, G_ll and, for outer_star = 1, G_tp, or their dense FP64
  * inverses: see rfcmp_options.projector) are set up on the device and

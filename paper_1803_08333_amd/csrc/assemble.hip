@@ -88,7 +88,8 @@ struct PairArgs {
 };
 
 constexpr int64_t kAsmScratch = 3 << 23;  // complex64 entries of a batch's blocks (192 MB)
-constexpr int64_t kAsmBatch = 4096;                // tile pairs of a batch
+constexpr int64_t kAsmBatch = 4096;       // tile pairs of a batch
+constexpr int kAsmMinShift = 2;           // the smallest tiles, for want of memory: 256 edges
 
 __global__ __launch_bounds__(256) void k_cell_pairs(const PairArgs g, float2* __restrict__ B, float2* __restrict__ Vm,
                                                     long ldV) {
@@ -633,6 +634,32 @@ RuleArgs rule_args() {
   return a;
 }
 
+// The mesh's edge tiles for the dense assembly.
+static rfcmp_status asm_upload(rfcmp_mesh m, int shift, int64_t cap, hipStream_t s) {
+  MeshDev& d = m->d;
+  AsmTiles at;
+  asm_tiles(m->h, shift, cap, at);
+  d.asm_hshift = -1;
+  auto up = [&](DevBuf& b, const void* src, size_t bytes) -> rfcmp_status {
+    RF_TRY(b.alloc(bytes));
+    RF_HIP(hipMemcpyAsync(b.p, src, bytes, hipMemcpyHostToDevice, s));
+    return RFCMP_OK;
+  };
+  RF_TRY(up(d.st_ptr, at.ptr.data(), sizeof(int) * at.ptr.size()));
+  RF_TRY(up(d.st_cell, at.cell.data(), sizeof(int) * at.cell.size()));
+  RF_TRY(up(d.st_span, at.span.data(), sizeof(int) * at.span.size()));
+  RF_TRY(up(d.st_pos, at.pos.data(), sizeof(int) * at.pos.size()));
+  RF_TRY(up(d.asm_pair, at.pair.data(), sizeof(int) * at.pair.size()));
+  RF_TRY(up(d.asm_off, at.off.data(), sizeof(long) * at.off.size()));
+  RF_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
+  d.asm_npair = (int64_t)at.off.size();
+  d.asm_batch = at.batch;
+  d.asm_scratch = at.scratch;
+  d.asm_cells_max = at.cmax;
+  d.asm_hshift = shift;
+  return RFCMP_OK;
+}
+
 rfcmp_status mesh_upload(rfcmp_mesh m, hipStream_t s) {
   const MeshHost& h = m->h;
   MeshDev& d = m->d;
@@ -679,23 +706,45 @@ rfcmp_status mesh_upload(rfcmp_mesh m, hipStream_t s) {
   RF_TRY(up(d.ve_idx, h.vtx_edge_idx.data(), sizeof(int) * 2 * N));
   std::vector<float> vs(h.vtx_edge_sgn.begin(), h.vtx_edge_sgn.end());
   RF_TRY(up(d.ve_sgn, vs.data(), sizeof(float) * 2 * N));
-  AsmTiles at;
-  asm_tiles(h, at);
   std::vector<int> home(C);
   for (int64_t c = 0; c < C; ++c) home[c] = int(h.cell_edge[3 * c] / kEdgeTile);
-  d.asm_npair = (int64_t)at.off.size();
-  d.asm_batch = at.batch;
-  d.asm_scratch = at.scratch;
-  d.asm_cells_max = at.cmax;
-  RF_TRY(up(d.st_ptr, at.ptr.data(), sizeof(int) * at.ptr.size()));
-  RF_TRY(up(d.st_cell, at.cell.data(), sizeof(int) * at.cell.size()));
-  RF_TRY(up(d.st_span, at.span.data(), sizeof(int) * at.span.size()));
-  RF_TRY(up(d.st_pos, at.pos.data(), sizeof(int) * at.pos.size()));
-  RF_TRY(up(d.asm_pair, at.pair.data(), sizeof(int) * at.pair.size()));
-  RF_TRY(up(d.asm_off, at.off.data(), sizeof(long) * at.off.size()));
   RF_TRY(up(d.cell_home, home.data(), sizeof(int) * C));
   RF_HIP(hipStreamSynchronize(s));  // host staging vectors die here
-  return RFCMP_OK;
+  return asm_upload(m, asm_shift(h.N), kAsmScratch, s);
+}
+
+// Where the blocks of a batch go: into the operator's slots of the symmetric
+// products, which nothing uses yet, where those are large enough (from about
+// 16 700 edges on, cells in order), else into `scratch`.  Where there is no
+// memory for that, the mesh takes tiles of half the edges, down to 256 (a pair
+// of them takes 3.5 MB, for cells in random order 16), in batches that fit the
+// slots or 12 MB: the same bits, an operator at level 4 in 1.74 ms instead of
+// 1.34.
+static rfcmp_status asm_room(rfcmp_op op, DevBuf& scratch, hipStream_t s, float2** B) {
+  rfcmp_mesh m = op->mesh;
+  MeshDev& d = m->d;
+  for (;;) {
+    if (d.asm_hshift < 0) RF_TRY(asm_upload(m, asm_shift(m->h.N), kAsmScratch, s));
+    if (d.near_host.hshift != d.asm_hshift) {
+      RF_HIP(hipStreamSynchronize(s));  // the map may still be on its way to the device
+      d.near_host.hshift = -1;
+      near_tiles(m->h, d.near_host.pairs, d.asm_hshift, d.near_host.tile_near);
+      RF_TRY(d.tile_near.alloc(d.near_host.tile_near.size()));
+      RF_HIP(hipMemcpyAsync(d.tile_near.p, d.near_host.tile_near.data(), d.near_host.tile_near.size(),
+                            hipMemcpyHostToDevice, s));
+      d.near_host.hshift = d.asm_hshift;
+    }
+    const size_t need = sizeof(float2) * (size_t)d.asm_scratch;
+    if (op->symv_scratch.bytes >= need) {
+      *B = op->symv_scratch.as<float2>();
+      return RFCMP_OK;
+    }
+    const rfcmp_status st = scratch.bytes >= need ? RFCMP_OK : scratch.alloc(need);
+    *B = scratch.as<float2>();
+    if (st != RFCMP_E_OOM || d.asm_hshift == kAsmMinShift) return st;
+    const int64_t cap = std::max<int64_t>(3 << 19, (int64_t)(op->symv_scratch.bytes / sizeof(float2)));
+    RF_TRY(asm_upload(m, d.asm_hshift - 1, cap, s));
+  }
 }
 
 rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
@@ -769,9 +818,8 @@ rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
     hm->dense_entries[1] = H.vd_total;
     return hm_aca(op, s);
   }
-  if (d.asm_npair == 0) return RFCMP_OK;
-  const size_t need = sizeof(float2) * (size_t)d.asm_scratch;
-  if (scratch.bytes < need) RF_TRY(scratch.alloc(need));
+  float2* B = nullptr;
+  RF_TRY(asm_room(op, scratch, s, &B));
   ProfScope prof("assemble_ta", s);
   PairArgs g;
   g.st_ptr = d.st_ptr.as<int>();
@@ -793,7 +841,7 @@ rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
   g.st_span = d.st_span.as<int>();
   g.st_pos = d.st_pos.as<int2>();
   g.N = (int)N;
-  g.hshift = asm_shift(N);
+  g.hshift = d.asm_hshift;
   const unsigned cmax = (unsigned)d.asm_cells_max, ncol = (cmax + 63) / 64;
   for (size_t q = 0; q + 1 < d.asm_batch.size(); ++q) {
     const unsigned np = (unsigned)(d.asm_batch[q + 1] - d.asm_batch[q]);
@@ -802,8 +850,8 @@ rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
     // work is the launch's tail: level 5 17.4 ms with 2, 18.1 with 4)
     g.rows = (long)ncol * cmax * np >= 16384 ? 2 : 1;
     hipLaunchKernelGGL(k_cell_pairs, dim3(ncol, (cmax + 4 * g.rows - 1) / (4 * g.rows), np), dim3(256), 0, s, g,
-                       scratch.as<float2>(), op->Vb.as<float2>(), (long)op->ldV);
-    hipLaunchKernelGGL(k_gather_ta, dim3(1u << (2 * g.hshift), np), dim3(256), 0, s, g, scratch.as<float2>(),
+                       B, op->Vb.as<float2>(), (long)op->ldV);
+    hipLaunchKernelGGL(k_gather_ta, dim3(1u << (2 * g.hshift), np), dim3(256), 0, s, g, B,
                        op->TA.as<float2>(), (long)op->ldA);
   }
   RF_HIP(hipGetLastError());
@@ -815,8 +863,8 @@ rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
 // 18.1 at 1024, 19.8 at 512; level 2: 0.027 ms at 512, 0.040 at 2048).
 int asm_shift(int64_t N) { return N > 6144 ? 5 : N > 1536 ? 4 : 3; }
 
-void asm_tiles(const MeshHost& h, AsmTiles& out) {
-  const int64_t N = h.N, E = (int64_t)kEdgeTile << asm_shift(N), nt = (N + E - 1) / E;
+void asm_tiles(const MeshHost& h, int shift, int64_t cap, AsmTiles& out) {
+  const int64_t N = h.N, E = (int64_t)kEdgeTile << shift, nt = (N + E - 1) / E;
   out.ptr.assign(nt + 1, 0);
   out.pos.resize(2 * N);
   std::vector<int> cells;
@@ -844,13 +892,13 @@ void asm_tiles(const MeshHost& h, AsmTiles& out) {
     out.cmax = std::max(out.cmax, (int)cells.size());
   }
   // tile pairs s <= t in batches whose blocks fit the scratch
-    int64_t used = 0;
+  int64_t used = 0;
   out.batch.assign(1, 0);
   for (int64_t t = 0; t < nt; ++t)
     for (int64_t s = 0; s <= t; ++s) {
       const int64_t need = 9 * (int64_t)(out.ptr[s + 1] - out.ptr[s]) * (out.ptr[t + 1] - out.ptr[t]);
       const int64_t p = (int64_t)out.off.size();
-      if (used > 0 && (used + need > kAsmScratch || p - out.batch.back() >= kAsmBatch)) {
+      if (used > 0 && (used + need > cap || p - out.batch.back() >= kAsmBatch)) {
         out.batch.push_back(p);
         used = 0;
       }
@@ -863,12 +911,39 @@ void asm_tiles(const MeshHost& h, AsmTiles& out) {
   if (!out.off.empty()) out.batch.push_back((int64_t)out.off.size());
 }
 
+static size_t near_tile_count(const MeshHost& h, int shift) {
+  const int64_t E = (int64_t)kEdgeTile << shift, nt = (h.N + E - 1) / E;
+  return (size_t)(nt * (nt + 1) / 2);
+}
+// Marks the pairs of edge tiles (s <= t, index t (t + 1)/2 + s) that the near
+// pairs p0 .. p1 - 1 of the list touch.
+static void mark_near_tiles(const MeshHost& h, const int32_t* pr, int64_t p0, int64_t p1, int shift,
+                            std::vector<uint8_t>& map) {
+  const int64_t E = (int64_t)kEdgeTile << shift;
+  for (int64_t p = p0; p < p1; ++p) {
+    int64_t ta[3], tb[3];
+    for (int i = 0; i < 3; ++i) {
+      ta[i] = h.cell_edge[3 * pr[2 * p] + i] / E;
+      tb[i] = h.cell_edge[3 * pr[2 * p + 1] + i] / E;
+    }
+    for (int i = 0; i < 3; ++i)
+      for (int j = 0; j < 3; ++j) {
+        const int64_t I = std::min(ta[i], tb[j]), J = std::max(ta[i], tb[j]);
+        map[(size_t)(J * (J + 1) / 2 + I)] = 1;
+      }
+  }
+}
+void near_tiles(const MeshHost& h, const std::vector<int32_t>& pairs, int shift, std::vector<uint8_t>& out) {
+  out.assign(near_tile_count(h, shift), 0);
+  mark_near_tiles(h, pairs.data(), 0, (int64_t)pairs.size() / 2, shift, out);
+}
+
 void near_data(const MeshHost& h, double factor, NearData& out) {
   near_pairs(h, factor, out.pairs);
-  const int64_t np = (int64_t)out.pairs.size() / 2, C = h.C, N = h.N;
+  const int64_t np = (int64_t)out.pairs.size() / 2, C = h.C;
   const int32_t* pr = out.pairs.data();
-  const int64_t E = (int64_t)kEdgeTile << asm_shift(N), nt = (N + E - 1) / E;
-  const size_t ntp = (size_t)(nt * (nt + 1) / 2);
+  out.hshift = asm_shift(h.N);
+  const size_t ntp = near_tile_count(h, out.hshift);
   // Contiguous chunks of the pair list on a few threads.  Pass 1 counts each
   // chunk's occurrences of every cell; pass 2 places them, chunk by chunk in
   // list order (the offsets of a chunk follow the earlier chunks' counts), so
@@ -905,18 +980,7 @@ void near_data(const MeshHost& h, double factor, NearData& out) {
     }
     std::vector<uint8_t>& m = tmap[t];
     m.assign(ntp, 0);
-    for (int64_t p = p0; p < p1; ++p) {
-      int64_t ta[3], tb[3];
-      for (int i = 0; i < 3; ++i) {
-        ta[i] = h.cell_edge[3 * pr[2 * p] + i] / E;
-        tb[i] = h.cell_edge[3 * pr[2 * p + 1] + i] / E;
-      }
-      for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-          const int64_t I = std::min(ta[i], tb[j]), J = std::max(ta[i], tb[j]);
-          m[(size_t)(J * (J + 1) / 2 + I)] = 1;
-        }
-    }
+    mark_near_tiles(h, pr, p0, p1, out.hshift, m);
   };
   auto run = [&](auto&& fn) {
     std::vector<std::thread> pool;

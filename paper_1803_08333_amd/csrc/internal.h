@@ -149,6 +149,7 @@ struct SpDevice;     // sparse Cholesky factor, device (spchol.h)
 struct NearData {
   std::vector<int32_t> pairs, ptr, other, code;
   std::vector<uint8_t> tile_near;
+  int hshift = 0;  // 64-edge tiles per tile, as a shift
 };
 
 // A sparse factor computed on a host thread.
@@ -187,6 +188,7 @@ struct MeshDev {
   std::vector<int64_t> asm_batch;
   int64_t asm_npair = 0, asm_scratch = 0;
   int asm_cells_max = 0;
+  int asm_hshift = -1;        // 64-edge tiles per tile, as a shift (-1: not uploaded)
   double near_factor = -1.0;  // factor of the cached near-pair list
   int64_t npairs = 0;
   DevBuf near;       // int [npairs][2]
@@ -281,18 +283,19 @@ namespace rfcmp {
 rfcmp_status build_mesh_host(const double* xyz, int64_t nv, const int32_t* tri, int64_t nc, MeshHost& h);
 void near_pairs(const MeshHost& h, double factor, std::vector<int32_t>& out);
 void near_data(const MeshHost& h, double factor, NearData& out);
+void near_tiles(const MeshHost& h, const std::vector<int32_t>& pairs, int shift, std::vector<uint8_t>& out);
 void build_cell_nb(MeshHost& h);
 
 // assemble.hip
 rfcmp_status mesh_upload(rfcmp_mesh m, hipStream_t s);
-// Edge tiles of the dense assembly (kEdgeTile << asm_shift(N) consecutive
-// edges): the cells of each tile (ptr/cell, ascending, at most cmax) with the
-// lowest and highest 64-edge tile, counted in the tile, of their edges in it
-// (span, lowest | highest << 16), the slot
-// 3 c + i of every edge in its c+ and c- (pos [N][2], c counted in the edge's
-// tile), the tile pairs (pair, int4) with the offsets of their blocks in the
-// scratch, in batches batch[q] .. batch[q + 1], and the scratch they need
-// (complex64 entries).
+// Edge tiles of the dense assembly (kEdgeTile << shift consecutive edges): the
+// cells of each tile (ptr/cell, ascending, at most cmax) with the lowest and
+// highest 64-edge tile, counted in the tile, of their edges in it (span,
+// lowest | highest << 16), the slot 3 c + i of every edge in its c+ and c-
+// (pos [N][2], c counted in the edge's tile), the tile pairs (pair, int4) with
+// the offsets of their blocks in the scratch, in batches batch[q] ..
+// batch[q + 1] of at most `cap` complex64 entries (or one pair), and the
+// scratch they need (entries).
 struct AsmTiles {
   std::vector<int> ptr, cell, span, pos, pair;
   std::vector<long> off;
@@ -301,9 +304,9 @@ struct AsmTiles {
   int cmax = 0;
 };
 int asm_shift(int64_t N);
-void asm_tiles(const MeshHost& h, AsmTiles& out);
-// scratch: the cell-pair blocks of a batch, grown as needed, shared by
-// assemblies queued on one stream
+void asm_tiles(const MeshHost& h, int shift, int64_t cap, AsmTiles& out);
+// scratch: the cell-pair blocks of a batch where op->symv_scratch has no room
+// for them, grown as needed, shared by assemblies queued on one stream
 rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s);
 // sv != nullptr: the split excitation e = Sigma sv + e (sv [nrhs][C], e the
 // plane wave less its static part)

@@ -37,3 +37,24 @@ def test_block_rows(name):
     assert rel(V[cells], assembly.block_rows(top, k, cells)[0]) < 2e-6
     op.close()
     m.close()
+
+
+@pytest.mark.parametrize("name", ["ico3", "torus28x13", "ico4"])
+def test_block_rows_of_shuffled_cells(name):
+    """Cells in random order: an edge's two cells lie anywhere in its tile, so
+    that pairs whose first cell has the higher index are taken in every tile."""
+    import paper_1803_08333_amd as rf
+    xyz, tri = synth.icosphere(4) if name == "ico4" else MESHES[name]()
+    tri = np.ascontiguousarray(tri[np.random.default_rng(7).permutation(len(tri))])
+    top, k = Topology(xyz, tri), 1.1
+    m = rf.Mesh(xyz, tri)
+    op = rf.Operator(m, k, scaling=1)
+    TA, V = (t.cpu().numpy() for t in op.export())
+    assert np.array_equal(TA, TA.T) and np.array_equal(V, V.T)
+    rng = np.random.default_rng(4)
+    edges = np.unique(np.concatenate([[0, 63, 64, top.N - 1], rng.integers(0, top.N, 6)]))
+    assert rel(TA[edges], assembly.ta_rows(top, k, edges)) < 2e-6
+    cells = np.unique(np.concatenate([[0, top.C - 1], rng.integers(0, top.C, 4)]))
+    assert rel(V[cells], assembly.block_rows(top, k, cells)[0]) < 2e-6
+    op.close()
+    m.close()

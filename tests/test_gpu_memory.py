@@ -1,8 +1,7 @@
 """Device memory that calls take: what an operator never uses it does not hold,
 and a call that a larger scratch only makes faster still runs without it.
 
-The allocator registered here is torch's, counted or refusing blocks above a
-size."""
+The allocator registered here is torch's, counted or refusing some."""
 import contextlib
 
 import numpy as np
@@ -14,14 +13,14 @@ pytestmark = pytest.mark.gpu
 
 
 @contextlib.contextmanager
-def _allocator(limit=None):
-    """torch's allocator, refusing blocks above `limit` bytes; yields the live blocks and the refused sizes."""
+def _allocator(refuse=lambda nbytes: False):
+    """torch's allocator, refusing what refuse(bytes) says; yields the live blocks and the refused sizes."""
     import torch
     import paper_1803_08333_amd as rf
     live, refused = {}, []
 
     def alloc(nbytes):
-        if limit is not None and nbytes > limit:
+        if refuse(nbytes):
             refused.append(nbytes)
             return None
         p = torch.cuda.caching_allocator_alloc(nbytes)
@@ -54,3 +53,46 @@ def test_compressed_operator_holds_no_dense_scratch():
         op.close()
         m.close()
         assert not live
+
+
+def _shuffled(xyz, tri, seed):
+    return xyz, np.ascontiguousarray(tri[np.random.default_rng(seed).permutation(len(tri))])
+
+
+# N = 1092 (tiles of 512 edges), 1920 (1024), 7680 (2048).  The ranges hold the scratch of the cell pairs' blocks alone,
+# which lies around the blocks of 5120^2 entries, below that of 7680^2 and above that of 1920^2 and everything else.
+ASSEMBLIES = {"torus28x13": (lambda: synth.torus(28, 13, seed=2), [(13e6, 1e9)]),
+              "ico3": (lambda: synth.icosphere(3), [(3.5e7, 1e9)]),
+              "ico4": (lambda: synth.icosphere(4), [(1e8, 2.05e8), (2.2e8, 4.6e8)])}
+
+
+@pytest.mark.parametrize("order", ["cells in order", "cells in random order"])
+@pytest.mark.parametrize("name", ["torus28x13", "ico3", "ico4"])
+def test_assembly_without_room_for_its_scratch(name, order):
+    """Where there is no memory for the batches of cell-pair blocks, the
+    assembly takes smaller tiles and batches: the same blocks bit for bit, on
+    the same mesh again, with another near factor, and once memory is back."""
+    import torch
+    import paper_1803_08333_amd as rf
+    make, ranges = ASSEMBLIES[name]
+    xyz, tri = make()
+    if order == "cells in random order":
+        xyz, tri = _shuffled(xyz, tri, 1)
+    want = {}
+    for factor in (2.0, 1.6):
+        m = rf.Mesh(xyz, tri)
+        op = rf.Operator(m, 1.1, scaling=1, near_factor=factor)
+        want[factor] = op.export()
+        op.close()
+        m.close()
+    m = rf.Mesh(xyz, tri)
+    with _allocator(lambda nbytes: any(lo < nbytes < hi for lo, hi in ranges)) as (_, refused):
+        ops = [rf.Operator(m, 1.1, scaling=1, near_factor=f) for f in (2.0, 2.0, 1.6)]
+        assert refused
+        for f, op in zip((2.0, 2.0, 1.6), ops):
+            assert all(torch.equal(a, b) for a, b in zip(op.export(), want[f]))
+    ops.append(rf.Operator(m, 1.1, scaling=1))
+    assert all(torch.equal(a, b) for a, b in zip(ops[-1].export(), want[2.0]))
+    for op in ops:
+        op.close()
+    m.close()
