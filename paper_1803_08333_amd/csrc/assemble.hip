@@ -763,6 +763,7 @@ rfcmp_status assemble_blocks(rfcmp_op op, DevBuf& scratch, hipStream_t s) {
     else
       near_data(h, op->opt.near_factor, nd);
     const int64_t np = (int64_t)nd.pairs.size() / 2;
+    d.near_factor = -1.0;  // none cached until every array below is in place
     RF_TRY(d.near.alloc(sizeof(int) * std::max<int64_t>(2 * np, 2)));
     RF_TRY(d.nearB.alloc(sizeof(float2) * 9 * std::max<int64_t>(np, 1)));
     RF_TRY(d.np_ptr.alloc(sizeof(int) * nd.ptr.size()));

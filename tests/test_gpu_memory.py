@@ -96,3 +96,36 @@ def test_assembly_without_room_for_its_scratch(name, order):
     for op in ops:
         op.close()
     m.close()
+
+
+def test_refused_near_pairs_leave_no_stale_list():
+    """Near pairs of another factor that find no memory, at any of their
+    arrays, leave the mesh without a list, not with half of the new one under
+    the former factor's name."""
+    import torch
+    import paper_1803_08333_amd as rf
+    m = rf.Mesh(*synth.icosphere(2))
+    op = rf.Operator(m, 1.1, scaling=1)
+    want = op.export()
+    op.close()
+    count, fail_at, failed = [0], [0], [0]
+
+    def refuse(nbytes):
+        count[0] += 1
+        return count[0] == fail_at[0]
+
+    with _allocator(refuse):
+        for k in range(1, 40):
+            count[0], fail_at[0] = 0, k
+            try:
+                rf.Operator(m, 1.1, scaling=1, near_factor=2.5).close()
+            except rf.RfcmpError:
+                failed[0] += 1
+            if count[0] < k:
+                break
+            fail_at[0] = 0
+            op = rf.Operator(m, 1.1, scaling=1)
+            assert all(torch.equal(a, b) for a, b in zip(op.export(), want))
+            op.close()
+        assert failed[0] >= 9  # T_A, V, the workspace and the list's six arrays
+    m.close()
