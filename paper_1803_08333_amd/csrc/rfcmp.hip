@@ -147,11 +147,16 @@ rfcmp_status ensure_work(rfcmp_op op, int R) {
 // has none.
 rfcmp_status alloc_symv_scratch(rfcmp_op op) {
   const MeshHost& h = op->mesh->h;
-  const size_t blocks = op->hm ? 0 : symv_scratch_bytes(h.N, 8) + symv_scratch_bytes(h.C, 8);
-  const size_t inverses = op->opt.projector == kProjSparse
-                              ? 0
-                              : symv_scratch_bytes(h.C, 8) + symv_scratch_bytes(std::max(h.C, h.V), 8);
-  return op->symv_scratch.alloc(std::max(blocks, inverses));
+  auto need = [&](int nr) {
+    const size_t blocks = op->hm ? 0 : symv_scratch_bytes(h.N, nr) + symv_scratch_bytes(h.C, nr);
+    const size_t inverses = op->opt.projector == kProjSparse
+                                ? 0
+                                : symv_scratch_bytes(h.C, nr) + symv_scratch_bytes(std::max(h.C, h.V), nr);
+    return std::max(blocks, inverses);
+  };
+  // without room for 8 columns a pass, 4 (half of it below n = 6900)
+  const rfcmp_status st = op->symv_scratch.alloc(need(8));
+  return st == RFCMP_E_OOM ? op->symv_scratch.alloc(need(4)) : st;
 }
 
 // ------------------------------------------------------------------ dense products

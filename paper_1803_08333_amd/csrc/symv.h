@@ -37,8 +37,9 @@ struct SymvJob {
   int nrhs = 0;          // job 1 of a pair: 1 of 2 right-hand sides, or 0 = all
 };
 
-// Bytes of scratch one job of size n needs (partial sums, up to 8
-// right-hand sides per pass); jobs launched together need the sum.
+// Bytes of scratch one job of size n takes for passes of nrhs right-hand sides
+// (partial sums, at most 8); jobs launched together take the sum.  A product
+// whose scratch holds fewer makes more passes, down to 4 right-hand sides.
 size_t symv_scratch_bytes(int64_t n, int nrhs);
 
 // y = M x for one or two jobs in one launch (same element type and

@@ -762,14 +762,21 @@ rfcmp_status symv_any(const SymvJob* jobs, int njobs, int nrhs, void* scratch, s
     blocks_big += blocks_of(jobs[q].n, kSmax);
   }
   const int S = blocks_big >= kMinBlocks256 ? kSmax : kSmin;
-  size_t need = 0;
-  for (int q = 0; q < njobs; ++q) need += part_bytes(jobs[q].n, std::min(jn[q], kMfmaNR), S);
-  if (need > scratch_bytes) {
-    set_error("symv: needs %zu bytes of scratch, %zu given", need, scratch_bytes);
+  // right-hand sides per pass: what the scratch holds, at least 4 (their
+  // sums do not depend on it)
+  auto need = [&](int per) {
+    size_t b = 0;
+    for (int q = 0; q < njobs; ++q) b += part_bytes(jobs[q].n, std::min(jn[q], per), S);
+    return b;
+  };
+  int per = kMfmaNR;
+  while (per > 4 && need(per) > scratch_bytes) --per;
+  if (need(per) > scratch_bytes) {
+    set_error("symv: needs %zu bytes of scratch, %zu given", need(per), scratch_bytes);
     return RFCMP_E_ARG;
   }
   for (int r0 = 0, nr = 0; r0 < nrhs; r0 += nr) {
-    nr = std::min(kMfmaNR, nrhs - r0);
+    nr = std::min(per, nrhs - r0);
     const bool split = jn[1] != nrhs;  // job 1: one column (nr == 2 here)
     JobsArg a{};
     a.nr = nr;

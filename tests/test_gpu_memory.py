@@ -129,3 +129,33 @@ def test_refused_near_pairs_leave_no_stale_list():
             op.close()
         assert failed[0] >= 9  # T_A, V, the workspace and the list's six arrays
     m.close()
+
+
+@pytest.mark.parametrize("name", ["cube5", "ico3", "torus60x30"])
+def test_products_without_room_for_eight_columns(name):
+    """An operator whose product slots for 8 columns are refused takes those
+    for 4: its products, plain, paired and of the inverses, make more passes
+    and have the same bits."""
+    import torch
+    import paper_1803_08333_amd as rf
+    xyz, tri = {"cube5": lambda: synth.cube(5), "ico3": lambda: synth.icosphere(3),
+                "torus60x30": lambda: synth.torus(60, 30, seed=2)}[name]()
+    m = rf.Mesh(xyz, tri)
+    slots = sum(16 * 128 * 8 * ((n + 127) // 128) ** 2 for n in (m.N, m.C))
+    asked = -(-slots // (1 << 21)) * (1 << 21) if slots >= 1 << 20 else slots  # requests of 1 MB on are rounded to 2 MB
+    ops = [rf.Operator(m, 1.1, scaling=1)]
+    with _allocator(lambda nbytes: nbytes == asked) as (_, refused):
+        ops.append(rf.Operator(m, 1.1, scaling=1))
+    assert refused
+    rng = np.random.default_rng(1)
+    for nrhs in (1, 2, 3, 4, 5, 7):
+        x = {n: torch.from_numpy(rng.normal(size=(nrhs, n)) + 1j * rng.normal(size=(nrhs, n))).cuda()
+             for n in (m.N, m.C, m.V)}
+        calls = [lambda op: op.matvec(0, x[m.N]), lambda op: op.matvec(1, x[m.C], conj=True),
+                 lambda op: op.apply(x[m.N]), lambda op: op.project(rf.PROJ_GSIGMA, x[m.N]),
+                 lambda op: op.project(rf.PROJ_GLL_INV, x[m.V])]
+        for call in calls:
+            assert torch.equal(call(ops[0]), call(ops[1]))
+    for op in ops:
+        op.close()
+    m.close()
