@@ -451,7 +451,8 @@ rfcmp_status rfcmp_batch_solve(const rfcmp_op* ops, int32_t nops, const void* co
  * (compressed blocks: dense tiles, ACA, products), "dmatvec_lp", "dmatvec_gll", "dmatvec_gtp" (dense FP64 projector
  * products), "spsolve_lp", "spsolve_gll", "spsolve_gtp" (sparse projector
  * solves), "gemm_ta", "gemm_v" (BF16x3 products), "spd_inverse" (whole FP64
- * inverse); a launch of k > 1 right-hand sides is timed as "<tag>_nr<k>"
+ * inverse), "farfield_w1" to "farfield_w8" (far-field sums, by the groups of 16
+ * columns, 6 a current, that a workgroup takes); a launch of k > 1 right-hand sides is timed as "<tag>_nr<k>"
  * (every "zgemm" launch carries its suffix).  rfcmp_profile_enable
  * clears the records (waiting for recorded events first); rfcmp_profile_read
  * waits for the events of one tag and returns their summed duration and

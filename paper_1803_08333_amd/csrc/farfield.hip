@@ -27,6 +27,7 @@
 // every point current again); C = 2352, 11 directions, 27 currents: 68 us a
 // call (84 before).
 #include <algorithm>
+#include <cmath>
 
 #include "farpair.h"
 #include "internal.h"
@@ -40,6 +41,7 @@ constexpr int kFfDirs = 16;         // directions per workgroup (an MFMA operand
 // workgroups of a launch: what the chip holds at once (registers: 4, 3 or 2
 // per compute unit), since a second round would run nearly empty
 constexpr int ff_waves(int ng) { return ng == 1 ? 4 : ng == 2 ? 3 : 2; }
+constexpr int kFfWidest = 8;        // column groups per workgroup, at most
 constexpr int kFfDirChunk = 16384;  // directions per launch (bounds the partial sums)
 
 // sin and cos of t.  Up to |t| = 1e5 (a body of 16 000 wavelengths) the
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(256) void k_ff_current(int C, int N, int nr, int ld
   }
 }
 
-// Partial sums of a slice of `ps` points (a multiple of 16) for 16 directions
+// Partial sums of a slice of `ps` points (a multiple of 32) for 16 directions
 // and NG of the ng 16-column groups:
 // part[slice][tile][cos, sin][group][direction][column].  The columns of J
 // beyond 6 nr hold anything: a column only reaches itself.
@@ -134,7 +136,7 @@ void k_ff_sum(int P, int ndir, int ps, int ng, double kk, const double* __restri
   const int ld = 16 * ng, g0 = blockIdx.z * NG;
   J += 16 * g0;
   Js += 16 * g0;
-  __shared__ double red[2 * NG * 4][64];
+  __shared__ double red[2][2 * NG * 4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col = lane & 15;
   const int d = min(blockIdx.x * kFfDirs + col, (unsigned)ndir - 1);
   const double d0 = dirs[3 * d], d1 = dirs[3 * d + 1], d2 = dirs[3 * d + 2];
@@ -159,7 +161,7 @@ void k_ff_sum(int P, int ndir, int ps, int ng, double kk, const double* __restri
     }
   };
   auto products = [&](const Operands& o, int p0) {
-    const double ph = kk * (d0 * o.x0 + d1 * o.x1 + d2 * o.x2);
+    const double ph = kk * fma(d2, o.x2, fma(d1, o.x1, d0 * o.x0));  // rounded alike in every instantiation
     double sn, cs;
     ff_sincos(ph, sn, cs);
     double lc = cs;
@@ -188,69 +190,94 @@ void k_ff_sum(int P, int ndir, int ps, int ng, double kk, const double* __restri
     load(oa, p0 + 32);
     products(ob, p0 + 16);
   }
-  // the four waves' sums, added in order; value v of lane l: direction
-  // 4 v + l / 16, column l % 16
-  for (int q = 1; q < 4; ++q) {
-    if (w == q)
+  // the four waves' sums, (0 + 1) + (2 + 3); wave 0 ends with the cosines', wave
+  // 2 with the sines'.  Value v of lane l: direction 4 v + l / 16, column l % 16
+  auto put = [&](double(*dst)[64], const dbl4(&a)[NG]) {
 #pragma unroll
-      for (int g = 0; g < NG; ++g)
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          red[g * 4 + v][lane] = ac[g][v];
-          red[(NG + g) * 4 + v][lane] = as[g][v];
-        }
-    __syncthreads();
-    if (w == 0)
+      for (int v = 0; v < 4; ++v) dst[4 * g + v][lane] = a[g][v];
+  };
+  auto add = [&](dbl4(&a)[NG], const double(*src)[64]) {
 #pragma unroll
-      for (int g = 0; g < NG; ++g)
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          ac[g][v] += red[g * 4 + v][lane];
-          as[g][v] += red[(NG + g) * 4 + v][lane];
-        }
-    __syncthreads();
+      for (int v = 0; v < 4; ++v) a[g][v] += src[4 * g + v][lane];
+  };
+  double(*mine)[64] = red[w >> 1];
+  if (w & 1) {
+    put(mine, ac);
+    put(mine + 4 * NG, as);
   }
-  if (w != 0) return;
+  __syncthreads();
+  if (!(w & 1)) {
+    add(ac, mine);
+    add(as, mine + 4 * NG);
+    put(mine, w == 0 ? as : ac);
+  }
+  __syncthreads();
+  if (w & 1) return;
   double* o = part + ((long)blockIdx.y * gridDim.x + blockIdx.x) * (2 * ng * 256) + g0 * 256;
+  auto out = [&](dbl4(&a)[NG], const double(*src)[64], double* dst) {
+    add(a, src);
 #pragma unroll
-  for (int g = 0; g < NG; ++g)
+    for (int g = 0; g < NG; ++g)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      o[g * 256 + (4 * v + (lane >> 4)) * 16 + col] = ac[g][v];
-      o[(ng + g) * 256 + (4 * v + (lane >> 4)) * 16 + col] = as[g][v];
-    }
+      for (int v = 0; v < 4; ++v) dst[g * 256 + (4 * v + (lane >> 4)) * 16 + col] = a[g][v];
+  };
+  if (w == 0)
+    out(ac, red[1], o);
+  else
+    out(as, red[0], o + ng * 256);
 }
 
 // The slices' sums in order (five interleaved sums, added in order), then
 // Re F = C_re + S_im, Im F = C_im - S_re (exp(-i t) = cos t - i sin t) and the
-// RCS.  One workgroup per 16 directions and right-hand side: threads
-// (part, cos or sin, direction, column).  F [nr][ndir_all][3], rcs
-// [nr][ndir_all] from direction dir0 on.
+// RCS.  One workgroup per 16 directions and R right-hand sides: threads (part,
+// sum), R sums (cos or sin, direction, column) each.  F [nr][ndir_all][3], rcs
+// [nr][ndir_all] from direction dir0 on.  Bound: the partial sums' bytes.  One
+// right-hand side takes 48 bytes of a 128-byte line, so with R = 1 the line is
+// fetched for each of the three it holds, by as many XCDs; eight take whole
+// lines.
 constexpr int kFfParts = 5, kFfSums = 2 * kFfDirs * 6;
-__global__ __launch_bounds__(kFfParts * kFfSums) void k_ff_finish(int ndir, int ng, int nslice, double kk,
+template <int R>
+constexpr int kFfAhead = R == 1 ? 8 : 2;  // slices in flight
+template <int R>
+__global__ __launch_bounds__(kFfParts * kFfSums) void k_ff_finish(int ndir, int nr, int ng, int nslice, double kk,
                                                                   const double* __restrict__ dirs,
                                                                   const double* __restrict__ part, long ndir_all,
                                                                   long dir0, double2* __restrict__ F,
                                                                   double* __restrict__ rcs) {
-  __shared__ double red[kFfParts][kFfSums];
-  const int t = threadIdx.x, q = t / kFfSums, e = t % kFfSums, r = blockIdx.y;
-  const int row = e / 6 % kFfDirs, b = e / (6 * kFfDirs), m = 6 * r + e % 6;  // column of the pass
+  __shared__ double red[kFfParts][kFfSums * R];
+  const int t = threadIdx.x, q = t / kFfSums, t0 = t % kFfSums, r0 = blockIdx.y * R;
   const long stride = (long)gridDim.x * (2 * ng * 256);
-  const double* src = part + (long)blockIdx.x * (2 * ng * 256) + (b * ng + m / 16) * 256 + row * 16 + m % 16;
-  double v = 0.0;
-#pragma unroll 8
-  for (int u = q; u < nslice; u += kFfParts) v += src[u * stride];
-  red[q][e] = v;
+  const double* src = part + (long)blockIdx.x * (2 * ng * 256);
+  int off[R];
+  double v[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const int e = t0 + kFfSums * k, c = min(6 * r0 + e % (6 * R), 6 * nr - 1);  // column of the pass
+    off[k] = (e / (6 * R * kFfDirs) * ng + c / 16) * 256 + e / (6 * R) % kFfDirs * 16 + c % 16;
+    v[k] = 0.0;
+  }
+#pragma unroll kFfAhead<R>
+  for (int u = q; u < nslice; u += kFfParts)
+#pragma unroll
+    for (int k = 0; k < R; ++k) v[k] += src[u * stride + off[k]];
+#pragma unroll
+  for (int k = 0; k < R; ++k) red[q][t0 + kFfSums * k] = v[k];
   __syncthreads();
   if (q == 0)
-    for (int u = 1; u < kFfParts; ++u) v += red[u][e];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      for (int u = 1; u < kFfParts; ++u) v[k] += red[u][t0 + kFfSums * k];
+      red[0][t0 + kFfSums * k] = v[k];
+    }
   __syncthreads();
-  if (q == 0) red[0][e] = v;
-  __syncthreads();
-  const int d = blockIdx.x * kFfDirs + t;
-  if (t >= kFfDirs || d >= ndir) return;
-  const double* c = &red[0][6 * t];
-  const double* sn = &red[0][6 * (kFfDirs + t)];
+  const int row = t % kFfDirs, d = blockIdx.x * kFfDirs + row, r = r0 + t / kFfDirs;
+  if (t >= kFfDirs * R || d >= ndir || r >= nr) return;
+  const double* c = &red[0][6 * (R * row + t / kFfDirs)];
+  const double* sn = c + 6 * R * kFfDirs;
   double f[6];
   for (int k = 0; k < 3; ++k) {
     f[2 * k] = c[2 * k] + sn[2 * k + 1];
@@ -280,41 +307,50 @@ void ff_launch(bool split, dim3 grid, hipStream_t s, int P, int ndir, int ps, in
     hipLaunchKernelGGL((k_ff_sum<NG, false>), grid, dim3(256), 0, s, P, ndir, ps, ng, kk, dirs, x, J, J, part);
 }
 
+// Points per slice.  It depends on the body alone, and so does the order in
+// which a current's points are summed: its far field has the same bits whichever
+// currents and directions share the call.  Long slices leave a call of few
+// directions few workgroups, short ones one of many directions much to write
+// and add up: in proportion to the root of the points both stay small (of 2.0
+// to 4.0 times the root, over bodies of 80 to 20 480 cells, 1 to 37 currents and
+// 1 to 720 directions, 2.4 was the fastest on the mean).
+int ff_slice(int64_t P) { return 32 * (int)std::ceil(2.4 * std::sqrt((double)P) / 32.0); }
+
+// Column groups per workgroup: the phases, about five groups' worth of products,
+// are formed once per workgroup, so the width that pads least does the least
+// work; but a small body gives few workgroups, which run at about two thirds of a
+// full chip's rate.  The width whose larger bound is least: at 5120 cells, 181
+// directions and 16 currents (6 groups) w = 6, 125 us a call (146 with w = 8), at
+// 972 cells with one direction and 37 currents w = 1, 52 us (55 with w = 8).
+int ff_width(int need, int tiles, int slices) {
+  int w = 1;
+  double least = 0.0;
+  for (int c = 1; c <= kFfWidest; ++c) {
+    const double cost = (5.0 + c) * std::max((double)tiles * ((need + c - 1) / c) * slices / 256.0, 1.4);
+    if (c == 1 || cost <= least) {
+      least = cost;
+      w = c;
+    }
+  }
+  return w;
+}
+
 }  // namespace
 
 rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrhs, const double* dirs, int ndir,
                        double2* F, double* rcs, hipStream_t s) {
-  rfcmp_mesh m = op->mesh;
-  const int64_t C = m->h.C, N = m->h.N, P = C * kQ;
+  rfcmp_mesh mesh = op->mesh;
+  const MeshDev& D = mesh->d;
+  const int64_t C = mesh->h.C, N = mesh->h.N, P = C * kQ;
   // right-hand sides per pass: all of them, fewer where the point currents
   // would take more than 1 GB
   const int64_t fit = std::max<int64_t>(1, (int64_t)(1 << 27) / (P * (js ? 2 : 1)) / 16 * 16 / 6);
   const int per = (int)std::min<int64_t>({nrhs, 4096, fit});
-  // column groups per workgroup (w): the phases, about five groups' worth of
-  // products, are formed once per workgroup, so wide ones do the least work;
-  // but a small body gives few of them (a slice holds 32 (w + 1) points at
-  // least), each as long as its slice, at about half the rate of a full chip.
-  // The w whose larger bound is least: at 972 cells with 10 directions and 37
-  // currents w = 2, 58 us a call (66 with the w = 8 of the least work), at 20480
-  // cells with 100 directions and 20 currents w = 8 by both bounds, 259 us.
   const int need = (6 * per + 15) / 16;
   const int dmax = std::min(ndir, kFfDirChunk), tiles = (dmax + kFfDirs - 1) / kFfDirs;
-  int w = 1;
-  int64_t slices = 1;
-  double least = 0.0;
-  for (int c = 1; c <= 8; c *= 2) {
-    const int64_t groups = (int64_t)tiles * ((need + c - 1) / c);
-    const int64_t sl = std::max<int64_t>(1, std::min<int64_t>(256 * ff_waves(c) / groups, P / (32 * (c + 1))));
-    const double cost = (5.0 + c) * (double)P * std::max(groups / 256.0, 2.0 / (double)sl);
-    if (c == 1 || cost <= least) {
-      least = cost;
-      w = c;
-      slices = sl;
-    }
-  }
+  const int ps = ff_slice(P), ns = (int)((P + ps - 1) / ps);
+  const int w = ff_width(need, tiles, ns);
   const int nz = (need + w - 1) / w, ng = nz * w;
-  const int ps = (int)(((P + slices - 1) / slices + 15) / 16 * 16);
-  const int ns = (int)((P + ps - 1) / ps);
   const size_t nj = (size_t)P * 16 * ng, npart = (size_t)ns * tiles * 2 * ng * 256;
   DevBuf buf;
   RF_TRY(buf.alloc(sizeof(double) * (3 * (size_t)ndir + 3 * (size_t)P + nj * (js ? 2 : 1) + npart)));
@@ -324,19 +360,29 @@ rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrh
   double* x = J + nj * (js ? 2 : 1);
   double* dd = x + 3 * P;
   RF_HIP(hipMemcpyAsync(dd, dirs, sizeof(double) * 3 * ndir, hipMemcpyHostToDevice, s));
-  const auto sums = w == 1 ? ff_launch<1> : w == 2 ? ff_launch<2> : w == 4 ? ff_launch<4> : ff_launch<8>;
+  using Sums = decltype(&ff_launch<1>);
+  constexpr Sums kSums[kFfWidest] = {ff_launch<1>, ff_launch<2>, ff_launch<3>, ff_launch<4>,
+                                     ff_launch<5>, ff_launch<6>, ff_launch<7>, ff_launch<8>};
+  constexpr const char* kTags[kFfWidest] = {"farfield_w1", "farfield_w2", "farfield_w3", "farfield_w4",
+                                            "farfield_w5", "farfield_w6", "farfield_w7", "farfield_w8"};
+  const Sums sums = kSums[w - 1];
   for (int r0 = 0; r0 < nrhs; r0 += per) {
     const int nr = std::min(per, nrhs - r0);
     const long tot = (long)P * nr;
     hipLaunchKernelGGL(k_ff_current, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, (int)C, (int)N, nr, 16 * ng,
-                       m->d.cell_edge.as<int>(), m->d.sgn.as<float>(), m->d.vtx.as<double>(), rule_args(),
+                       D.cell_edge.as<int>(), D.sgn.as<float>(), D.vtx.as<double>(), rule_args(),
                        j + (int64_t)r0 * N, js ? js + (int64_t)r0 * N : nullptr, x, J, Js);
     for (int q0 = 0; q0 < ndir; q0 += kFfDirChunk) {
       const int nd = std::min(kFfDirChunk, ndir - q0);
       const unsigned nt = (unsigned)((nd + kFfDirs - 1) / kFfDirs);
+      ProfScope prof(kTags[w - 1], s);
       sums(js != nullptr, dim3(nt, (unsigned)ns, (unsigned)nz), s, (int)P, nd, ps, ng, op->k, dd + 3L * q0, x, J, Js,
            part);
-      hipLaunchKernelGGL(k_ff_finish, dim3(nt, (unsigned)nr), dim3(kFfParts * kFfSums), 0, s, nd, ng, ns, op->k,
+      // eight right-hand sides a workgroup where that leaves 16 of them
+      const bool wide = nr >= 8 && (int64_t)nt * ((nr + 7) / 8) >= 16;
+      const auto finish = wide ? k_ff_finish<8> : k_ff_finish<1>;
+      hipLaunchKernelGGL(finish, dim3(nt, (unsigned)(wide ? (nr + 7) / 8 : nr)), dim3(kFfParts * kFfSums), 0, s, nd,
+                         nr, ng, ns, op->k,
                          dd + 3L * q0, part, (long)ndir, (long)q0, F + (int64_t)r0 * ndir * 3,
                          rcs ? rcs + (int64_t)r0 * ndir : nullptr);
     }
