@@ -85,18 +85,20 @@ __device__ inline void ff_sincos(double t, double& sn, double& cs) {
   cs = ((q + 1) & 2) ? -v : v;
 }
 
-// x [7 C][3] and the point currents J [7 C][ld], column 6 r + 2 k + (0: real,
-// 1: imaginary) of component k of right-hand side r; js (nullable) into Js.
-__global__ __launch_bounds__(256) void k_ff_current(int C, int N, int nr, int ld, const int* __restrict__ cell_edge,
-                                                    const float* __restrict__ sgn, const double* __restrict__ vtx,
-                                                    RuleArgs rule, const double2* __restrict__ j,
-                                                    const double2* __restrict__ js, double* __restrict__ x,
-                                                    double* __restrict__ J, double* __restrict__ Js) {
-  const unsigned t = blockIdx.x * 256u + threadIdx.x;  // 7 C nr < 2^27 (1 GB of point currents)
-  if (t >= (unsigned)C * kQ * (unsigned)nr) return;
+// Positions x [n][3] and point currents J [n][ld] of the points p0 .. p0 + n - 1
+// (7 c + q), column 6 r + 2 k + (0: real, 1: imaginary) of component k of
+// right-hand side r; js (nullable) into Js.
+__global__ __launch_bounds__(256) void k_ff_current(int p0, int n, int N, int nr, int ld,
+                                                    const int* __restrict__ cell_edge, const float* __restrict__ sgn,
+                                                    const double* __restrict__ vtx, RuleArgs rule,
+                                                    const double2* __restrict__ j, const double2* __restrict__ js,
+                                                    double* __restrict__ x, double* __restrict__ J,
+                                                    double* __restrict__ Js) {
+  const unsigned t = blockIdx.x * 256u + threadIdx.x;  // n nr < 2^26 (1 GB of point currents)
+  if (t >= (unsigned)n * (unsigned)nr) return;
   const int r = (int)(t % (unsigned)nr), pt = (int)(t / (unsigned)nr);
   const long p = pt;
-  const int c = pt / kQ, q = pt % kQ;
+  const int c = (p0 + pt) / kQ, q = (p0 + pt) % kQ;
   double P[9];
   for (int k = 0; k < 9; ++k) P[k] = vtx[(long)c * 9 + k];
   double2 jc[3], jsc[3];
@@ -335,6 +337,39 @@ int ff_width(int need, int tiles, int slices) {
   return w;
 }
 
+// One call's passes and memory: `per` right-hand sides, `dch` directions (a
+// multiple of 16) and `sch` slices at a time, in at most about `budget` bytes.
+// The order of the sums is the same in every plan.  Fewer slices at a time cost
+// nothing while the launches fill the chip, fewer right-hand sides form the
+// phases again.
+struct FfPlan {
+  int per, dch, sch, w, nz;
+  size_t nj, npart, bytes;  // doubles of the point currents and of the partial sums; all bytes
+  bool least;               // nothing left to shrink
+};
+FfPlan ff_plan(int64_t P, int ps, int ns, int nrhs, int ndir, bool split, size_t budget) {
+  FfPlan p{std::min(nrhs, 4096), (int)round_up(std::min(ndir, kFfDirChunk), kFfDirs), ns, 1, 1, 0, 0, 0, false};
+  for (;;) {
+    const int need = (6 * p.per + 15) / 16, tiles = p.dch / kFfDirs;
+    p.w = ff_width(need, tiles, p.sch);
+    p.nz = (need + p.w - 1) / p.w;
+    const size_t points = (size_t)std::min<int64_t>(P, (int64_t)p.sch * ps), ng = (size_t)p.nz * p.w;
+    p.nj = points * 16 * ng * (split ? 2 : 1);
+    p.npart = (size_t)ns * tiles * 2 * ng * 256;
+    p.bytes = sizeof(double) * (3 * (size_t)ndir + 3 * points + p.nj + p.npart);
+    p.least = p.per == 1 && p.dch == kFfDirs && p.sch == 1;
+    if (p.bytes <= budget || p.least) return p;
+    if (p.npart > p.nj && p.dch > kFfDirs)
+      p.dch = (int)round_up(p.dch / 2, kFfDirs);
+    else if (p.sch > 1 && ((int64_t)p.sch * tiles * p.nz >= 2048 || p.per == 1))
+      p.sch = (p.sch + 1) / 2;
+    else if (p.per > 1)
+      p.per = (p.per + 1) / 2;
+    else
+      p.dch = (int)round_up(p.dch / 2, kFfDirs);
+  }
+}
+
 }  // namespace
 
 rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrhs, const double* dirs, int ndir,
@@ -342,48 +377,51 @@ rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrh
   rfcmp_mesh mesh = op->mesh;
   const MeshDev& D = mesh->d;
   const int64_t C = mesh->h.C, N = mesh->h.N, P = C * kQ;
-  // right-hand sides per pass: all of them, fewer where the point currents
-  // would take more than 1 GB
-  const int64_t fit = std::max<int64_t>(1, (int64_t)(1 << 27) / (P * (js ? 2 : 1)) / 16 * 16 / 6);
-  const int per = (int)std::min<int64_t>({nrhs, 4096, fit});
-  const int need = (6 * per + 15) / 16;
-  const int dmax = std::min(ndir, kFfDirChunk), tiles = (dmax + kFfDirs - 1) / kFfDirs;
   const int ps = ff_slice(P), ns = (int)((P + ps - 1) / ps);
-  const int w = ff_width(need, tiles, ns);
-  const int nz = (need + w - 1) / w, ng = nz * w;
-  const size_t nj = (size_t)P * 16 * ng, npart = (size_t)ns * tiles * 2 * ng * 256;
   DevBuf buf;
-  RF_TRY(buf.alloc(sizeof(double) * (3 * (size_t)ndir + 3 * (size_t)P + nj * (js ? 2 : 1) + npart)));
+  FfPlan pl;
+  // 1 GB at most, a quarter of it at a time where that is refused
+  for (size_t budget = (size_t)1 << 30;; budget /= 4) {
+    pl = ff_plan(P, ps, ns, nrhs, ndir, js != nullptr, budget);
+    const rfcmp_status st = buf.alloc(pl.bytes);
+    if (st == RFCMP_OK) break;
+    if (st != RFCMP_E_OOM || pl.least) return st;
+  }
+  const int ng = pl.nz * pl.w;
   double* part = buf.as<double>();
-  double* J = part + npart;
-  double* Js = J + nj;
-  double* x = J + nj * (js ? 2 : 1);
-  double* dd = x + 3 * P;
+  double* J = part + pl.npart;
+  double* Js = J + pl.nj / 2;
+  double* x = J + pl.nj;
+  double* dd = x + 3 * std::min<int64_t>(P, (int64_t)pl.sch * ps);
   RF_HIP(hipMemcpyAsync(dd, dirs, sizeof(double) * 3 * ndir, hipMemcpyHostToDevice, s));
   using Sums = decltype(&ff_launch<1>);
   constexpr Sums kSums[kFfWidest] = {ff_launch<1>, ff_launch<2>, ff_launch<3>, ff_launch<4>,
                                      ff_launch<5>, ff_launch<6>, ff_launch<7>, ff_launch<8>};
   constexpr const char* kTags[kFfWidest] = {"farfield_w1", "farfield_w2", "farfield_w3", "farfield_w4",
                                             "farfield_w5", "farfield_w6", "farfield_w7", "farfield_w8"};
-  const Sums sums = kSums[w - 1];
-  for (int r0 = 0; r0 < nrhs; r0 += per) {
-    const int nr = std::min(per, nrhs - r0);
-    const long tot = (long)P * nr;
-    hipLaunchKernelGGL(k_ff_current, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, (int)C, (int)N, nr, 16 * ng,
-                       D.cell_edge.as<int>(), D.sgn.as<float>(), D.vtx.as<double>(), rule_args(),
-                       j + (int64_t)r0 * N, js ? js + (int64_t)r0 * N : nullptr, x, J, Js);
-    for (int q0 = 0; q0 < ndir; q0 += kFfDirChunk) {
-      const int nd = std::min(kFfDirChunk, ndir - q0);
+  const Sums sums = kSums[pl.w - 1];
+  for (int r0 = 0; r0 < nrhs; r0 += pl.per) {
+    const int nr = std::min(pl.per, nrhs - r0);
+    for (int q0 = 0; q0 < ndir; q0 += pl.dch) {
+      const int nd = std::min(pl.dch, ndir - q0);
       const unsigned nt = (unsigned)((nd + kFfDirs - 1) / kFfDirs);
-      ProfScope prof(kTags[w - 1], s);
-      sums(js != nullptr, dim3(nt, (unsigned)ns, (unsigned)nz), s, (int)P, nd, ps, ng, op->k, dd + 3L * q0, x, J, Js,
-           part);
+      for (int s0 = 0; s0 < ns; s0 += pl.sch) {
+        const int slices = std::min(pl.sch, ns - s0);
+        const int64_t p0 = (int64_t)s0 * ps, points = std::min<int64_t>(P - p0, (int64_t)slices * ps);
+        if (pl.sch < ns || q0 == 0)  // else the point currents are there
+          hipLaunchKernelGGL(k_ff_current, dim3((unsigned)((points * nr + 255) / 256)), dim3(256), 0, s, (int)p0,
+                             (int)points, (int)N, nr, 16 * ng, D.cell_edge.as<int>(), D.sgn.as<float>(),
+                             D.vtx.as<double>(), rule_args(), j + (int64_t)r0 * N,
+                             js ? js + (int64_t)r0 * N : nullptr, x, J, Js);
+        ProfScope prof(kTags[pl.w - 1], s);
+        sums(js != nullptr, dim3(nt, (unsigned)slices, (unsigned)pl.nz), s, (int)points, nd, ps, ng, op->k,
+             dd + 3L * q0, x, J, Js, part + (size_t)s0 * nt * (2 * ng * 256));
+      }
       // eight right-hand sides a workgroup where that leaves 16 of them
       const bool wide = nr >= 8 && (int64_t)nt * ((nr + 7) / 8) >= 16;
       const auto finish = wide ? k_ff_finish<8> : k_ff_finish<1>;
       hipLaunchKernelGGL(finish, dim3(nt, (unsigned)(wide ? (nr + 7) / 8 : nr)), dim3(kFfParts * kFfSums), 0, s, nd,
-                         nr, ng, ns, op->k,
-                         dd + 3L * q0, part, (long)ndir, (long)q0, F + (int64_t)r0 * ndir * 3,
+                         nr, ng, ns, op->k, dd + 3L * q0, part, (long)ndir, (long)q0, F + (int64_t)r0 * ndir * 3,
                          rcs ? rcs + (int64_t)r0 * ndir : nullptr);
     }
   }

@@ -159,3 +159,34 @@ def test_products_without_room_for_eight_columns(name):
     for op in ops:
         op.close()
     m.close()
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("nrhs,ndir", [(1, 600), (37, 1), (37, 600)])
+def test_far_field_with_little_memory(nrhs, ndir, split):
+    """A far field whose point currents and partial sums find no memory is
+    formed some currents, directions and points at a time, with the same bits;
+    only when next to nothing is left does it fail."""
+    import torch
+    import paper_1803_08333_amd as rf
+    m = rf.Mesh(*synth.cube(9))
+    op = rf.Operator(m, 0.8, scaling=1)
+    rng = np.random.default_rng(nrhs)
+    j, js = (torch.from_numpy(rng.normal(size=(nrhs, m.N)) + 1j * rng.normal(size=(nrhs, m.N))).cuda() for _ in range(2))
+    d = rng.normal(size=(ndir, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+
+    def call():
+        return op.far_field_split(j, js, d) if split else op.far_field(j, d)
+
+    F, s = call()
+    for limit in (1 << 24, 1 << 21, 1 << 18):
+        with _allocator(lambda nbytes: nbytes > limit) as (_, refused):
+            f, t = call()
+        assert torch.equal(f, F) and torch.equal(t, s)
+        assert refused or limit > 1 << 18
+    with _allocator(lambda nbytes: True):
+        with pytest.raises(rf.RfcmpError):
+            call()
+    op.close()
+    m.close()
