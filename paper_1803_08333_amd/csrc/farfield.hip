@@ -21,11 +21,11 @@
 // right-hand side (6 columns, twice, as MFMA; padded to 16 columns), 7 C ndir
 // of each.  One workgroup takes 16 directions, a slice of the points and up to
 // 8 of the column groups; its four waves take every fourth group of four
-// points.  Level 4 (C = 5120), 362 directions, 4 currents: 65 us for the sums
-// and 15 for the two small kernels around them, 98 us a call (306 before, one
+// points.  Level 4 (C = 5120), 362 directions, 4 currents: 61 us for the sums
+// and 14 for the two small kernels around them, 100 us a call (306 with one
 // workgroup per direction and right-hand side, each forming every phase and
-// every point current again); C = 2352, 11 directions, 27 currents: 68 us a
-// call (84 before).
+// every point current again).  A body of 80 to 320 cells takes 36 to 40 us, most
+// of them the call's own.
 #include <algorithm>
 #include <cmath>
 
@@ -45,11 +45,14 @@ constexpr int kFfWidest = 8;        // column groups per workgroup, at most
 constexpr int kFfDirChunk = 16384;  // directions per launch (bounds the partial sums)
 
 // sin and cos of t.  Up to |t| = 1e5 (a body of 16 000 wavelengths) the
-// nearest multiple of pi/2 is taken off with pi/2 as the sum of two doubles
-// (absolute error below 1e-21) and the rest, |r| <= pi/4, goes through the
-// Taylor series of both functions (the terms left out are below 2^-58 of
-// either); beyond, the library's.  About 35 operations where the library's
-// takes over 100.
+// nearest multiple n of pi/2 is taken off with pi/2 as the sum of two doubles
+// (Cody and Waite's reduction; n times what the two leave out is below 1e-27),
+// which leaves |r| <= pi/4 rounded once to double, by at most 2^-54.  r goes
+// through the Taylor series of both functions (the terms left out are below
+// 2^-58 of either), the cosine's as w = 1 - r^2/2 with what rounding took from w
+// added back to the rest of the series, as fdlibm does.  In all 1.2e-16 absolute,
+// 2.2e-16 relative (against 64-bit values over |t| <= 1e5).  Beyond, the
+// library's.  About 35 operations where the library's takes over 100.
 constexpr double kPio2Hi = 1.57079632679489655800e+00;
 constexpr double kPio2Lo = 6.12323399573676603587e-17;
 __device__ inline void ff_sincos(double t, double& sn, double& cs) {
@@ -85,45 +88,65 @@ __device__ inline void ff_sincos(double t, double& sn, double& cs) {
   cs = ((q + 1) & 2) ? -v : v;
 }
 
+// Up to kFfDirArgs directions ride in the arguments of the call's first kernel
+// (a copy from the caller's pageable memory takes longer than the kernel).
+constexpr int kFfDirArgs = 128;
+struct DirArgs {
+  int n = 0;
+  double d[3 * kFfDirArgs];
+};
+
+struct FfMesh {
+  int N;
+  const int* cell_edge;
+  const float* sgn;
+  const double* vtx;
+  RuleArgs rule;
+};
+// Component k of the position of quadrature point q of the cell with vertices P.
+__device__ inline double ff_position(const FfMesh& m, const double* P, int q, int k) {
+  return fma(m.rule.bary[q][2], P[6 + k], fma(m.rule.bary[q][1], P[3 + k], m.rule.bary[q][0] * P[k]));
+}
+// Component k of the current there (less its weight) of the three edges' values,
+// rounded alike wherever it is formed.
+__device__ inline double ff_current(const double* P, const double (&sg)[3], double xk, int k, double j0, double j1,
+                                    double j2) {
+  return fma(sg[2] * (xk - P[6 + k]), j2, fma(sg[1] * (xk - P[3 + k]), j1, sg[0] * (xk - P[k]) * j0));
+}
+
 // Positions x [n][3] and point currents J [n][ld] of the points p0 .. p0 + n - 1
 // (7 c + q), column 6 r + 2 k + (0: real, 1: imaginary) of component k of
 // right-hand side r; js (nullable) into Js.
-__global__ __launch_bounds__(256) void k_ff_current(int p0, int n, int N, int nr, int ld,
-                                                    const int* __restrict__ cell_edge, const float* __restrict__ sgn,
-                                                    const double* __restrict__ vtx, RuleArgs rule,
+__global__ __launch_bounds__(256) void k_ff_current(int p0, int n, int nr, int ld, const FfMesh m,
                                                     const double2* __restrict__ j, const double2* __restrict__ js,
                                                     double* __restrict__ x, double* __restrict__ J,
-                                                    double* __restrict__ Js) {
+                                                    double* __restrict__ Js, DirArgs da, double* __restrict__ dirs) {
+  if (blockIdx.x == 0)
+    for (int e = threadIdx.x; e < 3 * da.n; e += 256) dirs[e] = da.d[e];
   const unsigned t = blockIdx.x * 256u + threadIdx.x;  // n nr < 2^26 (1 GB of point currents)
   if (t >= (unsigned)n * (unsigned)nr) return;
   const int r = (int)(t % (unsigned)nr), pt = (int)(t / (unsigned)nr);
   const long p = pt;
   const int c = (p0 + pt) / kQ, q = (p0 + pt) % kQ;
-  double P[9];
-  for (int k = 0; k < 9; ++k) P[k] = vtx[(long)c * 9 + k];
+  double P[9], sg[3];
+  for (int k = 0; k < 9; ++k) P[k] = m.vtx[(long)c * 9 + k];
   double2 jc[3], jsc[3];
-  double sg[3];
   for (int i = 0; i < 3; ++i) {
-    const long m = (long)r * N + cell_edge[3 * c + i];
-    jc[i] = j[m];
-    jsc[i] = js ? js[m] : make_double2(0.0, 0.0);
-    sg[i] = 0.5 * (double)sgn[3 * c + i];
+    const long e = (long)r * m.N + m.cell_edge[3 * c + i];
+    jc[i] = j[e];
+    jsc[i] = js ? js[e] : make_double2(0.0, 0.0);
+    sg[i] = 0.5 * (double)m.sgn[3 * c + i];
   }
-  const double wq = rule.wd[q], b0 = rule.bary[q][0], b1 = rule.bary[q][1], b2 = rule.bary[q][2];
+  const double wq = m.rule.wd[q];
   for (int k = 0; k < 3; ++k) {
-    const double xk = b0 * P[k] + b1 * P[3 + k] + b2 * P[6 + k];
+    const double xk = ff_position(m, P, q, k);
     if (r == 0) x[3 * p + k] = xk;
-    double cr = 0.0, ci = 0.0, dr = 0.0, di = 0.0;
-    for (int i = 0; i < 3; ++i) {
-      const double arm = sg[i] * (xk - P[3 * i + k]);
-      cr += arm * jc[i].x;
-      ci += arm * jc[i].y;
-      dr += arm * jsc[i].x;
-      di += arm * jsc[i].y;
-    }
     const long o = p * ld + 6 * r + 2 * k;
-    *reinterpret_cast<double2*>(J + o) = make_double2(wq * cr, wq * ci);
-    if (js) *reinterpret_cast<double2*>(Js + o) = make_double2(wq * dr, wq * di);
+    *reinterpret_cast<double2*>(J + o) = make_double2(wq * ff_current(P, sg, xk, k, jc[0].x, jc[1].x, jc[2].x),
+                                                      wq * ff_current(P, sg, xk, k, jc[0].y, jc[1].y, jc[2].y));
+    if (js)
+      *reinterpret_cast<double2*>(Js + o) = make_double2(wq * ff_current(P, sg, xk, k, jsc[0].x, jsc[1].x, jsc[2].x),
+                                                         wq * ff_current(P, sg, xk, k, jsc[0].y, jsc[1].y, jsc[2].y));
   }
 }
 
@@ -313,17 +336,17 @@ void ff_launch(bool split, dim3 grid, hipStream_t s, int P, int ndir, int ps, in
 // which a current's points are summed: its far field has the same bits whichever
 // currents and directions share the call.  Long slices leave a call of few
 // directions few workgroups, short ones one of many directions much to write
-// and add up: in proportion to the root of the points both stay small (of 2.0
-// to 4.0 times the root, over bodies of 80 to 20 480 cells, 1 to 37 currents and
-// 1 to 720 directions, 2.4 was the fastest on the mean).
-int ff_slice(int64_t P) { return 32 * (int)std::ceil(2.4 * std::sqrt((double)P) / 32.0); }
+// and add up: in proportion to the root of the points both stay small (of 1.4
+// to 4.6 times the root, over bodies of 80 to 20 480 cells, 1 to 37 currents and
+// 1 to 720 directions, 2.0 to 3.6 were within 2 % on the mean, 1.4 and 4.6 slower).
+int ff_slice(int64_t P) { return 32 * (int)std::ceil(2.8 * std::sqrt((double)P) / 32.0); }
 
 // Column groups per workgroup: the phases, about five groups' worth of products,
 // are formed once per workgroup, so the width that pads least does the least
 // work; but a small body gives few workgroups, which run at about two thirds of a
 // full chip's rate.  The width whose larger bound is least: at 5120 cells, 181
-// directions and 16 currents (6 groups) w = 6, 125 us a call (146 with w = 8), at
-// 972 cells with one direction and 37 currents w = 1, 52 us (55 with w = 8).
+// directions and 16 currents (6 groups) w = 6, 132 us a call (148 with w = 8),
+// with 37 directions and 4 currents w = 2, 58 us (68 with w = 8).
 int ff_width(int need, int tiles, int slices) {
   int w = 1;
   double least = 0.0;
@@ -376,7 +399,7 @@ rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrh
                        double2* F, double* rcs, hipStream_t s) {
   rfcmp_mesh mesh = op->mesh;
   const MeshDev& D = mesh->d;
-  const int64_t C = mesh->h.C, N = mesh->h.N, P = C * kQ;
+  const int64_t N = mesh->h.N, P = mesh->h.C * kQ;
   const int ps = ff_slice(P), ns = (int)((P + ps - 1) / ps);
   DevBuf buf;
   FfPlan pl;
@@ -393,7 +416,14 @@ rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrh
   double* Js = J + pl.nj / 2;
   double* x = J + pl.nj;
   double* dd = x + 3 * std::min<int64_t>(P, (int64_t)pl.sch * ps);
-  RF_HIP(hipMemcpyAsync(dd, dirs, sizeof(double) * 3 * ndir, hipMemcpyHostToDevice, s));
+  DirArgs da;
+  if (ndir <= kFfDirArgs) {
+    da.n = ndir;
+    std::copy(dirs, dirs + 3 * ndir, da.d);
+  } else {
+    RF_HIP(hipMemcpyAsync(dd, dirs, sizeof(double) * 3 * ndir, hipMemcpyHostToDevice, s));
+  }
+  const FfMesh fm{(int)N, D.cell_edge.as<int>(), D.sgn.as<float>(), D.vtx.as<double>(), rule_args()};
   using Sums = decltype(&ff_launch<1>);
   constexpr Sums kSums[kFfWidest] = {ff_launch<1>, ff_launch<2>, ff_launch<3>, ff_launch<4>,
                                      ff_launch<5>, ff_launch<6>, ff_launch<7>, ff_launch<8>};
@@ -410,9 +440,8 @@ rfcmp_status far_field(rfcmp_op op, const double2* j, const double2* js, int nrh
         const int64_t p0 = (int64_t)s0 * ps, points = std::min<int64_t>(P - p0, (int64_t)slices * ps);
         if (pl.sch < ns || q0 == 0)  // else the point currents are there
           hipLaunchKernelGGL(k_ff_current, dim3((unsigned)((points * nr + 255) / 256)), dim3(256), 0, s, (int)p0,
-                             (int)points, (int)N, nr, 16 * ng, D.cell_edge.as<int>(), D.sgn.as<float>(),
-                             D.vtx.as<double>(), rule_args(), j + (int64_t)r0 * N,
-                             js ? js + (int64_t)r0 * N : nullptr, x, J, Js);
+                             (int)points, nr, 16 * ng, fm, j + (int64_t)r0 * N,
+                             js ? js + (int64_t)r0 * N : nullptr, x, J, Js, da, dd);
         ProfScope prof(kTags[pl.w - 1], s);
         sums(js != nullptr, dim3(nt, (unsigned)slices, (unsigned)pl.nz), s, (int)points, nd, ps, ng, op->k,
              dd + 3L * q0, x, J, Js, part + (size_t)s0 * nt * (2 * ng * 256));
