@@ -79,3 +79,29 @@ def test_far_field_of_every_width(nrhs, width, split):
     assert np.abs(s.cpu().numpy() - sref).max() <= 1e-11 * sref.max()
     op.close()
     m.close()
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("k", [5.0, 40.0, 3e4, 2e5])
+def test_far_field_of_large_phases(k, split):
+    """Phases k dhat . x of every quadrant, of thousands of turns, and on both
+    sides of 1e5, from where another sine is taken.  Each side rounds a phase by
+    at most 4 x 2^-53 k: 1e-12 + 2e-15 k."""
+    import paper_1803_08333_amd as rf
+    xyz, tri = synth.icosphere(2)
+    top = Topology(xyz, tri)
+    m = rf.Mesh(xyz, tri)
+    op = rf.Operator(m, k, scaling=1)
+    j, js = _currents(3, m.N, 5)
+    d = _dirs(40, 2)
+    F, s = _call(op, split, j, js, d)
+    j, js = j.cpu().numpy(), js.cpu().numpy()
+    ref = farfield.far_field(top, k, j, d)
+    if split:
+        ref = ref - farfield.far_field(top, 0.0, j, d) + farfield.far_field(top, k, js, d)
+    tol = 1e-12 + 2e-15 * k
+    assert rel(F.cpu().numpy(), ref) < tol
+    sref = farfield.rcs(k, ref, d)
+    assert np.abs(s.cpu().numpy() - sref).max() <= 10 * tol * sref.max()
+    op.close()
+    m.close()
