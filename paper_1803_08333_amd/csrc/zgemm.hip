@@ -5,7 +5,7 @@
 // FP32-path iterations) once there are enough right-hand sides that the
 // products are bound by FP64 arithmetic rather than by the matrix stream:
 // with 32 right-hand sides a pass does 192 flops per matrix entry (8 bytes),
-// where the symmetric streaming product (symv.hip) can take 4.
+// where the symmetric streaming product (symv.hip) can take 8.
 //
 // Three real products per complex one (Gauss): with M = Mr + i Mi and
 // X = Xr + i Xi,
@@ -18,10 +18,11 @@
 // that each pass over the matrix does 3 NG MFMAs per K step and 16 rows.
 //
 // A workgroup (4 waves) owns 128 rows over one K slice, a wave 32 rows in two
-// 16-row tiles.  M is symmetric and stored whole, so the operand M[i][k] is
-// read as M[k][i]: 16 neighbouring lanes take 256 contiguous bytes of row k, a
-// workgroup 1 KB (read along its own row, a lane's 16 bytes stood 64 apart and
-// every load touched 64 lines).  The accumulators live in plain VGPRs (at
+// 16-row tiles (64 and one where those would leave the chip idle, zgemm_wide).
+// M is symmetric and stored whole, so the operand M[i][k] is read as M[k][i]: 16
+// neighbouring lanes take 256 contiguous bytes of row k, a workgroup 1 KB (read
+// along its own row, a lane's 16 bytes stood 64 apart and every load touched 64
+// lines).  The accumulators live in plain VGPRs (at
 // least two waves per SIMD are asked for, else the compiler takes AGPRs).  The
 // X chunk of 32 columns sits in LDS in operand order, one 512-byte wave read
 // per operand, the next step's read while this step's products run.  Partial
@@ -35,6 +36,8 @@
 // of the matrix cores (8 FP64 operations per 12 MFMAs), the rest is the wait
 // at the chunk's barrier.  With 16 right-hand sides 1.74 ms (2.60 before), 4.3
 // TB/s of the matrix: there the stream weighs as much as the products.
+#include <type_traits>
+
 #include "internal.h"
 #include "gemm.h"
 
@@ -43,12 +46,10 @@ namespace rfcmp {
 namespace {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
-typedef float vf4 __attribute__((ext_vector_type(4)));
 
 constexpr int kZThreads = 256;
-constexpr int kZTiles = 2;                     // 16-row tiles per wave
-constexpr int kZRowsWave = 16 * kZTiles;
-constexpr int kZRows = 4 * kZRowsWave;         // rows per workgroup
+template <int TILES>
+constexpr int kZRows = 64 * TILES;             // rows per workgroup, TILES 16-row tiles a wave
 constexpr int kZK = 32;                        // K chunk
 constexpr int kZRhs = 32;                      // right-hand sides per launch (at most)
 constexpr int kZLd = 66;                       // padded lane row of a stage
@@ -90,15 +91,21 @@ __device__ inline void z_store_x(ZStage<NG>& st, const double2 (&xr)[2 * NG], in
 }
 
 // the matrix: M is symmetric, so operand row i, column k is read as M[k][i],
-// along the rows of the store: a lane takes two neighbouring operand rows
-// (one per tile), 16 lanes 256 contiguous bytes of one k.  Columns beyond the
-// slice repeat the last one (their X entries are zero).
-typedef vf4 ZFrag[kZK / 4];
-__device__ inline void z_load_m(ZFrag& av, const float2* __restrict__ src, long ld, int kc, int n, int lane) {
+// along the rows of the store: a lane takes one operand row per tile, neighbours
+// in the store, 16 lanes 256 (128 with one tile) contiguous bytes of one k.
+// Columns beyond the slice repeat the last one (their X entries are zero).
+template <int TILES>
+struct ZFrag {
+  typedef float Entries __attribute__((ext_vector_type(2 * TILES)));
+  Entries e[kZK / 4];
+};
+template <int TILES>
+__device__ inline void z_load_m(ZFrag<TILES>& av, const float2* __restrict__ src, long ld, int kc, int n, int lane) {
 #pragma unroll
   for (int e = 0; e < kZK / 4; ++e) {
     const int k = min(kc + 8 * (lane >> 4) + e, n - 1);
-    av[e] = __builtin_nontemporal_load(reinterpret_cast<const vf4*>(src + (long)k * ld));
+    av.e[e] =
+        __builtin_nontemporal_load(reinterpret_cast<const typename ZFrag<TILES>::Entries*>(src + (long)k * ld));
   }
 }
 
@@ -110,15 +117,15 @@ __device__ inline void z_operands(double (&xb)[NG][2], const ZStage<NG>& st, int
     for (int b = 0; b < 2; ++b) xb[g][b] = st.v[g][b][e][lane];
 }
 
-template <bool CONJ, int NG>
-__device__ inline void z_mfma(dbl4 (&acc)[kZTiles][NG][3], const ZFrag& av, const ZStage<NG>& st, int lane) {
+template <bool CONJ, int NG, int TILES>
+__device__ inline void z_mfma(dbl4 (&acc)[TILES][NG][3], const ZFrag<TILES>& av, const ZStage<NG>& st, int lane) {
   double xb[2][NG][2];
   z_operands<NG>(xb[0], st, 0, lane);
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     // the next step's operands leave LDS while this step's products run
     if (e + 1 < 8) z_operands<NG>(xb[(e + 1) & 1], st, e + 1, lane);
-    double mb[3][kZTiles], xs[NG][3];
+    double mb[3][TILES], xs[NG][3];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       xs[g][0] = xb[e & 1][g][0];
@@ -126,16 +133,16 @@ __device__ inline void z_mfma(dbl4 (&acc)[kZTiles][NG][3], const ZFrag& av, cons
       xs[g][2] = xs[g][0] + xs[g][1];
     }
 #pragma unroll
-    for (int a = 0; a < kZTiles; ++a) {
-      mb[0][a] = (double)av[e][2 * a];
-      mb[1][a] = CONJ ? -(double)av[e][2 * a + 1] : (double)av[e][2 * a + 1];
+    for (int a = 0; a < TILES; ++a) {
+      mb[0][a] = (double)av.e[e][2 * a];
+      mb[1][a] = CONJ ? -(double)av.e[e][2 * a + 1] : (double)av.e[e][2 * a + 1];
       mb[2][a] = mb[0][a] + mb[1][a];
     }
-    // each accumulator is taken once per step, 3 NG kZTiles instructions apart
+    // each accumulator is taken once per step, 3 NG TILES instructions apart
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
-      for (int a = 0; a < kZTiles; ++a)
+      for (int a = 0; a < TILES; ++a)
 #pragma unroll
         for (int g = 0; g < NG; ++g)
           acc[a][g][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(mb[b][a], xs[g][b], acc[a][g][b], 0, 0, 0);
@@ -144,11 +151,12 @@ __device__ inline void z_mfma(dbl4 (&acc)[kZTiles][NG][3], const ZFrag& av, cons
 }
 
 // Two chunks in flight: the loads of chunk c + 1 (matrix into registers, X
-// into the other LDS stage) are issued before the products of chunk c.  The
-// chunks run in pairs without an exit between them (a slice of an odd count
-// takes one of zeros): with one, the accumulators had two homes and were
-// copied between them.
-template <bool CONJ, int NG>
+// into the other LDS stage) are issued before the products of chunk c.  With two
+// tiles the chunks run in pairs without an exit between them (a slice of an odd
+// count takes one of zeros): with one, the accumulators had two homes and were
+// copied between them.  With one tile, whose slices are a few chunks, the chunk
+// of zeros costs more.
+template <bool CONJ, int NG, int TILES>
 __global__ __launch_bounds__(kZThreads) __attribute__((amdgpu_waves_per_eu(NG == 1 ? 3 : 2, NG == 1 ? 3 : 2)))
 void k_zgemm(const float2* __restrict__ M, int n, long ld, const double2* __restrict__ X, int nr, int kslice,
              double2* __restrict__ part) {
@@ -156,16 +164,16 @@ void k_zgemm(const float2* __restrict__ M, int n, long ld, const double2* __rest
   const int rb = blockIdx.x, ks = blockIdx.y;
   const int k_begin = ks * kslice, k_end = min(n, k_begin + kslice);
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int row0 = rb * kZRows + w * kZRowsWave;
-  const float2* src = M + min((long)row0 + 2 * (lane & 15), ld - 2);
-  dbl4 acc[kZTiles][NG][3];
+  const int row0 = rb * kZRows<TILES> + w * 16 * TILES;
+  const float2* src = M + min((long)row0 + TILES * (lane & 15), ld - TILES);
+  dbl4 acc[TILES][NG][3];
 #pragma unroll
-  for (int a = 0; a < kZTiles; ++a)
+  for (int a = 0; a < TILES; ++a)
 #pragma unroll
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int b = 0; b < 3; ++b) acc[a][g][b] = dbl4{0.0, 0.0, 0.0, 0.0};
-  ZFrag va, vb;
+  ZFrag<TILES> va, vb;
   double2 xr[2 * NG];
   z_load_m(va, src, ld, k_begin, n, lane);
   z_load_x<NG>(xr, X, n, nr, k_begin, tid);
@@ -176,26 +184,27 @@ void k_zgemm(const float2* __restrict__ M, int n, long ld, const double2* __rest
     z_load_x<NG>(xr, X, n, nr, k1, tid);
     z_load_m(vb, src, ld, k1, n, lane);
     __builtin_amdgcn_sched_barrier(0);
-    z_mfma<CONJ, NG>(acc, va, st[0], lane);
+    z_mfma<CONJ, NG, TILES>(acc, va, st[0], lane);
+    if (TILES == 1 && k1 >= k_end) break;
     z_store_x<NG>(st[1], xr, k1, k_end, nr, tid);  // waits for its loads here, after the products
     __syncthreads();                               // stage 1 written, stage 0 read
     z_load_x<NG>(xr, X, n, nr, k2, tid);
     z_load_m(va, src, ld, k2, n, lane);
     __builtin_amdgcn_sched_barrier(0);
-    z_mfma<CONJ, NG>(acc, vb, st[1], lane);
+    z_mfma<CONJ, NG, TILES>(acc, vb, st[1], lane);
     z_store_x<NG>(st[0], xr, k2, k_end, nr, tid);
     __syncthreads();  // stage 0 written, stage 1 read
   }
   // accumulator value v of lane l: operand row 4 v + l / 16 (tile a holds the
-  // wave's rows 2 i + a), right-hand side 16 g + l % 16
+  // wave's rows TILES i + a), right-hand side 16 g + l % 16
   double2* pd = part + (long)ks * kZRhs * n;
 #pragma unroll
-  for (int a = 0; a < kZTiles; ++a)
+  for (int a = 0; a < TILES; ++a)
 #pragma unroll
     for (int g = 0; g < NG; ++g)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = row0 + 2 * (4 * v + (lane >> 4)) + a;
+        const int row = row0 + TILES * (4 * v + (lane >> 4)) + a;
         const int r = 16 * g + (lane & 15);
         const double p1 = acc[a][g][0][v], p2 = acc[a][g][1][v], p3 = acc[a][g][2][v];
         if (row < n && r < nr) pd[(long)r * n + row] = make_double2(p1 - p2, p3 - p1 - p2);
@@ -227,6 +236,18 @@ int zgemm_slices(int64_t n) {
   return (int)std::min<int64_t>(16, std::max<int64_t>(1, (3840 + rbs / 2) / rbs));
 }
 
+// Two tiles a wave, or one where the launch leaves compute units short: by the
+// chunks that the fullest compute unit walks (pairs of them with two tiles, each
+// of twice the rows), one tile at 1.15 times its share (with nearly equal ones it
+// is 3 to 7 % slower: n = 7680 237 us to 222, 10 368 411 to 397).  The same bits either way.  With 32 right-hand
+// sides n = 320: 13.6 us with one tile, 15.8 with two; 480 13.5 and 17.1; 2352 41
+// and 54; 4608 99 and 112; 4056, where the shares are equal, 75 and 69.
+bool zgemm_wide(int64_t n, int kslice, int nsl) {
+  auto share = [&](int64_t rows) { return ((n + rows - 1) / rows * nsl + 255) / 256; };
+  const int64_t chunks = kslice / kZK;
+  return 2.0 * (chunks + chunks % 2) * share(kZRows<2>) <= 1.15 * chunks * share(kZRows<1>);
+}
+
 }  // namespace
 
 size_t zgemm_scratch_bytes(int64_t n) { return sizeof(double2) * (size_t)zgemm_slices(n) * kZRhs * (size_t)n; }
@@ -245,12 +266,18 @@ rfcmp_status zgemm_c64(const float2* M, int64_t n, int64_t ld, bool conj, const 
   const int ns = zgemm_slices(n);
   const int kslice = (int)(((n + ns - 1) / ns + kZK - 1) / kZK * kZK);
   const int nsl = (int)((n + kslice - 1) / kslice);
-  const dim3 grid((unsigned)((n + kZRows - 1) / kZRows), (unsigned)nsl);
+  const bool wide = zgemm_wide(n, kslice, nsl);
+  const int64_t rows = wide ? kZRows<2> : kZRows<1>;
+  const dim3 grid((unsigned)((n + rows - 1) / rows), (unsigned)nsl);
   double2* part = static_cast<double2*>(scratch);
   for (int r0 = 0; r0 < nrhs; r0 += kZRhs) {
     const int nr = std::min(kZRhs, nrhs - r0);
     ProfScope prof(profile_tag_suffix(tag, nr), s);
-    auto kern = conj ? (nr > 16 ? k_zgemm<true, 2> : k_zgemm<true, 1>) : (nr > 16 ? k_zgemm<false, 2> : k_zgemm<false, 1>);
+    auto pick = [&](auto c) {
+      constexpr bool C = decltype(c)::value;
+      return nr > 16 ? (wide ? k_zgemm<C, 2, 2> : k_zgemm<C, 2, 1>) : (wide ? k_zgemm<C, 1, 2> : k_zgemm<C, 1, 1>);
+    };
+    const auto kern = conj ? pick(std::true_type()) : pick(std::false_type());
     hipLaunchKernelGGL(kern, grid, dim3(kZThreads), 0, s, M, (int)n, (long)ld, X + (long)r0 * n, nr, kslice, part);
     hipLaunchKernelGGL(k_zgemm_sum, dim3((unsigned)(((long)nr * n + 255) / 256)), dim3(256), 0, s, part, (int)n, nr,
                        nsl, Y + (long)r0 * n);
