@@ -926,10 +926,14 @@ void spchol_arrays(const SpFactor& F, SpArrays& a) {
   int nsub = 0;
   for (int q = 0; q < nsn; ++q) {
     if (!bottom[q] || (F.parent[q] >= 0 && bottom[F.parent[q]])) continue;
-    // q roots a subtree: its supernodes are those in q's column range
-    std::vector<int> members;
-    for (int p = 0; p <= q; ++p)
-      if (F.col0[p] >= first[q] && F.col0[p + 1] <= F.col0[q + 1]) members.push_back(p);
+    // q roots a subtree: itself and its descendants (its column range can hold
+    // more: a part of the dissection that no separator's row reaches hangs
+    // below a later supernode, and is a subtree of its own or in the top)
+    std::vector<int> members{q};
+    for (size_t i = 0; i < members.size(); ++i)
+      members.insert(members.end(), F.child_idx.begin() + F.child_off[members[i]],
+                     F.child_idx.begin() + F.child_off[members[i] + 1]);
+    std::sort(members.begin(), members.end());
     int hmax = 0;
     for (int p : members) hmax = std::max(hmax, F.height[p]);
     a.sub_lvl.push_back((int)a.sub_nodes.size());
@@ -1008,6 +1012,10 @@ rfcmp_status spchol_upload(const SpFactor& F, SpDevice& D, hipStream_t s) {
       a.l21_off[nsn] > INT32_MAX) {
     set_error("spchol_upload: factor blocks beyond 32-bit offsets");
     return RFCMP_E_ARG;
+  }
+  if ((int)(a.sub_nodes.size() + a.top_nodes.size()) != nsn) {
+    set_error("spchol_upload: %zu bottom and %zu top supernodes of %d", a.sub_nodes.size(), a.top_nodes.size(), nsn);
+    return RFCMP_E_STATE;
   }
   D.n = n;
   D.nsn = nsn;
