@@ -583,7 +583,6 @@ __device__ void wave_backward(const SpArg& A, const SpStage<ROWS>& st, int4 d0, 
 // gather indices (`idx` ints, a multiple of 4).
 constexpr int kSpBottomWaves = 8;
 constexpr int kSpBottomMinWaves = 3;
-constexpr int kSpBottomTarget = 512;
 __host__ __device__ inline int sp_slice(int R, int vec, int fac, int idx) { return vec * R + fac / 2 + idx / 4; }
 template <int ROWS, bool backward>
 __global__ void __launch_bounds__(64 * kSpBottomWaves)
@@ -748,22 +747,44 @@ rfcmp_status spsolve_jobs(const SpSolveJob* jobs, int njobs, int nrhs, hipStream
     ntile = std::max(ntile, a.ntile);
     grounded = grounded || F.grounded;
   }
-  // bottom: about kSpBottomTarget workgroups, each of up to kSpBottomWaves
-  // waves and at least kSpBottomMinWaves where their slices fit 64 KB; the
-  // rows per lane from the widest bottom supernode
+  // bottom: right-hand sides and waves per workgroup (a right-hand side's sums
+  // do not depend on either), by the steps that a wave of the fullest compute
+  // unit walks.  The kernels' registers leave a compute unit 8 waves, two of
+  // each SIMD: a second round of workgroups of 5 to 8 waves doubles the time,
+  // where two of 3 or 4 run side by side.  At level 5 (128 subtrees) the
+  // Laplacian's solve with 6 right-hand sides takes 206 us with 4 a workgroup,
+  // 237 with 2 and 272 with 1; at level 6 (244) 467 with 4, 536 with 8, 615 with
+  // 2; with 32 at level 5 243 us with 8 a workgroup of 4 waves, 275 of 6.
   int Rb = 1, W = 1, rows = 1;
   int64_t slice = 0;
   if (nsub > 0) {
-    while (Rb < 16 && (int64_t)nrhs * nsub >= (int64_t)2 * Rb * kSpBottomTarget) Rb *= 2;
-    while (Rb > 1 && (int64_t)kSpBottomMinWaves * sp_slice(Rb, blds, bfac, bidx) * (int64_t)sizeof(double2) > 65536)
-      Rb /= 2;
-    slice = sp_slice(Rb, blds, bfac, bidx);
-    if (slice * (int64_t)sizeof(double2) > 65536) {
+    double least = 0.0;
+    for (int R = 1; R <= 16; R *= 2) {
+      const int64_t sl = sp_slice(R, blds, bfac, bidx), bytes = sl * (int64_t)sizeof(double2);
+      if (R == 1 ? bytes > 65536 : kSpBottomMinWaves * bytes > 65536) break;
+      int rw = 1;
+      while (rw * (64 / R) < bncol) rw *= 2;
+      int64_t groups = 0;
+      for (int q = 0; q < njobs; ++q) groups += (int64_t)jobs[q].F->nsub * ((args.a[q].nrhs + R - 1) / R);
+      const int64_t most = (groups + 255) / 256;
+      for (int w = (int)std::min<int64_t>(kSpBottomWaves, 65536 / bytes); w >= (R == 1 ? 1 : kSpBottomMinWaves); --w) {
+        const int side = (int)std::max<int64_t>(1, std::min<int64_t>(kSpBottomWaves / w, 163840 / (w * bytes)));
+        // rows of a lane beyond the first ones cost little of a step
+        const double step = rw == 1 ? 1.0 : rw == 2 ? 1.05 : rw == 4 ? 1.1 : 1.5;
+        const double cost = std::max(1.0, (double)most / side) * step / w;
+        if (slice == 0 || cost < least) {
+          least = cost;
+          Rb = R;
+          W = w;
+          rows = rw;
+          slice = sl;
+        }
+      }
+    }
+    if (slice == 0) {
       set_error("spsolve: a front of %d entries does not fit the LDS", blds);
       return RFCMP_E_STATE;
     }
-    W = (int)std::min<int64_t>(kSpBottomWaves, 65536 / (slice * (int64_t)sizeof(double2)));
-    while (rows * (64 / Rb) < bncol) rows *= 2;
   }
   // top: per height, about 256 workgroups
   std::vector<int> Rt(ntop), nodes(ntop), need(ntop);
