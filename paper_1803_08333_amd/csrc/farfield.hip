@@ -266,7 +266,7 @@ void k_ff_sum(int P, int ndir, int ps, int ng, double kk, const double* __restri
 // lines.
 constexpr int kFfParts = 5, kFfSums = 2 * kFfDirs * 6;
 template <int R>
-constexpr int kFfAhead = R == 1 ? 8 : 2;  // slices in flight
+constexpr int kFfAhead = R == 1 ? 16 : 2;  // slices in flight
 template <int R>
 __global__ __launch_bounds__(kFfParts * kFfSums) void k_ff_finish(int ndir, int nr, int ng, int nslice, double kk,
                                                                   const double* __restrict__ dirs,
