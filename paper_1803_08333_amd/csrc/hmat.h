@@ -91,15 +91,17 @@ struct HmMesh {
   DevBuf perm_e, perm_c, iperm_c, cell_start;
   DevBuf et_ptr, et_cell, et_rows, home;
   DevBuf dense_ij;          // int2 [ndense]: tile pairs I <= J
-  DevBuf vd_off;            // int64 [ndense]: offsets of the dense V blocks
+  DevBuf vd_off;            // int64 [ndense]: offsets of the dense V blocks, on the host in vd_host
+  std::vector<long> vd_host;
   int64_t vd_total = 0;     // complex entries of the dense V blocks
   DevBuf lrA, lrV;          // HmLr [nlr] in edge and in cell positions
   // per tile, the blocks its rows meet, in a fixed order: code 4 b + kind,
   // kind 0: dense block b with I = tile, 1: dense block b with J = tile and
   // I < J (its transpose), 2: low-rank block b with the tile in its rows,
-  // 3: the same with the tile in its columns (the transpose)
-  DevBuf list_ptr, list_ent;
-  std::vector<int> list_host;  // list_ent on the host
+  // 3: the same with the tile in its columns (the transpose); resolved per
+  // operator into HmEnt
+  DevBuf list_ptr;
+  std::vector<int> list_host;
 };
 
 // The compressed blocks of one operator.

@@ -669,9 +669,9 @@ rfcmp_status hm_mesh_setup(rfcmp_mesh m, hipStream_t s) {
   RF_TRY(upload(H->lrA, la, s));
   RF_TRY(upload(H->lrV, lv, s));
   RF_TRY(upload(H->list_ptr, lp, s));
-  RF_TRY(upload(H->list_ent, le, s));
   RF_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
   H->list_host = std::move(le);
+  H->vd_host = std::move(voff);
   m->hm = std::move(H);
   return RFCMP_OK;
 }
@@ -687,12 +687,6 @@ rfcmp_status hm_aca(rfcmp_op op, hipStream_t s) {
   P.unconverged = 0;
   std::vector<long> zoff_all[2];
   int64_t zw_need = 0;
-  std::vector<long> vd_off(t.dense_I.size());  // offsets of the dense V blocks
-  for (size_t b = 0, o = 0; b < vd_off.size(); ++b) {
-    vd_off[b] = (long)o;
-    o += (size_t)(t.cell_start[t.dense_I[b] + 1] - t.cell_start[t.dense_I[b]]) *
-         (size_t)(t.cell_start[t.dense_J[b] + 1] - t.cell_start[t.dense_J[b]]);
-  }
   for (int kind = 0; kind < 2; ++kind) {
     std::vector<HmLr> blk(nlr);
     for (int64_t b = 0; b < nlr; ++b) {
@@ -826,7 +820,7 @@ rfcmp_status hm_aca(rfcmp_op op, hipStream_t s) {
         const int qI = kind == 0 ? I * kEdgeTile : t.cell_start[I], qJ = kind == 0 ? J * kEdgeTile : t.cell_start[J];
         const int nI = kind == 0 ? (int)std::min<int64_t>(kEdgeTile, t.N - qI) : t.cell_start[I + 1] - qI;
         const int nJ = kind == 0 ? (int)std::min<int64_t>(kEdgeTile, t.N - qJ) : t.cell_start[J + 1] - qJ;
-        E.F = kind == 0 ? P.TAd.as<float2>() + (long)b * kEdgeTile * kEdgeTile : P.Vd.as<float2>() + vd_off[b];
+        E.F = kind == 0 ? P.TAd.as<float2>() + (long)b * kEdgeTile * kEdgeTile : P.Vd.as<float2>() + H.vd_host[b];
         E.start = rows ? qJ : qI;
         E.k = rows ? nJ : nI;
         E.len = kind == 0 ? kEdgeTile : nJ;

@@ -250,7 +250,7 @@ struct rfcmp_op_s {
   double alpha = 0, beta = 0, gamma = 0;
   double lam[3] = {0, 0, 0};
   int64_t ldA = 0, ldV = 0;  // leading dims (complex entries) of T_A and V
-  rfcmp::DevBuf TA;          // float2 [N][ldA], block upper triangle (kTriBlock)
+  rfcmp::DevBuf TA;          // float2 [N][ldA], whole (both triangles)
   rfcmp::DevBuf Vb;          // float2 [C][ldV]
   rfcmp::DevBuf work;        // complex128 workspace for work_nrhs right-hand sides
   int work_nrhs = 0;

@@ -161,7 +161,7 @@ rfcmp_status alloc_symv_scratch(rfcmp_op op) {
 
 // ------------------------------------------------------------------ dense products
 // The five dense matrices of the operator.  In complex64/FP64 each product is
-// a symmetric streaming pass (<= 4 right-hand sides per pass) whose input is
+// a symmetric streaming pass (<= 8 right-hand sides per pass) whose input is
 // formed while it is staged (plain vector, Sigma^T / Lambda^T gather, or a
 // fused operator line); two independent products of the same element type
 // share one launch.  As BF16x3 MFMA products (<= 64 right-hand sides per

@@ -63,23 +63,24 @@ __device__ inline double2 wave_sum(double2 v) {
   return v;
 }
 
-// Lanes of a team of T over R right-hand sides (R a power of two <= 16):
-// lane t serves right-hand side r = t mod R; G lanes (ids R apart, in one
-// wave) split each sum; S = T / (R G) rows are formed at once.  G is the
+// Lanes of a workgroup of T = kSpThreads over R right-hand sides (R a power of
+// two <= 16): lane t serves right-hand side r = t mod R; G lanes (ids R apart,
+// in one wave) split each sum; S = T / (R G) rows are formed at once.  G is the
 // largest power of two with R G <= 64 and rows R G <= T.
 struct Lanes {
   int r, g, slot, G, S;
 };
-__device__ inline Lanes lanes_of(int t, int T, int R, int rows) {
+constexpr int kSpThreads = 1024;
+__device__ inline Lanes lanes_of(int t, int R, int rows) {
   int G = 1;
-  while (R * G * 2 <= 64 && rows * R * G * 2 <= T) G *= 2;
+  while (R * G * 2 <= 64 && rows * R * G * 2 <= kSpThreads) G *= 2;
   Lanes l;
   l.G = G;
   l.r = t & (R - 1);
   const int q = t / R;
   l.g = q & (G - 1);
   l.slot = q / G;
-  l.S = T / (R * G);
+  l.S = kSpThreads / (R * G);
   return l;
 }
 __device__ inline double2 group_sum(double2 v, int R, int G) {
@@ -116,8 +117,7 @@ __device__ inline double2 strided_dot(const double* __restrict__ M, int ld, int 
 
 // Forward step of a supernode (descriptor d0 = {col0, ncol, str_off, nstr},
 // d1 = {front_off, linv_off, l21_off, 0}) for right-hand sides r0 .. r0+R-1
-// on a team of TEAM lanes; lds: (2 ncol + nstr) R entries.
-template <int TEAM>
+// on a workgroup of kSpThreads; lds: (2 ncol + nstr) R entries.
 __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int r0, double2* lds) {
   const int NR = A.nrhs;
   double2* x = A.scratch;
@@ -130,7 +130,7 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
      // plus the children's update entries
     const int r = t & (R - 1), rg = r0 + r;
     const double2 mu = (A.grounded && rg < NR) ? A.mean(0)[rg] : make_double2(0.0, 0.0);
-    for (int p = t / R; p < m; p += TEAM / R) {
+    for (int p = t / R; p < m; p += kSpThreads / R) {
       double2 val = make_double2(0.0, 0.0);
       if (rg < NR) {
         if (p < ncol) {
@@ -156,7 +156,7 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
   }
   team_sync();
   {  // y_i = (L_ss^-1 v)_i: columns j <= i
-    const Lanes L = lanes_of(t, TEAM, R, ncol);
+    const Lanes L = lanes_of(t, R, ncol);
     const double* M = A.linv + d1.y;
     const int rg = r0 + L.r;
     for (int base = 0; base < ncol; base += L.S) {
@@ -170,7 +170,7 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
   }
   team_sync();
   {  // u_q = v_(ncol + q) - (L_21 y)_q
-    const Lanes L = lanes_of(t, TEAM, R, nstr);
+    const Lanes L = lanes_of(t, R, nstr);
     const double* M = A.l21 + d1.z;
     const int rg = r0 + L.r;
     for (int base = 0; base < nstr; base += L.S) {
@@ -188,7 +188,6 @@ __device__ void node_forward(const SpArg& A, int4 d0, int4 d1, int t, int R, int
 // Backward step of a supernode: x_s = L_ss^-T (y - L_21^T x_struct).
 // ylds: y as the forward step left it in LDS (a root, right after its
 // forward step), else null (y read from x).
-template <int TEAM>
 __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, int r0, double2* lds,
                               const double2* ylds = nullptr) {
   const int NR = A.nrhs;
@@ -198,12 +197,12 @@ __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, in
   double2* z = lds + nstr * R;    // z [ncol][R]
   {
     const int r = t & (R - 1), rg = r0 + r;
-    for (int q = t / R; q < nstr; q += TEAM / R)
+    for (int q = t / R; q < nstr; q += kSpThreads / R)
       xs[q * R + r] = rg < NR ? x[(long)A.str[so + q] * NR + rg] : make_double2(0.0, 0.0);
   }
   team_sync();
   {  // z_j = y_j - (L_21^T x_struct)_j
-    const Lanes L = lanes_of(t, TEAM, R, ncol);
+    const Lanes L = lanes_of(t, R, ncol);
     const double* M = A.l21t + d1.z;  // (q, j) at M[q * ncol + j]
     const int rg = r0 + L.r;
     for (int base = 0; base < ncol; base += L.S) {
@@ -217,7 +216,7 @@ __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, in
   }
   team_sync();
   {  // x_i = (L_ss^-T z)_i: rows j >= i
-    const Lanes L = lanes_of(t, TEAM, R, ncol);
+    const Lanes L = lanes_of(t, R, ncol);
     const double* M = A.linvt + d1.y;  // (i, j) of L_ss^-T at M[j * ncol + i]
     const int rg = r0 + L.r;
     for (int base = 0; base < ncol; base += L.S) {
@@ -230,7 +229,6 @@ __device__ void node_backward(const SpArg& A, int4 d0, int4 d1, int t, int R, in
   team_sync();
 }
 
-constexpr int kSpThreads = 1024;
 constexpr int kSpTileR = 16;  // right-hand sides per workgroup of the permutation kernels
 static_assert(kSpTile * kSpTileR == kSpThreads, "one permutation tile per workgroup");
 
@@ -671,12 +669,12 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_top(const SpArgs args, int le
   extern __shared__ double2 lds[];
   const int4 d0 = A.top_desc[2 * k], d1 = A.top_desc[2 * k + 1];
   if (backward == 0) {
-    node_forward<kSpThreads>(A, d0, d1, threadIdx.x, R, r0, lds);
+    node_forward(A, d0, d1, threadIdx.x, R, r0, lds);
   } else if (backward == 1) {
-    node_backward<kSpThreads>(A, d0, d1, threadIdx.x, R, r0, lds);
+    node_backward(A, d0, d1, threadIdx.x, R, r0, lds);
   } else {  // a root: the forward step leaves y at lds + ncol R, past the z the backward step writes
-    node_forward<kSpThreads>(A, d0, d1, threadIdx.x, R, r0, lds);
-    node_backward<kSpThreads>(A, d0, d1, threadIdx.x, R, r0, lds, lds + d0.y * R);
+    node_forward(A, d0, d1, threadIdx.x, R, r0, lds);
+    node_backward(A, d0, d1, threadIdx.x, R, r0, lds, lds + d0.y * R);
   }
 }
 

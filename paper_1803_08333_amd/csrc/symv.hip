@@ -356,16 +356,16 @@ __global__ __launch_bounds__(kThreads) void k_symv(const JobsArg args) {
 // whichever others go with it.
 //
 // A workgroup of four waves owns a block.  It walks stages of 32 KB (32 rows at
-// S = 128, 16 at S = 256), two in flight: a wave loads its S / 4 columns (four
-// rows a load, in operand order: lane l takes column pair l % 16 of row
-// l / 16), takes the transposed sums M^T x_P straight from the registers
-// (tiles of 16 columns by G row groups), and stores the stage to LDS, from where it forms four of the
-// chains of 16 rows of M x_Q.  For complex64 K holds (im, re) of two entries;
-// in the transposed sums an exchange between neighbouring rows of 16 lanes
-// turns a load into the operands of its first and its last two rows.  x sits
-// in LDS as [entry][right-hand side][re, im], the right-hand sides of an entry
-// exchanged by its number, so that neither the stores nor the operand reads
-// meet in a bank.
+// S = 128, 16 at S = 256), one in flight while the one before is in LDS: a wave
+// loads its S / 4 columns (four rows a load, in operand order: lane l takes
+// column pair l % 16 of row l / 16), takes the transposed sums M^T x_P straight
+// from the registers (tiles of 16 columns by G row groups), and stores the stage
+// to LDS, from where it forms four of the chains of 16 rows of M x_Q.  For
+// complex64 K holds (im, re) of two entries; in the transposed sums an exchange
+// between neighbouring rows of 16 lanes turns a load into the operands of its
+// first and its last two rows.  x sits in LDS as [entry][right-hand side][re,
+// im], the right-hand sides of an entry exchanged by its number, so that neither
+// the stores nor the operand reads meet in a bank.
 //
 // Bound: with FP64 entries the stream (8 right-hand sides do 32 flops a byte
 // at half the rate of the matrix cores), with complex64 the matrix cores,
