@@ -182,8 +182,8 @@ TRAFFIC = {
                     "sha256": "3a9a7ba3393dd629b05455a8cc041999b61ce68e136862d80d6a7ab277421e29",
                     "kib": (3757058.1, 30720.0)},
         "zgemm_ta_nr32": {"source": "paper_1803_08333_amd/csrc/zgemm.hip",
-                          "sha256": "b5f856e59a01fc02f110ca81f0a7fd3222a02a45e215f68d6185ebfe4d609512",
-                          "kib": (3822829.9, 137082.6)},
+                          "sha256": "f784217654e603cdc519c3f949acfddbeb52eb1b0217dff1a3bd8bae70fcf14f",
+                          "kib": (3822698.1, 135036.3)},
     },
 }
 
