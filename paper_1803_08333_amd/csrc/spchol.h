@@ -81,9 +81,9 @@ constexpr int kSpTile = 64;
 //
 // The supernodes split into bottom subtrees (every supernode whose subtree
 // spans at most about n/96 columns and holds only supernodes whose blocks
-// have at most 1024 entries, grouped under the highest such supernodes) and
-// the top supernodes above them.  A solve is a short chain of
-// launches, each over many workgroups (and right-hand sides):
+// have at most 1024 entries, grouped with their descendants under the highest
+// such supernodes) and the top supernodes above them.  A solve is a short chain
+// of launches, each over many workgroups (and right-hand sides):
 //   input: the right-hand side formed (the operator's gathers) and permuted,
 //     a tile of entries by 16 right-hand sides per workgroup, transposed
 //     through LDS (for the Laplacian also its partial sums, then their mean);
@@ -106,8 +106,8 @@ constexpr int kSpTile = 64;
 // step forms z = y - L_21^T x_struct and x = L_ss^-T z.  Every matrix is stored
 // column- and row-major, so that each step reads it with neighbouring lanes at
 // neighbouring addresses.  A workgroup takes R right-hand sides at once (R
-// chosen per launch from the grid it gives and the LDS its fronts need): each
-// matrix entry it loads serves all R.
+// chosen per launch, at the bottom together with its waves from what a compute
+// unit holds of them): each matrix entry it loads serves all R.
 struct SpDevice {
   int n = 0, nsn = 0, grounded = 0;
   int max_front = 0, max_ncol = 0;

@@ -340,7 +340,8 @@ __global__ void __launch_bounds__(kSpThreads) k_sp_output(const SpArgs args) {
 // (n = 20480, 128 subtrees of up to 9 steps a wave) the forward sweep takes
 // 65 us and the backward one 48 (75 and 75 with the blocks loaded at the start
 // of their own step and every ordering of LDS waiting for the stores); at level
-// 6 with 8 right-hand sides 200 and 184 (250 and 214).
+// 6 with 8 right-hand sides 86 and 72 (166 and 158 in two rounds of workgroups,
+// see spsolve_jobs).
 constexpr int kSpStageMax = 1024;
 constexpr int kSpIdxMax = 256;
 __host__ __device__ inline bool sp_staged(int ncol, int nstr, int K) {
